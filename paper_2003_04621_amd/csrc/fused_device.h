@@ -20,11 +20,8 @@
 namespace ptsg {
 
 
-// 2D samples of 64 rows with one row per word get the in-register Houdayer
-// move (one row per lane).
-__host__ __device__ inline bool rows64_houdayer(const Geo& g) {
-  return g.d == 2 && g.NW == 64 && g.P == 1;
-}
+// 2D samples get the in-register Houdayer move (one row per lane: L <= 64).
+__host__ __device__ inline bool rows_houdayer(const Geo& g) { return g.d == 2; }
 
 // ---------------------------------------------------------------------------
 // Wave-level helpers.  Lanes of one wavefront exchange data through LDS; the
@@ -436,13 +433,15 @@ __device__ __forceinline__ bool grow_pair(const Geo& g, uint32_t* C, const uint3
 }
 
 // ---------------------------------------------------------------------------
-// Column fills for a square lattice of 64 rows held one row per lane (2D,
-// L = 64: one field per word, word = row).  The even sites of row r have
-// colour r & 1, and the site above bit b of row r's even-site word is bit b
-// of row r + 1's even-site word (likewise for the odd sites), so the chain
-// X_r = even-site word of row r (and Y, the odd-site words) links equal bits
-// of consecutive lanes, periodically (lane 63 to lane 0).  Filling a chain
-// from its cluster bits through its q bits is a scan with the associative
+// Column fills for a square lattice held one row per lane (2D: L <= 64 rows).
+// The even sites of row r have colour r & 1, and the site above bit b of row
+// r's even-site word is bit b of row r + 1's even-site word (likewise for the
+// odd sites), so the chain X_r = even-site word of row r (and Y, the odd-site
+// words) links equal bits of consecutive lanes, periodically (lane L - 1 to
+// lane 0).  The lanes past the last row take part as transparent ones (every
+// bit of q set, none of c): what reaches lane L - 1 passes through them to
+// lane 63 and wraps, so that every L runs the same 64-lane scans.  Filling a
+// chain from its cluster bits through its q bits is a scan with the associative
 // operator (q1, c1) then (q2, c2) -> (q1 & q2, c2 | (q2 & c1)).  Upward it
 // runs over rows of 16 lanes by DPP row shifts and then across rows by the
 // DPP broadcasts of lanes 15 and 31; downward by row shifts and then across
@@ -535,17 +534,81 @@ __device__ __forceinline__ void rank_in_row64(uint32_t E, uint32_t O, uint32_t m
   SO = even ? 0u : 1u << b;
 }
 
-// The Houdayer cluster of pair k of a 2D sample with 64 rows (L = 64), one
-// row per lane, everything in registers: overlap, seed (the m-th q = -1 site
-// in site order, by a scan over lanes), flood fill alternating column fills
-// and row closures until one of them adds nothing.  False (for the whole
+// x as a value that the compiler cannot hoist: what derives from it (masks,
+// addresses) is recomputed where it is used instead of staying live in
+// registers through the rest of the step loop.
+__device__ __forceinline__ int recomputed(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
+// Geometry of a 2D row held by itself in a word's low H bits.
+__device__ __forceinline__ Geo row_geo(const Geo& g) {
+  Geo r = g;
+  r.P = 1;
+  r.B = g.L;
+  r.LB = 1u;
+  r.HB = 1u << (g.H - 1);
+  r.maskW = g.maskH;
+  return r;
+}
+
+// A lane's row of a 2D lattice (lanes past the last row hold none): its word
+// and field shift, whether it exists, and the lanes of the next and previous
+// rows (periodic).  LS = 64: row = word = lane.
+struct LaneRow {
+  int w, sh, next, prev;
+  bool valid;
+};
+template <int LS>
+__device__ __forceinline__ LaneRow lane_row(const Geo& g, int lane) {
+  LaneRow r;
+  if constexpr (LS == 64) {
+    r.w = lane;
+    r.sh = 0;
+    r.next = r.prev = lane;  // unused: the wavefront rotates
+    r.valid = true;
+  } else {
+    r.valid = lane < g.L;
+    const int R = r.valid ? lane : 0, f = R / g.B;
+    r.w = R - f * g.B;
+    r.sh = f * g.H;
+    r.next = !r.valid ? lane : lane == g.L - 1 ? 0 : lane + 1;
+    r.prev = !r.valid ? lane : lane == 0 ? g.L - 1 : lane - 1;
+  }
+  return r;
+}
+// The row's field of word x (0 for a lane without a row).
+template <int LS>
+__device__ __forceinline__ uint32_t row_field(const Geo& g, const LaneRow& r, uint32_t x) {
+  if constexpr (LS == 64) return x;
+  return r.valid ? (x >> r.sh) & g.maskH : 0u;
+}
+// The next / previous row's value of x.
+template <int LS>
+__device__ __forceinline__ uint32_t row_next(const LaneRow& r, uint32_t x) {
+  if constexpr (LS == 64) return dpp_ones<kWaveRol1>(x);  // lane 63 takes lane 0
+  return (uint32_t)__builtin_amdgcn_ds_bpermute(4 * r.next, (int)x);
+}
+template <int LS>
+__device__ __forceinline__ uint32_t row_prev(const LaneRow& r, uint32_t x) {
+  if constexpr (LS == 64) return dpp_ones<kWaveRor1>(x);
+  return (uint32_t)__builtin_amdgcn_ds_bpermute(4 * r.prev, (int)x);
+}
+
+// The Houdayer cluster of pair k of a 2D sample, one row per lane, everything
+// in registers: overlap, seed (the m-th q = -1 site in site order, by a scan
+// over lanes), flood fill alternating column fills and row closures until one
+// of them adds nothing.  g is the row geometry.  False (for the whole
 // wavefront) if the pair has no q = -1 site; else c0, c1 are the cluster's
-// colour-0 and colour-1 words of this lane's row.
-__device__ __forceinline__ bool rows64_cluster(const Geo& g, const uint32_t* Wa, const uint32_t* Wb,
-                                               int s, int k, uint32_t v, int lane, uint32_t& c0,
-                                               uint32_t& c1) {
+// colour-0 and colour-1 fields of this lane's row.
+template <int LS>
+__device__ __forceinline__ bool rows_cluster(const Geo& g, const LaneRow& lr, int NW, const uint32_t* Wa,
+                                             const uint32_t* Wb, int s, int k, uint32_t v, int lane,
+                                             uint32_t& c0, uint32_t& c1) {
   const bool odd = lane & 1;  // parity of the row = colour of its even sites
-  const uint32_t q0 = Wa[lane] ^ Wb[lane], q1 = Wa[64 + lane] ^ Wb[64 + lane];
+  const uint32_t q0 = row_field<LS>(g, lr, Wa[lr.w] ^ Wb[lr.w]);
+  const uint32_t q1 = row_field<LS>(g, lr, Wa[NW + lr.w] ^ Wb[NW + lr.w]);
   const uint32_t qx = odd ? q1 : q0, qy = odd ? q0 : q1;
   // q = -1 sites up to and including this row (a DPP scan over the rows)
   const uint32_t lc = __popc(q0) + __popc(q1);
@@ -566,9 +629,14 @@ __device__ __forceinline__ bool rows64_cluster(const Geo& g, const uint32_t* Wa,
   if (m >= incl - lc && m < incl) rank_in_row64(qx, qy, m - (incl - lc), X, Y);
   const uint32_t rqx = __builtin_bitreverse32(qx), rqy = __builtin_bitreverse32(qy);
   row_closure(g, X, Y, qx, qy, rqx, rqy);
-  const ColumnChain hx = column_chain(qx, lane), hy = column_chain(qy, lane);
+  const uint32_t clear = lr.valid ? 0u : ~0u;  // transparent lanes of the column scans
+  const ColumnChain hx = column_chain(qx | clear, lane), hy = column_chain(qy | clear, lane);
   for (;;) {
     uint32_t nx = column_fill(hx, X), ny = column_fill(hy, Y);
+    if constexpr (LS != 64) {
+      nx &= ~clear;
+      ny &= ~clear;
+    }
     if (!__any(nx != X || ny != Y)) break;
     X = nx;
     Y = ny;
@@ -582,6 +650,30 @@ __device__ __forceinline__ bool rows64_cluster(const Geo& g, const uint32_t* Wa,
   return true;
 }
 
+// Exchanges the pair's replicas on the cluster fields c0, c1 of this lane's
+// row; ab: the row's words before the move (replica a's colours, then b's;
+// read by the whole-word form only).
+template <int LS>
+__device__ __forceinline__ void rows_exchange(const LaneRow& lr, int NW, uint32_t* Wa, uint32_t* Wb,
+                                              const uint32_t (&ab)[4], uint32_t c0, uint32_t c1) {
+  if constexpr (LS == 64) {
+    Wa[lr.w] = ab[0] ^ c0;
+    Wa[64 + lr.w] = ab[1] ^ c1;
+    Wb[lr.w] = ab[2] ^ c0;
+    Wb[64 + lr.w] = ab[3] ^ c1;
+  } else {
+    // rows that share a word write only their own bits
+    if (c0) {
+      atomicXor(&Wa[lr.w], c0 << lr.sh);
+      atomicXor(&Wb[lr.w], c0 << lr.sh);
+    }
+    if (c1) {
+      atomicXor(&Wa[NW + lr.w], c1 << lr.sh);
+      atomicXor(&Wb[NW + lr.w], c1 << lr.sh);
+    }
+  }
+}
+
 // The next pair of the Houdayer phase for this wavefront, from the hottest
 // down (clusters grow larger and take more passes at high temperature), each
 // to the next free wavefront; -1 when none is left.  Every lane adds 1 (one
@@ -593,53 +685,57 @@ __device__ __forceinline__ int take_pair_hottest(uint32_t* hctr, int NT) {
   return i >= (uint32_t)NT ? -1 : NT - 1 - (int)i;
 }
 
-// Houdayer moves of a 2D sample with 64 rows (L = 64), one wavefront per
-// pair at a time and one row per lane (rows64_cluster), then the energy
-// change from the bonds leaving the cluster (vertical neighbours taken from
-// the adjacent lanes) and the exchange on the cluster.
-__device__ __forceinline__ void houdayer_rows64(const Geo& g, uint32_t* W, const uint32_t* Jl,
-                                                int32_t* El, const int32_t* sotl, int s, uint32_t v,
-                                                uint32_t* hctr, int lane) {
-  const int NT = g.NT;
+// Houdayer moves of a 2D sample, one wavefront per pair at a time and one row
+// per lane (rows_cluster), then the energy change from the bonds leaving the
+// cluster (vertical neighbours taken from the adjacent rows' lanes) and the
+// exchange on the cluster.  gw is the sample's geometry (LS = 64: folded).
+// Any L <= 64 has at most one row per lane, so no 2D shape needs LDS for its
+// cluster; bound by the VALU work of the fills (about 8 rounds of two column
+// fills and a closure per hot pair).  Against the flood fill through LDS words
+// that every L < 64 took before, whole steps: L = 50, 77 samples x 2 x 13:
+// 62.6 -> 21.4 us; L = 50, 500 x 2 x 24: 172 -> 63 us; L = 32, 77 x 2 x 13:
+// 38.4 -> 14.8 us.
+template <int LS>
+__device__ __forceinline__ void houdayer_rows(const Geo& gw, uint32_t* W, const uint32_t* Jl, int32_t* El,
+                                              const int32_t* sotl, int s, uint32_t v, uint32_t* hctr,
+                                              int lane) {
+  const Geo g = LS == 64 ? gw : row_geo(gw);
+  const int NT = g.NT, NW = gw.NW;
   const bool odd = lane & 1;
+  const LaneRow lr = lane_row<LS>(gw, lane);
   for (;;) {
     const int k = take_pair_hottest(hctr, NT);
     if (k < 0) break;
     const int a = sotl[k], b = NT + sotl[NT + k];
-    uint32_t* Wa = W + (size_t)a * 128;
-    uint32_t* Wb = W + (size_t)b * 128;
+    uint32_t* Wa = W + (size_t)a * 2 * NW;
+    uint32_t* Wb = W + (size_t)b * 2 * NW;
     uint32_t c0, c1;
-    if (!rows64_cluster(g, Wa, Wb, s, k, v, lane, c0, c1)) continue;
-    const uint32_t a0 = Wa[lane], a1 = Wa[64 + lane], b0 = Wb[lane], b1 = Wb[64 + lane];
+    if (!rows_cluster<LS>(g, lr, NW, Wa, Wb, s, k, v, lane, c0, c1)) continue;
+    uint32_t ab[4] = {Wa[lr.w], Wa[NW + lr.w], 0u, 0u};
+    if constexpr (LS == 64) {
+      ab[2] = Wb[lr.w];
+      ab[3] = Wb[NW + lr.w];
+    }
+    const uint32_t a0 = row_field<LS>(g, lr, ab[0]), a1 = row_field<LS>(g, lr, ab[1]);
     // energy change of replica a over the bonds of the colour-0 sites (each
     // bond has one): +x0, -x0 in the row, +x1, -x1 in the next/previous row
     uint32_t nc[4], na[4];
     x0_neighbours(g, c1, odd, nc[0], nc[1]);
     x0_neighbours(g, a1, odd, na[0], na[1]);
-    nc[2] = dpp_ones<kWaveRol1>(c1);  // row + 1 (lane 63 takes lane 0)
-    nc[3] = dpp_ones<kWaveRor1>(c1);  // row - 1
-    na[2] = dpp_ones<kWaveRol1>(a1);
-    na[3] = dpp_ones<kWaveRor1>(a1);
+    nc[2] = row_next<LS>(lr, c1);
+    nc[3] = row_prev<LS>(lr, c1);
+    na[2] = row_next<LS>(lr, a1);
+    na[3] = row_prev<LS>(lr, a1);
     int cross = 0, cross_u = 0;
 #pragma unroll
     for (int dir = 0; dir < 4; ++dir) {
       const uint32_t X = c0 ^ nc[dir];
-      const uint32_t U = a0 ^ na[dir] ^ Jl[dir * 64 + lane];
+      const uint32_t U = a0 ^ na[dir] ^ (LS == 64 ? Jl[dir * NW + lr.w] : Jl[dir * NW + lr.w] >> lr.sh);
       cross += __popc(X);
       cross_u += __popc(X & U);
     }
-    uint32_t dsum = (uint32_t)(2 * (cross - 2 * cross_u));
-    dsum += dpp_zero<kRowShr1>(dsum);
-    dsum += dpp_zero<kRowShr2>(dsum);
-    dsum += dpp_zero<kRowShr4>(dsum);
-    dsum += dpp_zero<kRowShr8>(dsum);
-    dsum += dpp_zero<kBcast15, 0xA>(dsum);
-    dsum += dpp_zero<kBcast31, 0xC>(dsum);
-    const int delta = __builtin_amdgcn_readlane((int)dsum, 63);
-    Wa[lane] = a0 ^ c0;
-    Wa[64 + lane] = a1 ^ c1;
-    Wb[lane] = b0 ^ c0;
-    Wb[64 + lane] = b1 ^ c1;
+    const int delta = wave_total(2 * (cross - 2 * cross_u));
+    rows_exchange<LS>(lr, NW, Wa, Wb, ab, c0, c1);
     if (lane == 0) {
       El[a] += delta;
       El[b] -= delta;
@@ -662,16 +758,19 @@ __device__ __forceinline__ void houdayer_resident(const FusedArgs& A, uint32_t* 
   const uint32_t* Jl = lds + A.lay.J;  // colour-0 direction words first
   int32_t* El = reinterpret_cast<int32_t*>(lds + A.lay.E);
   const int32_t* sotl = reinterpret_cast<const int32_t*>(lds + A.lay.sot);
-  const int W2 = 2 * NW;
-  uint32_t* Qw = lds + A.lay.Qs + (size_t)wave * 2 * W2;
-  uint32_t* Cw = Qw + W2;
-  const int rpl = (g.NR + 63) / 64;  // rows per lane for the seed search
-  if (D == 2 && rows64_houdayer(g)) {
-    houdayer_rows64(fixed_shape<2, 64>(g), W, Jl, El, sotl, s, v, lds + A.lay.hq, lane);
+  if constexpr (D == 2) {
+    if (g.L == 64)
+      houdayer_rows<64>(fixed_shape<2, 64>(g), W, Jl, El, sotl, s, v, lds + A.lay.hq, recomputed(lane));
+    else
+      houdayer_rows<0>(g, W, Jl, El, sotl, s, v, lds + A.lay.hq, recomputed(lane));
     __syncthreads();
     if (tid == 0) lds[A.lay.hq] = 0u;  // the next use is behind the step's barriers
     return;
   }
+  const int W2 = 2 * NW;
+  uint32_t* Qw = lds + A.lay.Qs + (size_t)wave * 2 * W2;
+  uint32_t* Cw = Qw + W2;
+  const int rpl = (g.NR + 63) / 64;  // rows per lane for the seed search
   for (int k = wave; k < NT; k += nwave) {
     const int a = sotl[k], b = NT + sotl[NT + k];
     uint32_t* Wa = W + (size_t)a * W2;

@@ -49,7 +49,7 @@ GaussLayout gauss_layout(const Geo& g, int nwave) {
   l.hq = o;    o += 1;                      // the in-register Houdayer move's pair counter
   l.W = o;     o += 2 * g.NT * 2 * g.NW;    // [2 N_T][2 NW] configuration words
   // per wavefront: overlap and cluster words of the word-hop flood fill
-  l.Qs = o;    o += rows64_houdayer(g) ? 0 : nwave * 4 * g.NW;
+  l.Qs = o;    o += rows_houdayer(g) ? 0 : nwave * 4 * g.NW;
   l.words = o;
   return l;
 }
@@ -72,7 +72,7 @@ __device__ void gauss_houdayer_resident(const Geo& g, uint32_t* W, int64_t* El, 
                                         uint32_t v) {
   const int NT = g.NT, NW = g.NW, W2 = 2 * NW;
   int tid = threadIdx.x;
-  asm volatile("" : "+v"(tid));  // as in gauss_houdayer_rows64
+  asm volatile("" : "+v"(tid));  // as in gauss_houdayer_rows
   const int wave = tid >> 6, lane = tid & 63, nwave = blockDim.x >> 6;
   uint32_t* Qw = Qs + (size_t)wave * 2 * W2;
   uint32_t* Cw = Qw + W2;
@@ -124,39 +124,49 @@ __device__ void gauss_houdayer_resident(const Geo& g, uint32_t* W, int64_t* El, 
   __syncthreads();
 }
 
-// The same for a 2D sample with 64 rows (L = 64, one row per word): the
-// cluster is found in registers, one row per lane (rows64_cluster), pairs from
-// the hottest down; the energy change sums, over the cluster's boundary bonds
-// from this row's colour-0 sites (a few per row), the bond's -2n from its
-// coupling group with the sign of replica a across it.  Ends with a workgroup
-// barrier, after which the pair counter is cleared.
-__device__ void gauss_houdayer_rows64(const Geo& g, uint32_t* W, int64_t* El, const int32_t* sotl,
-                                      const int4* __restrict__ J0, int s, uint32_t v, uint32_t* hctr) {
-  const int NT = g.NT, NGc = gauss_groups(g);
+// The same for a 2D sample: the cluster is found in registers, one row per
+// lane (rows_cluster), pairs from the hottest down; the energy change sums,
+// over the cluster's boundary bonds from this row's colour-0 sites (a few per
+// row), the bond's -2n from its coupling group with the sign of replica a
+// across it.  Ends with a workgroup barrier, after which the pair counter is
+// cleared.
+template <int LS>
+__device__ void gauss_houdayer_rows(const Geo& gw, uint32_t* W, int64_t* El, const int32_t* sotl,
+                                    const int4* __restrict__ J0, int s, uint32_t v, uint32_t* hctr) {
+  const Geo g = LS == 64 ? gw : row_geo(gw);
+  const int NT = g.NT, NW = gw.NW, NGc = gauss_groups(gw);
   // recomputed at every call: what derives from the lane index (masks,
   // addresses) would otherwise be hoisted out of the step loop and stay live
   // through the sweep
   int lane = threadIdx.x & 63;
   asm volatile("" : "+v"(lane));
   const bool odd = lane & 1;
+  const LaneRow lr = lane_row<LS>(gw, lane);
+  // first coupling group of the row (groups of a word: field-major, then q)
+  const int g0 = LS == 64 ? lane : lr.w + (lr.sh / g.H) * ((g.H + 3) / 4) * NW;
   for (;;) {
     const int k = take_pair_hottest(hctr, NT);
     if (k < 0) break;
     const int a = sotl[k], b = NT + sotl[NT + k];
-    uint32_t* Wa = W + (size_t)a * 128;
-    uint32_t* Wb = W + (size_t)b * 128;
+    uint32_t* Wa = W + (size_t)a * 2 * NW;
+    uint32_t* Wb = W + (size_t)b * 2 * NW;
     uint32_t c0, c1;
-    if (!rows64_cluster(g, Wa, Wb, s, k, v, lane, c0, c1)) continue;
-    const uint32_t a0 = Wa[lane], a1 = Wa[64 + lane], b0 = Wb[lane], b1 = Wb[64 + lane];
+    if (!rows_cluster<LS>(g, lr, NW, Wa, Wb, s, k, v, lane, c0, c1)) continue;
+    uint32_t ab[4] = {Wa[lr.w], Wa[NW + lr.w], 0u, 0u};
+    if constexpr (LS == 64) {
+      ab[2] = Wb[lr.w];
+      ab[3] = Wb[NW + lr.w];
+    }
+    const uint32_t a0 = row_field<LS>(g, lr, ab[0]), a1 = row_field<LS>(g, lr, ab[1]);
     // the colour-0 sites' bonds: +x0, -x0 in the row, +x1, -x1 to the
     // next/previous row, the order of the coupling groups' directions
     uint32_t nc[4], na[4];
     x0_neighbours(g, c1, odd, nc[0], nc[1]);
     x0_neighbours(g, a1, odd, na[0], na[1]);
-    nc[2] = dpp_ones<kWaveRol1>(c1);
-    nc[3] = dpp_ones<kWaveRor1>(c1);
-    na[2] = dpp_ones<kWaveRol1>(a1);
-    na[3] = dpp_ones<kWaveRor1>(a1);
+    nc[2] = row_next<LS>(lr, c1);
+    nc[3] = row_prev<LS>(lr, c1);
+    na[2] = row_next<LS>(lr, a1);
+    na[3] = row_prev<LS>(lr, a1);
     int64_t dl = 0;
 #pragma unroll
     for (int dir = 0; dir < 4; ++dir) {
@@ -166,17 +176,14 @@ __device__ void gauss_houdayer_rows64(const Geo& g, uint32_t* W, int64_t* El, co
         const int q = __builtin_ctz(grp) >> 2;  // group of four sites of the row
         const uint32_t xb = (X >> (4 * q)) & 0xFu, ub = (U >> (4 * q)) & 0xFu;
         grp &= ~(0xFu << (4 * q));
-        const int4 m = J0[(size_t)dir * NGc + lane + 64 * q];
+        const int4 m = J0[(size_t)dir * NGc + g0 + NW * q];
 #pragma unroll
         for (int j = 0; j < 4; ++j)
           if ((xb >> j) & 1u) dl += ((ub >> j) & 1u) ? lane_of(m, j) : -lane_of(m, j);
       }
     }
     const int64_t delta = wave_sum64(dl);
-    Wa[lane] = a0 ^ c0;
-    Wa[64 + lane] = a1 ^ c1;
-    Wb[lane] = b0 ^ c0;
-    Wb[64 + lane] = b1 ^ c1;
+    rows_exchange<LS>(lr, NW, Wa, Wb, ab, c0, c1);
     if (lane == 0) {
       El[a] += delta;
       El[b] -= delta;
@@ -326,11 +333,15 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) k
     }
     // ---- Houdayer move per pair
     if (HOU) {
-      if (D == 2 && rows64_houdayer(g))
-        gauss_houdayer_rows64(fixed_shape<2, 64>(g), W, El, sotl, Js, s, v0 + (uint32_t)step,
-                              lds + lay.hq);
-      else
+      if constexpr (D == 2) {
+        if (g.L == 64)
+          gauss_houdayer_rows<64>(fixed_shape<2, 64>(g), W, El, sotl, Js, s, v0 + (uint32_t)step,
+                                  lds + lay.hq);
+        else
+          gauss_houdayer_rows<0>(g, W, El, sotl, Js, s, v0 + (uint32_t)step, lds + lay.hq);
+      } else {
         gauss_houdayer_resident<D>(g, W, El, sotl, lds + lay.Qs, Js, s, v0 + (uint32_t)step);
+      }
     }
     // ---- replica exchange, one thread per set, k ascending with the updated map
     if (lane == 0 && wave < 2) {
