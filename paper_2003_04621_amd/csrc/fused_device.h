@@ -79,47 +79,37 @@ __device__ __forceinline__ void exchange_prepare(const FusedArgs& A, uint32_t* l
   }
 }
 
-// The pass itself, after exchange_prepare and a workgroup barrier; with WALK
-// and `walk`, pass m (counted from 1) of the replica walk, with round trips
-// summed in LDS (`walk` is false where the job does not track the walk or
-// another workgroup of the sample keeps it).
-template <bool WALK>
-__device__ __forceinline__ void exchange_resident(const FusedArgs& A, uint32_t* lds, int c_lo,
-                                                  int nsets, uint32_t m, bool walk) {
-  const Geo& g = A.g;
-  const int NT = g.NT, tid = threadIdx.x, T = blockDim.x;
-  const int32_t* El = reinterpret_cast<const int32_t*>(lds + A.lay.E);
-  int32_t* sotl = reinterpret_cast<int32_t*>(lds + A.lay.sot);
-  int32_t* tosl = reinterpret_cast<int32_t*>(lds + A.lay.tos);
-  const int32_t* sot0 = reinterpret_cast<const int32_t*>(lds + A.lay.sot0);
-  const uint32_t* rpt = lds + A.lay.rpt;
-  uint32_t* acc = lds + A.lay.acc;  // bit j of row (c, k): rows of NB bits, c-major
-  const int NB = (NT + 31) & ~31;
-  {
-    const int lane = tid & 63, total = nsets * (NT - 1) * NB;  // a multiple of 32
-    uint32_t* accs = acc + (size_t)c_lo * (NT - 1) * (NB >> 5);
-    for (int base = tid - lane; base < total; base += T) {  // uniform per wavefront
-      const int i = base + lane;
-      bool ok = false;
-      if (i < total) {
-        const int row = i / NB, j = i - row * NB;
-        const int cl = row / (NT - 1), k = row - cl * (NT - 1), c = c_lo + cl;
-        if (j <= k) {
-          const int a = sot0[c * NT + j], b = sot0[c * NT + k + 1];
-          const int32_t D = El[c * NT + b] - El[c * NT + a];
-          ok = D <= 0;
-          if (!ok) {
-            const int m = D >> 1;
-            ok = m < A.M && rpt[c * NT + k] < A.thrpt[(size_t)k * A.M + m];
-          }
-        }
-      }
-      const uint64_t bits = __ballot(ok);
-      if (lane == 0) accs[base >> 5] = (uint32_t)bits;
-      if (lane == 32 && base + 32 < total) accs[(base >> 5) + 1] = (uint32_t)(bits >> 32);
+// All candidate decisions of one pass for sets [c_lo, c_lo + nsets) as bits:
+// decide(c, k, j), j <= k, says whether step k of set c exchanges when the
+// configuration carried up from position j meets the one at k + 1.  acc: bit
+// j of row (c, k), c-major, (N_T + 31) / 32 words a row.
+template <typename F>
+__device__ __forceinline__ void exchange_decide(int NT, int c_lo, int nsets, uint32_t* acc, F&& decide) {
+  const int tid = threadIdx.x, T = blockDim.x, NB = (NT + 31) & ~31;
+  const int lane = tid & 63, total = nsets * (NT - 1) * NB;  // a multiple of 32
+  uint32_t* accs = acc + (size_t)c_lo * (NT - 1) * (NB >> 5);
+  for (int base = tid - lane; base < total; base += T) {  // uniform per wavefront
+    const int i = base + lane;
+    bool ok = false;
+    if (i < total) {
+      const int row = i / NB, j = i - row * NB;
+      const int cl = row / (NT - 1), k = row - cl * (NT - 1), c = c_lo + cl;
+      if (j <= k) ok = decide(c, k, j);
     }
+    const uint64_t bits = __ballot(ok);
+    if (lane == 0) accs[base >> 5] = (uint32_t)bits;
+    if (lane == 32 && base + 32 < total) accs[(base >> 5) + 1] = (uint32_t)(bits >> 32);
   }
-  __syncthreads();
+}
+
+// Follows the chain of those decisions from the maps before the pass (sot0)
+// to the new ones; with WALK and `walk` not null, pass m of the replica walk.
+// The caller synchronises before and after.
+template <bool WALK>
+__device__ __forceinline__ void exchange_chain(int NT, int c_lo, int nsets, int32_t* sotl, int32_t* tosl,
+                                               const int32_t* sot0, const uint32_t* acc, int32_t* walk,
+                                               uint64_t* trips, uint32_t m) {
+  const int tid = threadIdx.x, T = blockDim.x, NB = (NT + 31) & ~31;
   const int wave = tid >> 6, lane = tid & 63, nwave = T >> 6;
   if (NT <= 64) {
     // One wavefront per set; lane k holds decision row k.  From the carried
@@ -166,9 +156,7 @@ __device__ __forceinline__ void exchange_resident(const FusedArgs& A, uint32_t* 
         const int hot = m0[cur];
         so[NT - 1] = hot;
         to[hot] = NT - 1;
-        if (WALK && walk)
-          walk_observe(reinterpret_cast<int32_t*>(lds + A.lay.walk) + 2 * c * NT,
-                       reinterpret_cast<uint64_t*>(lds + A.lay.trip), so[0], hot, m);
+        if (WALK && walk) walk_observe(walk + 2 * c * NT, trips, so[0], hot, m);
       }
     }
     if (wave < nsets) __builtin_amdgcn_s_setprio(0);
@@ -192,10 +180,35 @@ __device__ __forceinline__ void exchange_resident(const FusedArgs& A, uint32_t* 
     }
     so[NT - 1] = m0[cur];
     to[m0[cur]] = NT - 1;
-    if (WALK && walk)
-      walk_observe(reinterpret_cast<int32_t*>(lds + A.lay.walk) + 2 * c * NT,
-                   reinterpret_cast<uint64_t*>(lds + A.lay.trip), so[0], m0[cur], m);
+    if (WALK && walk) walk_observe(walk + 2 * c * NT, trips, so[0], m0[cur], m);
   }
+}
+
+// The pass itself, after exchange_prepare and a workgroup barrier; with WALK
+// and `walk`, pass m (counted from 1) of the replica walk, with round trips
+// summed in LDS (`walk` is false where the job does not track the walk or
+// another workgroup of the sample keeps it).
+template <bool WALK>
+__device__ __forceinline__ void exchange_resident(const FusedArgs& A, uint32_t* lds, int c_lo,
+                                                  int nsets, uint32_t m, bool walk) {
+  const Geo& g = A.g;
+  const int NT = g.NT;
+  const int32_t* El = reinterpret_cast<const int32_t*>(lds + A.lay.E);
+  const int32_t* sot0 = reinterpret_cast<const int32_t*>(lds + A.lay.sot0);
+  const uint32_t* rpt = lds + A.lay.rpt;
+  uint32_t* acc = lds + A.lay.acc;
+  exchange_decide(NT, c_lo, nsets, acc, [&](int c, int k, int j) {
+    const int a = sot0[c * NT + j], b = sot0[c * NT + k + 1];
+    const int32_t D = El[c * NT + b] - El[c * NT + a];
+    if (D <= 0) return true;
+    const int md = D >> 1;
+    return md < A.M && rpt[c * NT + k] < A.thrpt[(size_t)k * A.M + md];
+  });
+  __syncthreads();
+  exchange_chain<WALK>(NT, c_lo, nsets, reinterpret_cast<int32_t*>(lds + A.lay.sot),
+                       reinterpret_cast<int32_t*>(lds + A.lay.tos), sot0, acc,
+                       WALK && walk ? reinterpret_cast<int32_t*>(lds + A.lay.walk) : nullptr,
+                       WALK && walk ? reinterpret_cast<uint64_t*>(lds + A.lay.trip) : nullptr, m);
   __syncthreads();
 }
 

@@ -110,10 +110,14 @@ __host__ __device__ inline bool gauss_accept_dd(uint32_t r, double b, int64_t u)
   return (double)r - s.hi < s.lo;
 }
 
-// The float32 tier's per-temperature constant, b log2(e) 2^-16 rounded to
-// float (host and device compute it with the same double operations).
+// The float32 tier's per-temperature constant, b log2(e) 2^-15 rounded to
+// float (host and device compute it with the same double operations): cz x is
+// the log2 of the inverse acceptance probability of a flip with local field x
+// (energy change 2x units).  Capped so that its product with any x is finite
+// (beyond the cap no x >= 1 is accepted by a word r >= 1 anyway).
 __host__ __device__ inline float gauss_cz(double b) {
-  return (float)(b * 1.4426950408889634 / 65536.0);
+  const double c = b * 1.4426950408889634 / 32768.0;
+  return c < 0x1p100 ? (float)c : 0x1p100f;
 }
 
 // The double tier: y = b u 2^-16 rounded once (relative error 2^-53), exp in
@@ -129,25 +133,26 @@ __device__ inline bool gauss_accept_d(uint32_t r, double b, int64_t u) {
   return gauss_accept_dd(r, b, u);
 }
 
-// The Metropolis decision for u = 2x energy units (2 <= u < 2^24), with
-// cz = float(b log2(e) 2^-16) from the host: z = u cz carries a relative
-// error below 2^-23, so for z < 33 the float32 threshold 2^32 2^-z
-// (v_exp_f32) is within 2^-18 of the true one; a word outside a 2^-15 band
-// around it is decided here, the rest by the double tier.  For z >= 33 the
-// threshold is below 1 and only r = 0 accepts.
-// The float32 tier alone, without branches: 1 accept, 0 reject, -1
-// undecided (inside the band).  For z >= 33 the threshold is below 1/2 (or
-// flushed to 0): every r >= 1 is rejected and r = 0 is accepted or, if the
-// threshold underflowed, left to the double tier, which accepts it.
-__device__ __forceinline__ int gauss_metro_f32(uint32_t r, float cz, uint32_t u) {
-  const float z = (float)u * cz;
-  const float t = __builtin_amdgcn_exp2f(-z) * 4294967296.0f;
-  const float rf = (float)r;
-  return rf < t * (1.0f - 0x1p-15f) ? 1 : (rf > t * (1.0f + 0x1p-15f) ? 0 : -1);
+// The Metropolis decision for local field x (u = 2x < 2^24 energy units, any
+// sign), in base-2 logarithms: d = log2 r - 32 + cz x, accepted iff d < 0.  The
+// logarithm of the word does not wait for the local field, one fma forms d,
+// and the decision is its sign bit; the threshold form 2^32 2^-z needs two
+// more multiplies and two compares per site.  Errors: r to float 2^-24
+// relative (2^-23.5 in log2), v_log_f32 2^-19 (one ulp below 32), the
+// difference 2^-20, cz x 2^-24 relative (2^-18.9 where cz x <= 33), the sum
+// below 2^-19: under 2^-17 in all, so a |d| above 2^-15 is decided here.  Where
+// cz x > 33 every r >= 1 gives d > 1/2 and is rejected, rightly (the threshold
+// is below 1/2); r = 0 gives d = -inf and is accepted, rightly; x <= 0 gives
+// d <= 0 up to those errors.  Words inside the band (4e-5 of the threshold)
+// go to the double tier, which decides x <= 0 too.
+constexpr float kMetroBand = 0x1p-15f;
+__device__ __forceinline__ float gauss_metro_log(uint32_t r, float cz, int x) {
+  return __builtin_fmaf((float)x, cz, __builtin_amdgcn_logf((float)r) - 32.0f);
 }
 __device__ inline bool gauss_accept_metro(uint32_t r, float cz, double b, uint32_t u) {
-  const int f = gauss_metro_f32(r, cz, u);
-  return f >= 0 ? f != 0 : gauss_accept_d(r, b, (int64_t)u);
+  // (test entry: u may be odd; u cz / 2 is as exact as x cz)
+  const float d = __builtin_fmaf((float)u, 0.5f * cz, __builtin_amdgcn_logf((float)r) - 32.0f);
+  return fabsf(d) > kMetroBand ? d < 0.0f : gauss_accept_d(r, b, (int64_t)u);
 }
 
 // ---------------------------------------------------------------------------
@@ -176,78 +181,85 @@ __device__ __forceinline__ uint32_t word_of(const Ctr4& v, int j) {
   return j == 0 ? v.x : j == 1 ? v.y : j == 2 ? v.z : v.w;
 }
 
-// Bit j of a sign-extended to a mask (0 or -1), one v_bfe_i32.  Written as
+// Bit `at` of a sign-extended to a mask (0 or -1), one v_bfe_i32.  Written as
 // an instruction so that the compiler keeps the mask-and-add form (its own
 // canonical form, a compare and a select per term, costs one more).
-template <int J>
-__device__ __forceinline__ int bit_mask(uint32_t a) {
+__device__ __forceinline__ int bit_mask(uint32_t a, int at) {
   int r;
-  asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(r) : "v"(a), "i"(J));
+  asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(r) : "v"(a), "v"(at));
   return r;
 }
 
-// x = s_i h_i of the four sites of a group from the antiparallel words a[k]
-// (already shifted to the group) and the group's coupling data: bit j of a[k]
-// as a mask selects the term.
+// x = s_i h_i of the four sites of a group (bits sh .. sh + 3) from the
+// antiparallel words a[k] and the group's coupling data: the site's bit of
+// a[k] as a mask selects the term.
 template <int D>
-__device__ __forceinline__ void group_fields(const uint32_t (&a)[2 * D], const int4 (&m)[2 * D],
+__device__ __forceinline__ void group_fields(const uint32_t (&a)[2 * D], int sh, const int4 (&m)[2 * D],
                                              const int4& hs, int (&x)[4]) {
   x[0] = hs.x;
   x[1] = hs.y;
   x[2] = hs.z;
   x[3] = hs.w;
 #pragma unroll
-  for (int k = 0; k < 2 * D; ++k) {
-    x[0] += m[k].x & bit_mask<0>(a[k]);
-    x[1] += m[k].y & bit_mask<1>(a[k]);
-    x[2] += m[k].z & bit_mask<2>(a[k]);
-    x[3] += m[k].w & bit_mask<3>(a[k]);
+  for (int k = 0; k < 2 * D; k += 2) {
+    // two terms at a time: one three-input add
+    x[0] += (m[k].x & bit_mask(a[k], sh)) + (m[k + 1].x & bit_mask(a[k + 1], sh));
+    x[1] += (m[k].y & bit_mask(a[k], sh + 1)) + (m[k + 1].y & bit_mask(a[k + 1], sh + 1));
+    x[2] += (m[k].z & bit_mask(a[k], sh + 2)) + (m[k + 1].z & bit_mask(a[k + 1], sh + 2));
+    x[3] += (m[k].w & bit_mask(a[k], sh + 3)) + (m[k + 1].w & bit_mask(a[k + 1], sh + 3));
   }
 }
 
-// The Metropolis decisions of one group of four same-colour sites (the first
-// nv valid) whose Philox words are r, in two parts so that a caller can
-// interleave two groups: gauss_group_fast computes the local fields and the
-// float32 tier for the four sites without branches (x <= 0 flips at once):
-// the flip bits F and the undecided bits und; gauss_group_finish decides the
-// rare undecided sites by the exact tiers and adds the flips' energy change
-// 2x to dE.
+// The Metropolis decisions of one group of four same-colour sites whose
+// Philox words are r, in two parts so that a caller can interleave two groups:
+// gauss_group_fast computes the local fields and the float32 tier without
+// branches: the flip bits F and `sure`, whether all four are decided (for
+// lanes of a part group, the unused sites' too: x = 0 there);
+// gauss_group_finish decides the rare undecided sites by the exact tiers.
+// F keeps the valid sites (vmask).
 template <int D>
-__device__ __forceinline__ void gauss_group_fast(const uint32_t (&a)[2 * D], const int4 (&m)[2 * D],
-                                                 const int4& hs, int nv, const Ctr4& r, float cz,
-                                                 int (&x)[4], uint32_t& F, uint32_t& und) {
-  group_fields<D>(a, m, hs, x);
-  F = 0;
-  und = 0;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int xj = x[j];
-    int f = gauss_metro_f32(word_of(r, j), cz, 2u * (uint32_t)(xj > 0 ? xj : 0));
-    f = xj <= 0 ? 1 : f;
-    f = j < nv ? f : 0;
-    F |= (uint32_t)(f > 0) << j;
-    und |= (uint32_t)(f < 0) << j;
-  }
+__device__ __forceinline__ void gauss_group_fast(const uint32_t (&a)[2 * D], int sh,
+                                                 const int4 (&m)[2 * D], const int4& hs, const Ctr4& r,
+                                                 float cz, int (&x)[4], uint32_t& F, bool& sure) {
+  group_fields<D>(a, sh, m, hs, x);
+  const float d0 = gauss_metro_log(r.x, cz, x[0]), d1 = gauss_metro_log(r.y, cz, x[1]);
+  const float d2 = gauss_metro_log(r.z, cz, x[2]), d3 = gauss_metro_log(r.w, cz, x[3]);
+  // sign bits, the last site's first
+  F = __float_as_uint(d3) >> 31;
+  F = __builtin_amdgcn_alignbit(F, __float_as_uint(d2), 31);
+  F = __builtin_amdgcn_alignbit(F, __float_as_uint(d1), 31);
+  F = __builtin_amdgcn_alignbit(F, __float_as_uint(d0), 31);
+  sure = fminf(fminf(fabsf(d0), fabsf(d1)), fminf(fabsf(d2), fabsf(d3))) > kMetroBand;
 }
-__device__ __forceinline__ uint32_t gauss_group_finish(const int (&x)[4], const Ctr4& r, double beta,
-                                                       uint32_t F, uint32_t und, int& dE) {
-  while (und) {
-    const int j = __builtin_ctz(und);
-    und &= und - 1u;
-    if (gauss_accept_d(word_of(r, j), beta, (int64_t)(2 * x[j]))) F |= 1u << j;
+__device__ __forceinline__ uint32_t gauss_group_finish(const int (&x)[4], const Ctr4& r, float cz,
+                                                       double beta, uint32_t F, bool sure,
+                                                       uint32_t vmask) {
+  if (!sure) {
+    for (int j = 0; j < 4; ++j) {
+      const int xj = j == 0 ? x[0] : j == 1 ? x[1] : j == 2 ? x[2] : x[3];
+      const uint32_t rj = word_of(r, j);
+      if (fabsf(gauss_metro_log(rj, cz, xj)) > kMetroBand) continue;
+      const bool acc = gauss_accept_d(rj, beta, 2 * (int64_t)xj);
+      F = (F & ~(1u << j)) | ((uint32_t)acc << j);
+    }
   }
-#pragma unroll
-  for (int j = 0; j < 4; ++j) dE += ((F >> j) & 1u) ? 2 * x[j] : 0;
-  return F;
+  return F & vmask;
+}
+// Energy change of the group's flips F.
+__device__ __forceinline__ int gauss_flip_energy(const int (&x)[4], uint32_t F) {
+  int s = (x[0] & bit_mask(F, 0)) + (x[1] & bit_mask(F, 1));
+  s += (x[2] & bit_mask(F, 2)) + (x[3] & bit_mask(F, 3));
+  return 2 * s;
 }
 template <int D>
-__device__ __forceinline__ uint32_t gauss_group_flips(const uint32_t (&a)[2 * D], const int4 (&m)[2 * D],
-                                                      const int4& hs, int nv, const Ctr4& r, float cz,
-                                                      double beta, int& dE) {
-  int x[4];
-  uint32_t F, und;
-  gauss_group_fast<D>(a, m, hs, nv, r, cz, x, F, und);
-  return gauss_group_finish(x, r, beta, F, und, dE);
+__device__ __forceinline__ uint32_t gauss_group_flips(const uint32_t (&a)[2 * D], int sh,
+                                                      const int4 (&m)[2 * D], const int4& hs,
+                                                      uint32_t vmask, const Ctr4& r, float cz,
+                                                      double beta, int (&x)[4]) {
+  uint32_t F;
+  bool sure;
+  gauss_group_fast<D>(a, sh, m, hs, r, cz, x, F, sure);
+  return gauss_group_finish(x, r, cz, beta, F, sure, vmask);
 }
 
 // Energy change of replica a when the cluster C (both colours' words) is

@@ -102,12 +102,12 @@ __global__ void __launch_bounds__(256) k_genergy(Geo g, const void* spins, const
     int4 m[2 * D];
 #pragma unroll
     for (int k = 0; k < 2 * D; ++k) {
-      a[k] = (Wc ^ n[k]) >> gp.shift;
+      a[k] = Wc ^ n[k];
       m[k] = J0[(size_t)k * NGc + gi];
     }
     const int4 hs = J0[(size_t)2 * D * NGc + gi];
     int x[4];
-    group_fields<D>(a, m, hs, x);
+    group_fields<D>(a, gp.shift, m, hs, x);
     for (int j = 0; j < gp.nv; ++j) sum += x[j];
   }
   if (sum) atomicAdd(&acc, (unsigned long long)(-sum));
@@ -189,10 +189,13 @@ __global__ void __launch_bounds__(512) k_gsweep(Geo g, void* spins, const int4* 
             uint32_t n[2 * D], a[2 * D];
             neighbour_words<D>(g, Wl + (1 - c) * NW, gp.w, nb, p, n);
 #pragma unroll
-            for (int k = 0; k < 2 * D; ++k) a[k] = (Wc ^ n[k]) >> gp.shift;
+            for (int k = 0; k < 2 * D; ++k) a[k] = Wc ^ n[k];
             const uint32_t slot = (uint32_t)(set * g.NT + j0 + l);
             const Ctr4 r = philox10(Ctr4{c0, c1, slot, c3}, g.key0, g.key1);
-            const uint32_t F = gauss_group_flips<D>(a, m, hs, gp.nv, r, czl[l], bl[l], dE);
+            int x[4];
+            const uint32_t F = gauss_group_flips<D>(a, gp.shift, m, hs, (1u << gp.nv) - 1u, r, czl[l],
+                                                    bl[l], x);
+            dE = gauss_flip_energy(x, F);
             if (F) atomicXor(&Wl[c * NW + gp.w], F << gp.shift);
           }
           // every lane of the wavefront is here (see above): a DPP sum

@@ -25,20 +25,27 @@ namespace ptsg {
 
 namespace {
 
-// Threads of the fused Gaussian workgroup: one per site group of a colour,
-// at least 256 (four wavefronts for the Houdayer pairs), at most 512.
-int gauss_fused_threads(const Geo& g) {
-  const int groups = gauss_groups(g);
-  return std::min(512, std::max(256, (groups + 63) / 64 * 64));
-}
-
-// LDS word offsets (64-bit arrays first, so that they stay 8-byte aligned).
+// LDS word offsets (64-bit arrays first, so that they stay 8-byte aligned);
+// acc < 0: the exchange pass walks serially (ladders above 64 temperatures).
 struct GaussLayout {
-  int E, beta, mom, cz, sot, tos, hq, W, Qs, words;
+  int E, beta, mom, cz, sot, tos, hq, W, Qs, sot0, rpt, acc, words;
+  int team;  // threads of a team
+  int PC;    // wavefronts with a Houdayer scratch area (3D)
 };
 
+// Threads of the fused Gaussian workgroup and its LDS plan.  A team of
+// threads, one per site group of a colour, sweeps one configuration (in 2D two)
+// at a time; a workgroup holds as many teams as its threads allow.  The kernel
+// takes four wavefronts per SIMD (its registers), so a CU runs 1024 of its
+// threads: one workgroup of 1024 where there are no more samples than CUs or
+// two would not fit the LDS, else two of 512.  (One team of 256 to 512 threads
+// whatever the sample count, as before: 3D L = 10, 150 samples x 2 x 15, 55 us
+// per step against 25 us, the chip holding one wavefront per SIMD.)
+constexpr int kCUs = 256;
+int gauss_fused_threads(const Geo& g, GaussLayout& l);
+
 GaussLayout gauss_layout(const Geo& g, int nwave) {
-  GaussLayout l;
+  GaussLayout l{};
   int o = 0;
   l.E = o;     o += 2 * 2 * g.NT;           // int64 [2 N_T] energies (2^-16 units)
   l.beta = o;  o += 2 * g.NT;               // double [N_T]
@@ -49,9 +56,50 @@ GaussLayout gauss_layout(const Geo& g, int nwave) {
   l.hq = o;    o += 1;                      // the in-register Houdayer move's pair counter
   l.W = o;     o += 2 * g.NT * 2 * g.NW;    // [2 N_T][2 NW] configuration words
   // per wavefront: overlap and cluster words of the word-hop flood fill
-  l.Qs = o;    o += rows_houdayer(g) ? 0 : nwave * 4 * g.NW;
+  l.PC = rows_houdayer(g) ? 0 : nwave;
+  l.Qs = o;    o += l.PC * 4 * g.NW;
   l.words = o;
+  // the exchange pass's maps before the pass, Philox words and decisions
+  l.acc = -1;
+  if (g.NT <= 64) {
+    l.sot0 = o;  o += 2 * g.NT;
+    l.rpt = o;   o += 2 * g.NT;
+    l.acc = o;   o += 2 * (g.NT - 1) * ((g.NT + 31) / 32);
+    l.words = o;
+  }
   return l;
+}
+
+// The LDS of the smallest workgroup (four to eight wavefronts, serial
+// exchange): what decides whether a sample's steps run fused.
+size_t gauss_least_lds(const Geo& g) {
+  const int threads = std::min(512, std::max(256, (gauss_groups(g) + 63) / 64 * 64));
+  GaussLayout l = gauss_layout(g, threads / 64);
+  return sizeof(uint32_t) * (size_t)(l.acc >= 0 ? l.sot0 : l.words);
+}
+
+int gauss_fused_threads(const Geo& g, GaussLayout& l) {
+  const int groups = (gauss_groups(g) + 63) / 64 * 64, configs = g.d == 2 ? g.NT : 2 * g.NT;
+  for (int most : {512, 1024}) {
+    if (most == 512 && g.S <= kCUs) continue;
+    const int team = std::min(most, groups);
+    const int threads = std::max(256, team * std::min(most / team, configs));
+    l = gauss_layout(g, threads / 64);
+    // fewer scratch areas, then the serial exchange, where the LDS is short
+    const size_t limit = kGaussFusedMaxLds / (most == 512 ? 2 : 1);
+    while (l.PC > 4 && sizeof(uint32_t) * (size_t)l.words > limit) {
+      const int pc = l.PC - 1;
+      l = gauss_layout(g, pc);
+    }
+    if (sizeof(uint32_t) * (size_t)l.words > limit && l.acc >= 0) {
+      l.words = l.sot0;
+      l.acc = -1;
+    }
+    l.team = team;
+    if (most == 512 && sizeof(uint32_t) * (size_t)l.words > limit) continue;
+    return threads;
+  }
+  return 0;
 }
 
 // Wavefront sum of a 64-bit value.
@@ -68,16 +116,16 @@ __device__ __forceinline__ int64_t wave_sum64(int64_t v) {
 // cluster.  Ends with a workgroup barrier.
 template <int D>
 __device__ void gauss_houdayer_resident(const Geo& g, uint32_t* W, int64_t* El, const int32_t* sotl,
-                                        uint32_t* Qs, const int4* __restrict__ J0, int s,
+                                        uint32_t* Qs, int PC, const int4* __restrict__ J0, int s,
                                         uint32_t v) {
   const int NT = g.NT, NW = g.NW, W2 = 2 * NW;
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));  // as in gauss_houdayer_rows
-  const int wave = tid >> 6, lane = tid & 63, nwave = blockDim.x >> 6;
+  const int wave = tid >> 6, lane = tid & 63;
   uint32_t* Qw = Qs + (size_t)wave * 2 * W2;
   uint32_t* Cw = Qw + W2;
   const int rpl = (g.NR + 63) / 64;  // rows per lane for the seed search
-  for (int k = wave; k < NT; k += nwave) {
+  for (int k = wave < PC ? wave : NT; k < NT; k += PC) {
     const int a = sotl[k], b = NT + sotl[NT + k];
     uint32_t* Wa = W + (size_t)a * W2;
     uint32_t* Wb = W + (size_t)b * W2;
@@ -193,11 +241,107 @@ __device__ void gauss_houdayer_rows(const Geo& gw, uint32_t* W, int64_t* El, con
   if (threadIdx.x == 0) *hctr = 0u;  // the next use is behind the step's barriers
 }
 
+// The Metropolis sweep of every configuration, colour 0, then colour 1.  A
+// thread takes a group of four same-colour sites (one Philox call, its
+// coupling data in registers) and updates it in every configuration of its
+// team's share.  The energies come from the colour-1 half alone: a bond has one
+// colour-1 end, so E = -(sum of x over the colour-1 sites after their
+// updates); El holds zeros before.  Bound by its VALU instructions,
+// half of them Philox: 2D L = 64, 500 samples x 2 x 24, sweep + exchange 150 ->
+// 99 us per step from the logarithm form of the float32 tier, energies in one
+// half instead of a change per flip in both, the L = 64 geometry folded and the
+// exchange's decisions taken in parallel (one lane per set walked them before).
+// Ends with a workgroup barrier.
+template <int D, int LS>
+__device__ __forceinline__ void gauss_sweep_resident(const Geo& g, int team_threads, uint32_t* W,
+                                                     int64_t* El, const int32_t* tosl, const float* czl,
+                                                     const double* bl, const int4* __restrict__ Js,
+                                                     int s, uint32_t t) {
+  constexpr int U = D == 2 ? 2 : 1;  // configurations per round (2 N_T is even)
+  const int NW = g.NW, W2 = 2 * NW, NS = 2 * g.NT, NGc = gauss_groups(g);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), tw = team_threads >> 6;
+  const int team = wave / tw, teams = max(1, (int)(blockDim.x >> 6) / tw);
+  const int tt = tid - team * team_threads;
+  const uint32_t c3 = (kTagMetro << 28) | (uint32_t)s;
+  for (int c = 0; c < 2; ++c) {
+    const int4* Jc = Js + (size_t)c * (2 * D + 1) * NGc;
+    const uint32_t c1 = 2u * t + (uint32_t)c;
+    for (int gi0 = 0; gi0 < NGc && team < teams; gi0 += team_threads) {
+      // the group's position is recomputed every step: hoisted out of the
+      // step loop it would stay live through the Houdayer move, whose
+      // in-register cluster then no longer fits the register budget
+      const int gi = recomputed(gi0 + tt);
+      const bool valid = gi < NGc;
+      int4 m[2 * D];
+      int4 hs = make_int4(0, 0, 0, 0);
+      GroupPos gp{};
+      WordNb nb{};
+      int p = 0;
+      uint32_t c0 = 0;
+      if (valid) {
+#pragma unroll
+        for (int k = 0; k < 2 * D; ++k) m[k] = Jc[(size_t)k * NGc + gi];
+        hs = Jc[(size_t)2 * D * NGc + gi];
+        gp = group_pos(g, gi);
+        nb = word_nb(g, gp.w);
+        p = (c + nb.par) & 1;
+        c0 = (uint32_t)word_row(g, nb, gp.f) * (uint32_t)g.G + (uint32_t)gp.q;
+      }
+      const uint32_t vmask = (1u << gp.nv) - 1u;
+      // 2D: two configurations per round, two independent chains of loads,
+      // Philox rounds and decisions for the scheduler; in 3D two would not fit
+      // the register budget of four wavefronts per SIMD
+      for (int l = U * team; l < NS; l += U * teams) {
+        int e[U];
+#pragma unroll
+        for (int i = 0; i < U; ++i) e[i] = 0;
+        if (valid) {
+          Ctr4 r[U];
+          int x[U][4], k[U];
+          uint32_t F[U];
+          bool sure[U];
+#pragma unroll
+          for (int i = 0; i < U; ++i) {
+            uint32_t* Wl = W + (size_t)(l + i) * W2;
+            const uint32_t Wc = Wl[c * NW + gp.w];
+            uint32_t a[2 * D];
+            neighbour_words<D>(g, Wl + (1 - c) * NW, gp.w, nb, p, a);
+#pragma unroll
+            for (int dir = 0; dir < 2 * D; ++dir) a[dir] ^= Wc;
+            r[i] = philox10_u(Ctr4{c0, c1, (uint32_t)(l + i), c3}, g.key0, g.key1);
+            k[i] = tosl[l + i];
+            gauss_group_fast<D>(a, gp.shift, m, hs, r[i], czl[k[i]], x[i], F[i], sure[i]);
+          }
+#pragma unroll
+          for (int i = 0; i < U; ++i) {
+            F[i] = gauss_group_finish(x[i], r[i], czl[k[i]], bl[k[i]], F[i], sure[i], vmask);
+            if (F[i]) atomicXor(&W[(size_t)(l + i) * W2 + c * NW + gp.w], F[i] << gp.shift);
+            if (c == 1) e[i] = gauss_flip_energy(x[i], F[i]) - (x[i][0] + x[i][1] + x[i][2] + x[i][3]);
+          }
+        }
+        if (c == 1) {
+          // every lane of the wavefront is here: DPP sums
+          // (|sum| < 64 x 4 x 6 x 2^19 < 2^31), one LDS atomic each
+#pragma unroll
+          for (int i = 0; i < U; ++i) {
+            e[i] = wave_total(e[i]);
+            if (lane == 0)
+              atomicAdd(reinterpret_cast<unsigned long long*>(&El[l + i]),
+                        (unsigned long long)(int64_t)e[i]);
+          }
+        }
+      }
+    }
+    __syncthreads();
+  }
+}
+
 // One workgroup per sample, `n` steps of sweep (+ Houdayer) + exchange
 // (+ measurement at the job's interval).  The counters are read at the start;
 // the caller advances them by n steps afterwards.
 template <int D, bool HOU, bool MEAS>
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) k_gfused(Geo g, void* spins, const int4* __restrict__ Jg,
+__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) k_gfused(Geo g, void* spins, const int4* __restrict__ Jg,
                                                 int64_t* __restrict__ E64, int32_t* __restrict__ sot,
                                                 int32_t* __restrict__ tos,
                                                 const double* __restrict__ beta,
@@ -235,101 +379,29 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) k
   __syncthreads();
 
   const int4* Js = Jg + (size_t)s * 2 * (2 * D + 1) * NGc;
-  const uint32_t c3 = (kTagMetro << 28) | (uint32_t)s;
   for (int step = 0; step < n; ++step) {
     const uint32_t t = t0 + (uint32_t)step;
-    // ---- Metropolis sweep: colour 0 of every configuration, then colour 1.
-    // A thread takes a group of four same-colour sites (one Philox call, its
-    // coupling data in registers) and updates it in every configuration.
-    for (int c = 0; c < 2; ++c) {
-      const int4* Jc = Js + (size_t)c * (2 * D + 1) * NGc;
-      const uint32_t c1 = 2u * t + (uint32_t)c;
-      for (int gi0 = 0; gi0 < NGc; gi0 += T) {
-        // the group's position is recomputed every step: hoisted out of the
-        // step loop it would stay live through the Houdayer move, whose
-        // in-register cluster then no longer fits the register budget
-        int gi = gi0 + tid;
-        asm volatile("" : "+v"(gi));
-        const bool valid = gi < NGc;
-        int4 m[2 * D];
-        int4 hs = make_int4(0, 0, 0, 0);
-        GroupPos gp{};
-        WordNb nb{};
-        int p = 0;
-        uint32_t c0 = 0;
-        if (valid) {
-#pragma unroll
-          for (int k = 0; k < 2 * D; ++k) m[k] = Jc[(size_t)k * NGc + gi];
-          hs = Jc[(size_t)2 * D * NGc + gi];
-          gp = group_pos(g, gi);
-          nb = word_nb(g, gp.w);
-          p = (c + nb.par) & 1;
-          c0 = (uint32_t)word_row(g, nb, gp.f) * (uint32_t)g.G + (uint32_t)gp.q;
-        }
-        if constexpr (D == 2) {
-          // two configurations per round (2 N_T is even): two independent
-          // chains of loads, Philox rounds and compares for the scheduler
-          for (int l = 0; l < NS; l += 2) {
-            int dE0 = 0, dE1 = 0;
-            if (valid) {
-              uint32_t* W0 = W + (size_t)l * W2;
-              uint32_t* W1 = W0 + W2;
-              const uint32_t Wc0 = W0[c * NW + gp.w], Wc1 = W1[c * NW + gp.w];
-              uint32_t n0[2 * D], n1[2 * D], a0[2 * D], a1[2 * D];
-              neighbour_words<D>(g, W0 + (1 - c) * NW, gp.w, nb, p, n0);
-              neighbour_words<D>(g, W1 + (1 - c) * NW, gp.w, nb, p, n1);
-#pragma unroll
-              for (int k = 0; k < 2 * D; ++k) {
-                a0[k] = (Wc0 ^ n0[k]) >> gp.shift;
-                a1[k] = (Wc1 ^ n1[k]) >> gp.shift;
-              }
-              const Ctr4 r0 = philox10(Ctr4{c0, c1, (uint32_t)l, c3}, g.key0, g.key1);
-              const Ctr4 r1 = philox10(Ctr4{c0, c1, (uint32_t)l + 1u, c3}, g.key0, g.key1);
-              const int k0 = tosl[l], k1 = tosl[l + 1];
-              int x0[4], x1[4];
-              uint32_t F0, F1, u0, u1;
-              gauss_group_fast<D>(a0, m, hs, gp.nv, r0, czl[k0], x0, F0, u0);
-              gauss_group_fast<D>(a1, m, hs, gp.nv, r1, czl[k1], x1, F1, u1);
-              F0 = gauss_group_finish(x0, r0, bl[k0], F0, u0, dE0);
-              F1 = gauss_group_finish(x1, r1, bl[k1], F1, u1, dE1);
-              if (F0) atomicXor(&W0[c * NW + gp.w], F0 << gp.shift);
-              if (F1) atomicXor(&W1[c * NW + gp.w], F1 << gp.shift);
-            }
-            // every lane of the workgroup runs every round: DPP wavefront sums
-            // (|sum| < 64 x 4 x 2 x 6 x 2^19 < 2^31), one LDS atomic each
-            dE0 = wave_total(dE0);
-            dE1 = wave_total(dE1);
-            if (lane == 0) {
-              if (dE0)
-                atomicAdd(reinterpret_cast<unsigned long long*>(&El[l]), (unsigned long long)(int64_t)dE0);
-              if (dE1)
-                atomicAdd(reinterpret_cast<unsigned long long*>(&El[l + 1]), (unsigned long long)(int64_t)dE1);
-            }
-          }
-        } else {
-          // 3D: one configuration per round (two would not fit the register
-          // budget of four wavefronts per SIMD)
-          for (int l = 0; l < NS; ++l) {
-            int dE = 0;
-            if (valid) {
-              uint32_t* Wl = W + (size_t)l * W2;
-              const uint32_t Wc = Wl[c * NW + gp.w];
-              uint32_t nw[2 * D], a[2 * D];
-              neighbour_words<D>(g, Wl + (1 - c) * NW, gp.w, nb, p, nw);
-#pragma unroll
-              for (int k = 0; k < 2 * D; ++k) a[k] = (Wc ^ nw[k]) >> gp.shift;
-              const Ctr4 r = philox10(Ctr4{c0, c1, (uint32_t)l, c3}, g.key0, g.key1);
-              const int kt = tosl[l];
-              const uint32_t F = gauss_group_flips<D>(a, m, hs, gp.nv, r, czl[kt], bl[kt], dE);
-              if (F) atomicXor(&Wl[c * NW + gp.w], F << gp.shift);
-            }
-            dE = wave_total(dE);
-            if (lane == 0 && dE)
-              atomicAdd(reinterpret_cast<unsigned long long*>(&El[l]), (unsigned long long)(int64_t)dE);
-          }
-        }
+    // what the exchange pass needs from before it; the energies, which the
+    // sweep's colour-1 half sums anew
+    if (lay.acc >= 0) {
+      int32_t* sot0 = reinterpret_cast<int32_t*>(lds + lay.sot0);
+      for (int i = tid; i < NS; i += T) sot0[i] = sotl[i];
+      for (int i = tid; i < 2 * (NT - 1); i += T) {
+        const int c = i / (NT - 1), k = i - c * (NT - 1);
+        lds[lay.rpt + c * NT + k] =
+            philox10(Ctr4{(uint32_t)k, u0 + (uint32_t)step, (uint32_t)c, (kTagPT << 28) | (uint32_t)s},
+                     g.key0, g.key1).x;
       }
-      __syncthreads();
+    }
+    for (int i = tid; i < NS; i += T) El[i] = 0;
+    // ---- Metropolis sweep
+    if constexpr (D == 2) {
+      if (g.L == 64)
+        gauss_sweep_resident<D, 64>(fixed_shape<2, 64>(g), lay.team, W, El, tosl, czl, bl, Js, s, t);
+      else
+        gauss_sweep_resident<D, 0>(g, lay.team, W, El, tosl, czl, bl, Js, s, t);
+    } else {
+      gauss_sweep_resident<D, 0>(g, lay.team, W, El, tosl, czl, bl, Js, s, t);
     }
     // ---- Houdayer move per pair
     if (HOU) {
@@ -340,11 +412,20 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) k
         else
           gauss_houdayer_rows<0>(g, W, El, sotl, Js, s, v0 + (uint32_t)step, lds + lay.hq);
       } else {
-        gauss_houdayer_resident<D>(g, W, El, sotl, lds + lay.Qs, Js, s, v0 + (uint32_t)step);
+        gauss_houdayer_resident<D>(g, W, El, sotl, lds + lay.Qs, lay.PC, Js, s, v0 + (uint32_t)step);
       }
     }
-    // ---- replica exchange, one thread per set, k ascending with the updated map
-    if (lane == 0 && wave < 2) {
+    // ---- replica exchange, k ascending with the updated map
+    if (lay.acc >= 0) {
+      const int32_t* sot0 = reinterpret_cast<const int32_t*>(lds + lay.sot0);
+      const uint32_t* rpt = lds + lay.rpt;
+      exchange_decide(NT, 0, 2, lds + lay.acc, [&](int c, int k, int j) {
+        const int64_t Dl = El[c * NT + sot0[c * NT + k + 1]] - El[c * NT + sot0[c * NT + j]];
+        return Dl <= 0 || gauss_accept_d(rpt[c * NT + k], bl[k] - bl[k + 1], Dl);
+      });
+      __syncthreads();
+      exchange_chain<false>(NT, 0, 2, sotl, tosl, sot0, lds + lay.acc, nullptr, nullptr, 0u);
+    } else if (lane == 0 && wave < 2) {
       const int c = wave;
       const uint32_t u = u0 + (uint32_t)step;
       int32_t* so = sotl + c * NT;
@@ -411,8 +492,8 @@ template <int D, bool HOU, bool MEAS>
 hipError_t launch_gfused(const Geo& g, void* spins, const int4* Jg, int64_t* E64, int32_t* sot,
                          int32_t* tos, const double* beta, const float* cz, int64_t* mom,
                          const DevCounters* ctr, int n, int every, hipStream_t st) {
-  const int threads = gauss_fused_threads(g);
-  const GaussLayout lay = gauss_layout(g, threads / 64);
+  GaussLayout lay;
+  const int threads = gauss_fused_threads(g, lay);
   const size_t lds = sizeof(uint32_t) * (size_t)lay.words;
   auto k = k_gfused<D, HOU, MEAS>;
   if (lds > 65536) {
@@ -427,7 +508,11 @@ hipError_t launch_gfused(const Geo& g, void* spins, const int4* Jg, int64_t* E64
 }  // namespace
 
 size_t gauss_fused_lds(const Geo& g) {
-  return sizeof(uint32_t) * (size_t)gauss_layout(g, gauss_fused_threads(g) / 64).words;
+  const size_t least = gauss_least_lds(g);
+  if (least > kGaussFusedMaxLds) return least;
+  GaussLayout lay;
+  gauss_fused_threads(g, lay);
+  return sizeof(uint32_t) * (size_t)lay.words;
 }
 
 hipError_t launch_gauss_fused(const Geo& g, void* spins, const int4* Jg, int64_t* E64, int32_t* sot,
