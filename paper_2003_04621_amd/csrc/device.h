@@ -389,27 +389,6 @@ __device__ __forceinline__ int row_parity(const Geo& g, int R) {
   return R & 1;
 }
 
-// The q = -1 site with rank m (counted in increasing site order) inside row
-// R, given the two colour words of R's word w and its field f.  Returns the
-// colour c and the bit b = x0 >> 1 of that site within field f.
-__device__ __forceinline__ void select_in_row(const Geo& g, int R, uint32_t Q0, uint32_t Q1, int f,
-                                              uint32_t m, int& c_out, int& b_out) {
-  const int p0 = row_parity(g, R);
-  const uint32_t q0 = (Q0 >> (f * g.H)) & g.maskH, q1 = (Q1 >> (f * g.H)) & g.maskH;
-  c_out = -1;
-  b_out = 0;
-  for (int x0 = 0; x0 < g.L; ++x0) {
-    const int c = (x0 & 1) ^ p0;
-    if ((((c ? q1 : q0) >> (x0 >> 1)) & 1u) == 0) continue;
-    if (m == 0) {
-      c_out = c;
-      b_out = x0 >> 1;
-      return;
-    }
-    --m;
-  }
-}
-
 // Field rotations of a P*H-bit word: result field f = source field f+1
 // (rot_fields_down) or f-1 (rot_fields_up), cyclically.
 __device__ __forceinline__ uint32_t rot_fields_down(const Geo& g, uint32_t X) {

@@ -79,7 +79,7 @@ bool fused_plan(const Geo& g, bool hou, int nsets, int waves, FusedLayout& lay, 
     lay.Qs = take(pc * per, 2);
   } else if (hou && nsets == 2) {
     lay.hq = take(1, 1);  // Houdayer pair counter
-    if (!rows_houdayer(g)) {
+    if (!rows_houdayer(g) && !words_houdayer(g)) {
       // overlap and cluster words for each wavefront
       lay.PC = waves;
       lay.Qs = take((size_t)waves * 2 * W2, 1);

@@ -36,21 +36,6 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__device__ __forceinline__ int wave_sum(int v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
-__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v, int lane) {
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t t = __shfl_up(v, o, 64);
-    if (lane >= o) v += t;
-  }
-  return v;
-}
-
 // ---------------------------------------------------------------------------
 // Replica exchange for both sets of the resident sample.  The pass is
 // sequential in k, but every decision depends only on which configuration is
@@ -356,95 +341,6 @@ __device__ __forceinline__ void measure_resident(const FusedArgs& A, uint32_t* l
 }
 
 
-// Upward fill along the chain F_0, G_0, F_1, G_1, ... of every row field,
-// where F_b -> G_b and G_b -> F_(b+1) (no link across a field boundary; nLB
-// clears the lowest bit of each field): from seeds SF <= MF, SG <= MG, the
-// sites of the masks MF, MG reachable by increasing steps.  F sites that can
-// be entered from below form runs of R; adding the entry points Z to R
-// carries through each run up to its first gap, so (R + Z) ^ R marks the
-// reached bits of the run (an entry point already inside a carry is lost
-// from the sum, hence the | Z).
-__device__ __forceinline__ void chain_fill_up(uint32_t SF, uint32_t SG, uint32_t MF, uint32_t MG,
-                                              uint32_t nLB, uint32_t& UF, uint32_t& UG) {
-  const uint32_t Sp = SF | ((SG << 1) & nLB & MF);
-  const uint32_t R = (MG << 1) & MF & nLB;
-  const uint32_t Z = (Sp << 1) & R;
-  const uint32_t V = (R & ((R + Z) ^ R)) | Z;
-  UF = Sp | V;
-  UG = SG | (UF & MG);
-}
-
-// Closure along x0 of the cluster words of one word index in row form: E and
-// O hold the even and odd sites of each row field (E_0 O_0 E_1 O_1 ...), ME
-// and MO the q sites, rME and rMO their bit reversals.  Every site of q
-// linked to the cluster through a run of q sites of its row is added,
-// periodic in x0: an upward fill and a bit-reversed (downward) fill cover
-// each run from its lowest to its highest seed, and a run through the row's
-// end is continued from its other end in one more pass.
-__device__ __forceinline__ void row_closure(const Geo& g, uint32_t& E_io, uint32_t& O_io,
-                                            uint32_t ME, uint32_t MO, uint32_t rME, uint32_t rMO) {
-  const uint32_t nLB = ~g.LB, nLBr = ~__builtin_bitreverse32(g.HB);
-  uint32_t SE = E_io, SO = O_io;
-  for (;;) {
-    uint32_t UE, UO, DO, DE;
-    chain_fill_up(SE, SO, ME, MO, nLB, UE, UO);
-    chain_fill_up(__builtin_bitreverse32(SO), __builtin_bitreverse32(SE), rMO, rME, nLBr, DO, DE);
-    const uint32_t E = UE | __builtin_bitreverse32(DE), O = UO | __builtin_bitreverse32(DO);
-    const uint32_t nE = E | (((O & g.HB) >> (g.H - 1)) & ME);  // O_(H-1) -> E_0
-    const uint32_t nO = O | (((E & g.LB) << (g.H - 1)) & MO);  // E_0 -> O_(H-1)
-    if (nE == E && nO == O) {
-      E_io = E;
-      O_io = O;
-      return;
-    }
-    SE = nE;
-    SO = nO;
-  }
-}
-
-// The same closure for the colour words c0, c1 of a word whose rows have
-// parity p0 (the even sites of a row have colour p0).
-__device__ __forceinline__ void x0_closure(const Geo& g, uint32_t& c0, uint32_t& c1, uint32_t q0,
-                                           uint32_t q1, int p0) {
-  uint32_t E = p0 ? c1 : c0, O = p0 ? c0 : c1;
-  const uint32_t ME = p0 ? q1 : q0, MO = p0 ? q0 : q1;
-  row_closure(g, E, O, ME, MO, __builtin_bitreverse32(ME), __builtin_bitreverse32(MO));
-  c0 = p0 ? O : E;
-  c1 = p0 ? E : O;
-}
-
-// Grows both colour words w of a cluster: neighbours through other words,
-// then the closure along x0, where the two colour words of index w are each
-// other's only neighbours.  True if anything changed.  Stored cluster words
-// are closed along x0, so without new bits from other words there is nothing
-// to do, except on the first pass (`first`), which closes the seed.
-template <int D>
-__device__ __forceinline__ bool grow_pair(const Geo& g, uint32_t* C, const uint32_t* Q, int w,
-                                          bool first) {
-  const int NW = g.NW;
-  const uint32_t q0 = Q[w], q1 = Q[NW + w];
-  if (!(q0 | q1)) return false;
-  const WordNb q = word_nb(g, w);
-  const int p0 = q.par, p1 = 1 - q.par;  // p(0, w), p(1, w)
-  uint32_t n0[2 * D], n1[2 * D];
-  neighbour_words<D>(g, C + NW, w, q, p0, n0);  // colour-1 neighbours of colour-0 word
-  neighbour_words<D>(g, C, w, q, p1, n1);       // colour-0 neighbours of colour-1 word
-  uint32_t e0 = n0[2] | n0[3], e1 = n1[2] | n1[3];
-  if (D == 3) {
-    e0 |= n0[4] | n0[5];
-    e1 |= n1[4] | n1[5];
-  }
-  const uint32_t c0_old = C[w], c1_old = C[NW + w];
-  uint32_t c0 = c0_old | (q0 & e0);
-  uint32_t c1 = c1_old | (q1 & e1);
-  if (!(c0 | c1) || (!first && c0 == c0_old && c1 == c1_old)) return false;
-  x0_closure(g, c0, c1, q0, q1, p0);
-  if (c0 == c0_old && c1 == c1_old) return false;
-  C[w] = c0;
-  C[NW + w] = c1;
-  return true;
-}
-
 // ---------------------------------------------------------------------------
 // Column fills for a square lattice held one row per lane (2D: L <= 64 rows).
 // The even sites of row r have colour r & 1, and the site above bit b of row
@@ -528,31 +424,46 @@ __device__ __forceinline__ uint32_t column_fill(const ColumnChain& h, uint32_t c
   return u | d;
 }
 
-// The q site of rank m (counted in increasing x0) of a 64-site row held as
-// its even-site word E and odd-site word O (site x0 = 2b + e is bit b of E
-// for e = 0, of O for e = 1): sets that bit in SE or SO.  f(b), the number of
-// q sites with x0 < 2b, is nondecreasing; a binary search finds the largest
-// b with f(b) <= m, whose pair of sites holds the one sought.
-__device__ __forceinline__ void rank_in_row64(uint32_t E, uint32_t O, uint32_t m, uint32_t& SE,
-                                              uint32_t& SO) {
-  int b = 0;
-#pragma unroll
-  for (int st = 16; st >= 1; st >>= 1) {
-    const uint32_t lm = (1u << (b + st)) - 1u;
-    if ((uint32_t)(__popc(E & lm) + __popc(O & lm)) <= m) b += st;
-  }
-  const uint32_t lm = (1u << b) - 1u;
-  const bool even = ((E >> b) & 1u) && (uint32_t)(__popc(E & lm) + __popc(O & lm)) == m;
-  SE = even ? 1u << b : 0u;
-  SO = even ? 0u : 1u << b;
-}
-
 // x as a value that the compiler cannot hoist: what derives from it (masks,
 // addresses) is recomputed where it is used instead of staying live in
 // registers through the rest of the step loop.
 __device__ __forceinline__ int recomputed(int x) {
   asm volatile("" : "+v"(x));
   return x;
+}
+
+// The Houdayer cluster of pair k grown by one wavefront in LDS words (Qw, Cw:
+// 2 NW words each), for lattices of more words than lanes.  False if the pair
+// has no q = -1 site; else Cw holds the cluster's colour words.
+template <int D>
+__device__ __forceinline__ bool lds_cluster(const Geo& g, const uint32_t* Wa, const uint32_t* Wb,
+                                            uint32_t* Qw, uint32_t* Cw, int s, int k, uint32_t v,
+                                            int lane) {
+  const int NW = g.NW;
+  for (int w = lane; w < NW; w += 64) {
+    const uint32_t q0 = Wa[w] ^ Wb[w], q1 = Wa[NW + w] ^ Wb[NW + w];
+    const bool par = word_nb(g, w).par;
+    Qw[w] = par ? q1 : q0;
+    Qw[NW + w] = par ? q0 : q1;
+    Cw[w] = Cw[NW + w] = 0u;
+  }
+  wave_lds_sync();
+  if (!seed_words(g, Qw, Cw, s, k, v, lane)) return false;
+  wave_lds_sync();
+  for (bool first = true;; first = false) {
+    bool changed = false;
+    for (int w = lane; w < NW; w += 64) changed |= grow_rows<D>(g, Cw, Qw, w, first);
+    wave_lds_sync();
+    if (!__any(changed)) break;
+  }
+  for (int w = lane; w < NW; w += 64)
+    if (word_nb(g, w).par) {  // colour form
+      const uint32_t e = Cw[w];
+      Cw[w] = Cw[NW + w];
+      Cw[NW + w] = e;
+    }
+  wave_lds_sync();
+  return true;
 }
 
 // Geometry of a 2D row held by itself in a word's low H bits.
@@ -625,19 +536,11 @@ __device__ __forceinline__ bool rows_cluster(const Geo& g, const LaneRow& lr, in
   const uint32_t qx = odd ? q1 : q0, qy = odd ? q0 : q1;
   // q = -1 sites up to and including this row (a DPP scan over the rows)
   const uint32_t lc = __popc(q0) + __popc(q1);
-  uint32_t incl = lc;
-  incl += dpp_zero<kRowShr1>(incl);
-  incl += dpp_zero<kRowShr2>(incl);
-  incl += dpp_zero<kRowShr4>(incl);
-  incl += dpp_zero<kRowShr8>(incl);
-  incl += dpp_zero<kBcast15, 0xA>(incl);
-  incl += dpp_zero<kBcast31, 0xC>(incl);
+  const uint32_t incl = wave_scan(lc);
   const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
   if (n == 0) return false;
   // seed: the m-th q = -1 site in increasing site order (row by row)
-  const Ctr4 r = philox10(Ctr4{(uint32_t)k, v, 0u, (kTagHou << 28) | (uint32_t)s}, g.key0, g.key1);
-  const uint64_t r64 = (uint64_t)r.x | ((uint64_t)r.y << 32);
-  const uint32_t m = (uint32_t)__umul64hi(r64, (uint64_t)n);
+  const uint32_t m = seed_rank(g, s, k, v, n);
   uint32_t X = 0, Y = 0;  // cluster: even-site and odd-site words of the row
   if (m >= incl - lc && m < incl) rank_in_row64(qx, qy, m - (incl - lc), X, Y);
   const uint32_t rqx = __builtin_bitreverse32(qx), rqy = __builtin_bitreverse32(qy);
@@ -757,6 +660,153 @@ __device__ __forceinline__ void houdayer_rows(const Geo& gw, uint32_t* W, const 
 }
 
 // ---------------------------------------------------------------------------
+// The same move for a 3D sample with at most 64 words per colour, one word
+// index (P rows of one x1) per lane, everything in registers.  The cluster is
+// kept in row form (even and odd sites of each row field), in which the
+// neighbours along x1 and x2 of a lane's even word are the even words of four
+// other lanes.
+// ---------------------------------------------------------------------------
+__host__ __device__ inline bool words_houdayer(const Geo& g) { return g.d == 3 && g.NW <= 64; }
+
+// A lane's word: whether it exists, its neighbour geometry, and the lanes (as
+// ds_bpermute byte indices) holding the words next to it.  LS = 16: rows of 16
+// lanes are the x1 chains, so x1 neighbours are DPP row rotations.
+struct LaneWord {
+  WordNb nb;
+  int w, up1, dn1, ups, dns;
+  bool valid;
+};
+__device__ __forceinline__ LaneWord lane_word(const Geo& g, int lane) {
+  LaneWord r;
+  r.valid = lane < g.NW;
+  r.w = r.valid ? lane : 0;
+  r.nb = word_nb(g, r.w);
+  r.up1 = 4 * (r.valid ? r.nb.w1p : lane);
+  r.dn1 = 4 * (r.valid ? r.nb.w1m : lane);
+  r.ups = 4 * (r.valid ? r.nb.wsp : lane);
+  r.dns = 4 * (r.valid ? r.nb.wsm : lane);
+  return r;
+}
+constexpr int kRowRor1 = 0x121, kRowRor15 = 0x12F;  // lane i takes i - 1 / i + 1 (mod 16)
+template <int LS>
+__device__ __forceinline__ uint32_t word_up1(const LaneWord& r, uint32_t x) {
+  if constexpr (LS == 16) return dpp_zero<kRowRor15>(x);
+  return (uint32_t)__builtin_amdgcn_ds_bpermute(r.up1, (int)x);
+}
+template <int LS>
+__device__ __forceinline__ uint32_t word_dn1(const LaneWord& r, uint32_t x) {
+  if constexpr (LS == 16) return dpp_zero<kRowRor1>(x);
+  return (uint32_t)__builtin_amdgcn_ds_bpermute(r.dn1, (int)x);
+}
+__device__ __forceinline__ uint32_t word_ups(const Geo& g, const LaneWord& r, uint32_t x) {
+  const uint32_t y = (uint32_t)__builtin_amdgcn_ds_bpermute(r.ups, (int)x);
+  return r.nb.crp ? rot_fields_down(g, y) : y;
+}
+__device__ __forceinline__ uint32_t word_dns(const Geo& g, const LaneWord& r, uint32_t x) {
+  const uint32_t y = (uint32_t)__builtin_amdgcn_ds_bpermute(r.dns, (int)x);
+  return r.nb.crm ? rot_fields_up(g, y) : y;
+}
+
+// The Houdayer cluster of pair k: as rows_cluster, with the fill advancing one
+// word along x1 and x2 per round and a whole run along x0.  c0, c1: the
+// cluster's colour-0 and colour-1 bits of this lane's word.
+template <int LS>
+__device__ __forceinline__ bool words_cluster(const Geo& g, const LaneWord& lw, const uint32_t* Wa,
+                                              const uint32_t* Wb, int s, int k, uint32_t v, uint32_t& c0,
+                                              uint32_t& c1) {
+  const int NW = g.NW;
+  const bool par = lw.nb.par;
+  uint32_t q0 = Wa[lw.w] ^ Wb[lw.w], q1 = Wa[NW + lw.w] ^ Wb[NW + lw.w];
+  if (!lw.valid) q0 = q1 = 0u;
+  const uint32_t ME = par ? q1 : q0, MO = par ? q0 : q1;
+  const uint32_t n = (uint32_t)wave_total(__popc(ME) + __popc(MO));
+  if (n == 0) return false;
+  uint32_t m = seed_rank(g, s, k, v, n);
+  // site order is field by field, then lane by lane (x2 = f B + xs', then x1)
+  uint32_t E = 0, O = 0;
+  for (int f = 0;; ++f) {
+    const uint32_t fe = (ME >> (f * g.H)) & g.maskH, fo = (MO >> (f * g.H)) & g.maskH;
+    const uint32_t lc = __popc(fe) + __popc(fo), incl = wave_scan(lc);
+    const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+    if (m >= tot) {
+      m -= tot;
+      continue;
+    }
+    if (m >= incl - lc && m < incl) {
+      rank_in_row64(fe, fo, m - (incl - lc), E, O);
+      E <<= f * g.H;
+      O <<= f * g.H;
+    }
+    break;
+  }
+  const uint32_t rME = __builtin_bitreverse32(ME), rMO = __builtin_bitreverse32(MO);
+  row_fill(g, E, O, ME, MO, rME, rMO);
+  for (;;) {
+    const uint32_t xe = word_up1<LS>(lw, E) | word_dn1<LS>(lw, E) | word_ups(g, lw, E) | word_dns(g, lw, E);
+    const uint32_t xo = word_up1<LS>(lw, O) | word_dn1<LS>(lw, O) | word_ups(g, lw, O) | word_dns(g, lw, O);
+    uint32_t nE = E | (ME & (xe | ((O & g.HB) >> (g.H - 1))));
+    uint32_t nO = O | (MO & (xo | ((E & g.LB) << (g.H - 1))));
+    if (!__any(nE != E || nO != O)) break;
+    E = nE;
+    O = nO;
+    row_fill(g, E, O, ME, MO, rME, rMO);
+  }
+  c0 = par ? O : E;
+  c1 = par ? E : O;
+  return true;
+}
+
+// Houdayer moves of such a sample, one wavefront per pair at a time.  Bound by
+// the rounds of the fill (a round waits for its cross-lane moves); 3D L = 12,
+// 256 samples x 2 x 20: 30 -> 15 us of a 49 -> 34 us step against the fill
+// through LDS words; L = 16: 34 -> 12 us.
+template <int LS>
+__device__ __forceinline__ void houdayer_words(const Geo& g, uint32_t* W, const uint32_t* Jl, int32_t* El,
+                                               const int32_t* sotl, int s, uint32_t v, uint32_t* hctr,
+                                               int lane) {
+  const int NT = g.NT, NW = g.NW;
+  const LaneWord lw = lane_word(g, lane);
+  for (;;) {
+    const int k = take_pair_hottest(hctr, NT);
+    if (k < 0) break;
+    const int a = sotl[k], b = NT + sotl[NT + k];
+    uint32_t* Wa = W + (size_t)a * 2 * NW;
+    uint32_t* Wb = W + (size_t)b * 2 * NW;
+    uint32_t c0, c1;
+    if (!words_cluster<LS>(g, lw, Wa, Wb, s, k, v, c0, c1)) continue;
+    // energy change of replica a over the bonds of the colour-0 sites
+    uint32_t nc[6], na[6];
+    x0_neighbours(g, c1, lw.nb.par, nc[0], nc[1]);
+    nc[2] = word_up1<LS>(lw, c1);
+    nc[3] = word_dn1<LS>(lw, c1);
+    nc[4] = word_ups(g, lw, c1);
+    nc[5] = word_dns(g, lw, c1);
+    neighbour_words<3>(g, Wa + NW, lw.w, lw.nb, lw.nb.par, na);
+    const uint32_t a0 = Wa[lw.w];
+    int cross = 0, cross_u = 0;
+#pragma unroll
+    for (int dir = 0; dir < 6; ++dir) {
+      const uint32_t X = c0 ^ nc[dir];
+      const uint32_t U = a0 ^ na[dir] ^ Jl[dir * NW + lw.w];
+      cross += __popc(X);
+      cross_u += __popc(X & U);
+    }
+    const int delta = wave_total(lw.valid ? 2 * (cross - 2 * cross_u) : 0);
+    wave_lds_sync();  // every lane has read its neighbours' words
+    if (lw.valid) {
+      Wa[lw.w] ^= c0;
+      Wa[NW + lw.w] ^= c1;
+      Wb[lw.w] ^= c0;
+      Wb[NW + lw.w] ^= c1;
+    }
+    if (lane == 0) {
+      El[a] += delta;
+      El[b] -= delta;
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Houdayer moves for all NT pairs of the resident sample: each wavefront
 // takes one pair at a time and grows its cluster alone, so clusters of very
 // different size (cold versus hot pairs) do not wait for one another.
@@ -766,74 +816,52 @@ __device__ __forceinline__ void houdayer_resident(const FusedArgs& A, uint32_t* 
                                                   uint32_t v) {
   const Geo& g = A.g;
   const int NT = g.NT, NW = g.NW, tid = threadIdx.x;
-  const int wave = tid >> 6, lane = tid & 63, nwave = blockDim.x >> 6;
+  const int wave = tid >> 6, lane = tid & 63;
   uint32_t* W = lds + A.lay.W;
   const uint32_t* Jl = lds + A.lay.J;  // colour-0 direction words first
   int32_t* El = reinterpret_cast<int32_t*>(lds + A.lay.E);
   const int32_t* sotl = reinterpret_cast<const int32_t*>(lds + A.lay.sot);
+  uint32_t* hctr = lds + A.lay.hq;
   if constexpr (D == 2) {
     if (g.L == 64)
-      houdayer_rows<64>(fixed_shape<2, 64>(g), W, Jl, El, sotl, s, v, lds + A.lay.hq, recomputed(lane));
+      houdayer_rows<64>(fixed_shape<2, 64>(g), W, Jl, El, sotl, s, v, hctr, recomputed(lane));
     else
-      houdayer_rows<0>(g, W, Jl, El, sotl, s, v, lds + A.lay.hq, recomputed(lane));
-    __syncthreads();
-    if (tid == 0) lds[A.lay.hq] = 0u;  // the next use is behind the step's barriers
-    return;
-  }
-  const int W2 = 2 * NW;
-  uint32_t* Qw = lds + A.lay.Qs + (size_t)wave * 2 * W2;
-  uint32_t* Cw = Qw + W2;
-  const int rpl = (g.NR + 63) / 64;  // rows per lane for the seed search
-  for (int k = wave; k < NT; k += nwave) {
-    const int a = sotl[k], b = NT + sotl[NT + k];
-    uint32_t* Wa = W + (size_t)a * W2;
-    uint32_t* Wb = W + (size_t)b * W2;
-    int cnt = 0;
-    for (int i = lane; i < W2; i += 64) {
-      const uint32_t q = Wa[i] ^ Wb[i];
-      Qw[i] = q;
-      Cw[i] = 0;
-      cnt += __popc(q);
-    }
-    const uint32_t n = (uint32_t)wave_sum(cnt);
-    if (n == 0) continue;
-    wave_lds_sync();
-    // seed: the m-th q = -1 site in increasing i; lanes own contiguous rows
-    const Ctr4 r = philox10(Ctr4{(uint32_t)k, v, 0u, (kTagHou << 28) | (uint32_t)s}, g.key0, g.key1);
-    const uint64_t r64 = (uint64_t)r.x | ((uint64_t)r.y << 32);
-    const uint32_t m = (uint32_t)__umul64hi(r64, (uint64_t)n);
-    const int r0 = min(g.NR, lane * rpl), r1 = min(g.NR, r0 + rpl);
-    uint32_t lc = 0;
-    for (int R = r0; R < r1; ++R) lc += row_minus_count(g, Qw, R);
-    const uint32_t incl = wave_inclusive_scan(lc, lane);
-    if (m >= incl - lc && m < incl) seed_in_rows(g, Qw, Cw, r0, r1, m - (incl - lc));
-    wave_lds_sync();
-    // flood fill until no word of the pair changes
-    for (bool first = true;; first = false) {
-      int changed = 0;
-      for (int w = lane; w < NW; w += 64)
-        if (grow_pair<D>(g, Cw, Qw, w, first)) changed = 1;
-      wave_lds_sync();
-      if (!__any(changed)) break;
-    }
-    // energy change of replica a, then exchange the replicas on the cluster
-    int dl = 0;
-    for (int w = lane; w < NW; w += 64) dl += cluster_delta_word<D>(g, Cw, Wa, Jl, w);
-    const int delta = wave_sum(dl);
-    for (int i = lane; i < W2; i += 64) {
-      const uint32_t cw = Cw[i];
-      if (cw) {
-        Wa[i] ^= cw;
-        Wb[i] ^= cw;
+      houdayer_rows<0>(g, W, Jl, El, sotl, s, v, hctr, recomputed(lane));
+  } else if (g.L == 16) {
+    houdayer_words<16>(fixed_shape<3, 16>(g), W, Jl, El, sotl, s, v, hctr, recomputed(lane));
+  } else if (words_houdayer(g)) {
+    houdayer_words<0>(g, W, Jl, El, sotl, s, v, hctr, recomputed(lane));
+  } else {
+    const int W2 = 2 * NW;
+    uint32_t* Qw = lds + A.lay.Qs + (size_t)wave * 2 * W2;  // row form
+    uint32_t* Cw = Qw + W2;
+    for (;;) {
+      const int k = take_pair_hottest(hctr, NT);
+      if (k < 0) break;
+      const int a = sotl[k], b = NT + sotl[NT + k];
+      uint32_t* Wa = W + (size_t)a * W2;
+      uint32_t* Wb = W + (size_t)b * W2;
+      if (!lds_cluster<D>(g, Wa, Wb, Qw, Cw, s, k, v, lane)) continue;
+      // energy change of replica a, then exchange the replicas on the cluster
+      int dl = 0;
+      for (int w = lane; w < NW; w += 64) dl += cluster_delta_word<D>(g, Cw, Wa, Jl, w);
+      const int delta = wave_total(dl);
+      for (int i = lane; i < W2; i += 64) {
+        const uint32_t cw = Cw[i];
+        if (cw) {
+          Wa[i] ^= cw;
+          Wb[i] ^= cw;
+        }
       }
+      if (lane == 0) {
+        El[a] += delta;
+        El[b] -= delta;
+      }
+      wave_lds_sync();
     }
-    if (lane == 0) {
-      El[a] += delta;
-      El[b] -= delta;
-    }
-    wave_lds_sync();
   }
   __syncthreads();
+  if (tid == 0) *hctr = 0u;  // the next use is behind the step's barriers
 }
 
 // ---------------------------------------------------------------------------
@@ -865,7 +893,7 @@ __device__ __forceinline__ void houdayer_multi_resident(const FusedArgs& A, uint
       multi_cluster_words<D>(g, Qw, Cw, Cw + W2, s, k, v, lane, 64, [] { wave_lds_sync(); });
       int dl = 0;
       for (int w = lane; w < NW; w += 64) dl += cluster_delta_word<D>(g, Cw, Wa, Jl, w);
-      const int delta = wave_sum(dl);
+      const int delta = wave_total(dl);
       for (int i = lane; i < W2; i += 64) {
         const uint32_t cw = Cw[i];
         if (cw) {

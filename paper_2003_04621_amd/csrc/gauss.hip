@@ -252,7 +252,7 @@ __global__ void k_gexchange(Geo g, const int64_t* __restrict__ E64, int32_t* __r
 // if the bond's two spins of replica a are antiparallel.
 // ---------------------------------------------------------------------------
 template <int D, bool MULTI>
-__global__ void __launch_bounds__(256) k_ghoudayer(Geo g, void* spins, const int4* __restrict__ Jg,
+__global__ void __launch_bounds__(MULTI ? 256 : 1024) k_ghoudayer(Geo g, void* spins, const int4* __restrict__ Jg,
                                                    int64_t* __restrict__ E64,
                                                    const int32_t* __restrict__ sot,
                                                    const DevCounters* __restrict__ ctr) {
@@ -262,8 +262,7 @@ __global__ void __launch_bounds__(256) k_ghoudayer(Geo g, void* spins, const int
   uint32_t* A = lds_h;         // replica a, both colours
   uint32_t* Q = A + 2 * NW;    // overlap words (later replica b)
   uint32_t* Cl = Q + 2 * NW;   // exchanged sites
-  uint32_t* scr = Cl + 2 * NW; // single: chunk prefix sums [T]; multi: the team's scratch
-  __shared__ uint32_t n_minus;
+  uint32_t* scr = Cl + 2 * NW; // multi: the team's scratch
   __shared__ unsigned long long delta_acc;
 
   const uint32_t v = load_counter(&ctr->v);
@@ -277,47 +276,12 @@ __global__ void __launch_bounds__(256) k_ghoudayer(Geo g, void* spins, const int
   load_lattice(g, spins, lat_b, Q, t, T);
   if (t == 0) delta_acc = 0ull;
   __syncthreads();
-  for (int i = t; i < 2 * NW; i += T) {
-    Q[i] ^= A[i];
-    Cl[i] = 0;
-  }
-  __syncthreads();
   if constexpr (MULTI) {
+    for (int i = t; i < 2 * NW; i += T) Q[i] ^= A[i];
+    __syncthreads();
     multi_cluster_words<D>(g, Q, Cl, scr, s, k, v, t, T, [] { __syncthreads(); });
   } else {
-    const int chunk = (g.NR + T - 1) / T;
-    const int r_begin = t * chunk, r_end = min(g.NR, r_begin + chunk);
-    uint32_t cnt = 0;
-    for (int R = r_begin; R < r_end; ++R) cnt += row_minus_count(g, Q, R);
-    scr[t] = cnt;
-    __syncthreads();
-    if (t == 0) {
-      uint32_t run = 0;
-      for (int i = 0; i < T; ++i) {
-        const uint32_t c = scr[i];
-        scr[i] = run;
-        run += c;
-      }
-      n_minus = run;
-    }
-    __syncthreads();
-    const uint32_t n = n_minus;
-    if (n == 0) return;  // uniform: nothing to exchange
-    const Ctr4 r = philox10(Ctr4{(uint32_t)k, v, 0u, (kTagHou << 28) | (uint32_t)s}, g.key0, g.key1);
-    const uint64_t r64 = (uint64_t)r.x | ((uint64_t)r.y << 32);
-    const uint32_t m = (uint32_t)__umul64hi(r64, (uint64_t)n);
-    if (m >= scr[t] && m < scr[t] + cnt) seed_in_rows(g, Q, Cl, r_begin, r_end, m - scr[t]);
-    __syncthreads();
-    int any;
-    do {
-      int changed = 0;
-      for (int c = 0; c < 2; ++c) {
-        for (int w = t; w < NW; w += T)
-          if (grow_word<D>(g, Cl, Q, c, w)) changed = 1;
-        if (c == 0) __syncthreads();
-      }
-      any = __syncthreads_or(changed);
-    } while (any);
+    if (!team_cluster<D>(g, A, Q, Cl, s, k, v, t, T)) return;  // uniform: nothing to exchange
   }
   const int4* J0 = Jg + (size_t)s * 2 * (2 * D + 1) * gauss_groups(g);
   const int64_t dl = gauss_cluster_delta<D>(g, Cl, A, J0, t, T);
@@ -478,15 +442,15 @@ hipError_t launch_gauss_exchange(const Geo& g, const int64_t* E64, int32_t* sot,
 hipError_t launch_gauss_houdayer(const Geo& g, void* spins, const int4* Jg, int64_t* E64,
                                  const int32_t* sot, const DevCounters* ctr, bool multi,
                                  hipStream_t st) {
-  // single cluster: one thread per colour word of the flood fill (at most
-  // 256), so that a lattice with few words grows its cluster in one
-  // wavefront; the multi-cluster teams take 256 threads
-  const int threads = multi ? 256 : std::min(256, (g.NW + 63) / 64 * 64);
+  // single cluster: one thread per word of the flood fill (team_threads), so
+  // that a lattice with few words grows its cluster in one wavefront; the
+  // multi-cluster teams take 256 threads
+  const int threads = multi ? 256 : team_threads(g);
   if (multi && g.N > kMultiMaxSites) return hipErrorInvalidValue;
-  // A, Q and the cluster words (6 NW), then the chunk sums [threads], or for
-  // the multi-cluster move A and the team scratch (which begins with Q and C)
+  // A, Q and the cluster words (6 NW), or for the multi-cluster move A and the
+  // team scratch (which begins with Q and C)
   const size_t words = multi ? 2 * (size_t)g.NW + (size_t)multi_scratch_words(g.N, g.NR, g.NW)
-                             : 6 * (size_t)g.NW + (size_t)threads;
+                             : 6 * (size_t)g.NW;
   const size_t lds = sizeof(uint32_t) * words;
   const unsigned blocks = (unsigned)(g.S * g.NT);
 #define PTSG_GH(DD, MM)                                                                          \

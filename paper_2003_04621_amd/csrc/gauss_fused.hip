@@ -124,36 +124,22 @@ __device__ void gauss_houdayer_resident(const Geo& g, uint32_t* W, int64_t* El, 
   const int wave = tid >> 6, lane = tid & 63;
   uint32_t* Qw = Qs + (size_t)wave * 2 * W2;
   uint32_t* Cw = Qw + W2;
-  const int rpl = (g.NR + 63) / 64;  // rows per lane for the seed search
+  const bool in_regs = words_houdayer(g);
+  const LaneWord lw = in_regs ? lane_word(g, lane) : LaneWord{};
   for (int k = wave < PC ? wave : NT; k < NT; k += PC) {
     const int a = sotl[k], b = NT + sotl[NT + k];
     uint32_t* Wa = W + (size_t)a * W2;
     uint32_t* Wb = W + (size_t)b * W2;
-    int cnt = 0;
-    for (int i = lane; i < W2; i += 64) {
-      const uint32_t q = Wa[i] ^ Wb[i];
-      Qw[i] = q;
-      Cw[i] = 0;
-      cnt += __popc(q);
-    }
-    const uint32_t n = (uint32_t)wave_total(cnt);
-    if (n == 0) continue;
-    wave_lds_sync();
-    const Ctr4 r = philox10(Ctr4{(uint32_t)k, v, 0u, (kTagHou << 28) | (uint32_t)s}, g.key0, g.key1);
-    const uint64_t r64 = (uint64_t)r.x | ((uint64_t)r.y << 32);
-    const uint32_t m = (uint32_t)__umul64hi(r64, (uint64_t)n);
-    const int r0 = min(g.NR, lane * rpl), r1 = min(g.NR, r0 + rpl);
-    uint32_t lc = 0;
-    for (int R = r0; R < r1; ++R) lc += row_minus_count(g, Qw, R);
-    const uint32_t incl = wave_inclusive_scan(lc, lane);
-    if (m >= incl - lc && m < incl) seed_in_rows(g, Qw, Cw, r0, r1, m - (incl - lc));
-    wave_lds_sync();
-    for (bool first = true;; first = false) {
-      int changed = 0;
-      for (int w = lane; w < NW; w += 64)
-        if (grow_pair<D>(g, Cw, Qw, w, first)) changed = 1;
+    if (in_regs) {
+      uint32_t c0, c1;
+      if (!words_cluster<0>(g, lw, Wa, Wb, s, k, v, c0, c1)) continue;
+      if (lw.valid) {
+        Cw[lw.w] = c0;
+        Cw[NW + lw.w] = c1;
+      }
       wave_lds_sync();
-      if (!__any(changed)) break;
+    } else if (!lds_cluster<D>(g, Wa, Wb, Qw, Cw, s, k, v, lane)) {
+      continue;
     }
     const int64_t delta = wave_sum64(gauss_cluster_delta<D>(g, Cw, Wa, J0, lane, 64));
     for (int i = lane; i < W2; i += 64) {

@@ -1,9 +1,9 @@
-"""Single-cluster Houdayer moves inside the fused steps at the sizes where the
-in-register cluster can go wrong: rows of 2 to 32 sites per colour, one to
-several row fields per word, lattices that fill the wavefront's lanes and
-lattices that leave lanes empty.  Ladders start cold, so that clusters wrap
-around the lattice.  Everything is exact: spins, energies, maps and moments
-equal the oracle's (+-J) or the per-step kernels' (Gaussian couplings)."""
+"""Single-cluster Houdayer moves at the sizes where a cluster can go wrong: in
+registers, rows of 2 to 32 sites per colour, one to several row fields per word,
+lattices that fill the wavefront's lanes and lattices that leave lanes empty;
+in LDS, lattices of more words than lanes; and the per-step kernels.  Ladders
+start cold, so that clusters wrap around the lattice.  Everything is exact:
+spins, energies, maps and moments equal the oracle's."""
 import numpy as np
 import pytest
 
@@ -28,6 +28,17 @@ CASES = [(2, L, 2, nt, lay, 30) for L, nt, lay in
           (34, 3, 0), (46, 3, 1), (48, 4, 0), (50, 17, 1), (62, 3, 0), (64, 4, 0)]]
 
 
+CASES += [(3, L, 2, nt, lay, 12) for L, nt, lay in
+          [(4, 3, 0), (6, 2, 1), (8, 5, 0), (10, 18, 0), (12, 4, 1), (14, 3, 0), (16, 4, 0), (16, 17, 1), (18, 2, 0),
+           (20, 3, 1), (24, 2, 0)]]
+
+
+def same(pt, job, ref):
+    for a, b in zip(pt.pt_get_maps(job), ref.maps()):
+        assert (a == b).all()
+    assert (pt.pt_get_spins(job) == ref.spins()).all()
+
+
 @pytest.mark.parametrize("d,L,S,NT,layout,steps", CASES)
 def test_fused_clusters_match_oracle(pt, d, L, S, NT, layout, steps):
     J = W.couplings_pm_j(S, L, d, 40 + L)
@@ -39,28 +50,36 @@ def test_fused_clusters_match_oracle(pt, d, L, S, NT, layout, steps):
         pt.pt_mcs(job, n, houdayer=True, measure=True)
         ref.mcs(n, houdayer=True, measure=True)
         assert (pt.pt_get_energies(job) == ref.energies()).all()
-        for a, b in zip(pt.pt_get_maps(job), ref.maps()):
-            assert (a == b).all()
-        assert (pt.pt_get_spins(job) == ref.spins()).all()
+        same(pt, job, ref)
         gm, rm = pt.pt_get_moments(job), ref.moments()
         for k in rm:
             assert (np.asarray(gm[k]) == np.asarray(rm[k]).astype(np.asarray(gm[k]).dtype)).all(), k
     pt.pt_destroy(job)
 
 
+@pytest.mark.parametrize("plain", [False, True])
 @pytest.mark.parametrize("d,L,S,NT,layout,steps", CASES)
-def test_fused_clusters_match_steps_gauss(pt, d, L, S, NT, layout, steps):
+def test_gauss_clusters_match_oracle(pt, d, L, S, NT, layout, steps, plain):
     J = W.couplings_gauss(S, L, d, 60 + L)
     betas = W.geometric_betas(0.3 if d == 2 else 0.7, 2.5, NT)
-    a = pt.pt_init_gauss(S, NT, L, d, J, betas, 99 + L, layout=layout)
-    b = pt.pt_init_gauss(S, NT, L, d, J, betas, 99 + L, layout=layout)
-    assert pt.pt_get_plan(a, houdayer=True)["mode"] == 0
-    pt.pt_mcs(a, steps, houdayer=True, measure=True)
-    pt.pt_mcs(b, steps, houdayer=True, measure=True, plain=True)
-    assert (pt.pt_get_energies64(a) == pt.pt_get_energies64(b)).all()
-    for x, y in zip(pt.pt_get_maps(a), pt.pt_get_maps(b)):
-        assert (x == y).all()
-    assert (pt.pt_get_spins(a) == pt.pt_get_spins(b)).all()
-    assert (pt.pt_get_moments8(a) == pt.pt_get_moments8(b)).all()
-    pt.pt_destroy(a)
-    pt.pt_destroy(b)
+    job = pt.pt_init_gauss(S, NT, L, d, J, betas, 99 + L, layout=layout)
+    assert pt.pt_get_plan(job, houdayer=True, plain=plain)["mode"] == (-1 if plain else 0)
+    ref = oracle.OracleGaussJob(S, NT, L, d, W.gauss_units(J), betas, 99 + L)
+    pt.pt_mcs(job, steps, houdayer=True, measure=True, plain=plain)
+    ref.mcs(steps, houdayer=True, measure=True)
+    assert (pt.pt_get_energies64(job) == ref.energies()).all()
+    same(pt, job, ref)
+    pt.pt_destroy(job)
+
+
+@pytest.mark.parametrize("d,L,S,NT,layout,steps", CASES + [(3, 28, 1, 2, 0, 3), (3, 32, 1, 2, 1, 3), (3, 36, 1, 2, 0, 2)])
+def test_step_clusters_match_oracle(pt, d, L, S, NT, layout, steps):
+    J = W.couplings_pm_j(S, L, d, 20 + L)
+    betas = W.geometric_betas(0.3 if d == 2 else 0.7, 2.5, NT)
+    job = pt.pt_init(S, NT, L, d, J, betas, 55 + L, layout=layout, stats=True)
+    ref = oracle.OracleJob(S, NT, L, d, J, betas, 55 + L)
+    pt.pt_mcs(job, steps, houdayer=True, measure=True)
+    ref.mcs(steps, houdayer=True, measure=True)
+    assert (pt.pt_get_energies(job) == ref.energies()).all()
+    same(pt, job, ref)
+    pt.pt_destroy(job)
