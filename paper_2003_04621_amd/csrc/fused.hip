@@ -71,9 +71,10 @@ bool fused_plan(const Geo& g, bool hou, int nsets, int waves, FusedLayout& lay, 
     // multi-cluster moves: a scratch area for each of the first PC
     // wavefronts (8-byte aligned: the row masks are 64-bit), as many as fit
     if (g.N > kMultiMaxSites) return false;
-    const size_t per = (size_t)((multi_scratch_words(g.N, g.NR, g.NW) + 1) & ~1);
+    const size_t per = (size_t)((multi_scratch_words(g) + 1) & ~1);
+    lay.hq = take(1, 1);  // Houdayer pair counter
     const size_t base = (off + 1) / 2 * 2;
-    int pc = waves < 8 ? waves : 8;
+    int pc = waves < g.NT ? waves : g.NT;
     while (pc > 1 && base + pc * per > budget) --pc;
     lay.PC = pc;
     lay.Qs = take(pc * per, 2);

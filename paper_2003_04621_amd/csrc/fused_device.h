@@ -866,7 +866,7 @@ __device__ __forceinline__ void houdayer_resident(const FusedArgs& A, uint32_t* 
 
 // ---------------------------------------------------------------------------
 // Multi-cluster Houdayer moves for all NT pairs of the resident sample: the
-// first PC wavefronts (those with a scratch area) take the pairs in turn,
+// first PC wavefronts (those with a scratch area) take the pairs, hottest first,
 // each finding the exchanged clusters of its pair (multi_cluster_words),
 // then applying them as the single-cluster move applies its cluster.
 // ---------------------------------------------------------------------------
@@ -881,16 +881,23 @@ __device__ __forceinline__ void houdayer_multi_resident(const FusedArgs& A, uint
   int32_t* El = reinterpret_cast<int32_t*>(lds + A.lay.E);
   const int32_t* sotl = reinterpret_cast<const int32_t*>(lds + A.lay.sot);
   if (wave < PC) {
-    const int stride = (multi_scratch_words(g.N, g.NR, NW) + 1) & ~1;
+    const int stride = (multi_scratch_words(g) + 1) & ~1;
     uint32_t* Qw = lds + A.lay.Qs + (size_t)wave * stride;
     uint32_t* Cw = Qw + W2;
-    for (int k = wave; k < NT; k += PC) {
+    for (;;) {
+      const int k = take_pair_hottest(lds + A.lay.hq, NT);
+      if (k < 0) break;
       const int a = sotl[k], b = NT + sotl[NT + k];
       uint32_t* Wa = W + (size_t)a * W2;
       uint32_t* Wb = W + (size_t)b * W2;
       for (int i = lane; i < W2; i += 64) Qw[i] = Wa[i] ^ Wb[i];
       wave_lds_sync();
-      multi_cluster_words<D>(g, Qw, Cw, Cw + W2, s, k, v, lane, 64, [] { wave_lds_sync(); });
+      multi_cluster_words<D>(
+          g, Qw, Cw, Cw + W2, s, k, v, lane, 64, [] { wave_lds_sync(); },
+          [](bool b) {
+            wave_lds_sync();
+            return (bool)__any(b);
+          });
       int dl = 0;
       for (int w = lane; w < NW; w += 64) dl += cluster_delta_word<D>(g, Cw, Wa, Jl, w);
       const int delta = wave_total(dl);
@@ -909,6 +916,7 @@ __device__ __forceinline__ void houdayer_multi_resident(const FusedArgs& A, uint
     }
   }
   __syncthreads();
+  if (tid == 0) lds[A.lay.hq] = 0u;  // the next use is behind the step's barriers
 }
 
 // ---------------------------------------------------------------------------

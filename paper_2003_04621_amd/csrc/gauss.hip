@@ -279,7 +279,9 @@ __global__ void __launch_bounds__(MULTI ? 256 : 1024) k_ghoudayer(Geo g, void* s
   if constexpr (MULTI) {
     for (int i = t; i < 2 * NW; i += T) Q[i] ^= A[i];
     __syncthreads();
-    multi_cluster_words<D>(g, Q, Cl, scr, s, k, v, t, T, [] { __syncthreads(); });
+    multi_cluster_words<D>(
+        g, Q, Cl, scr, s, k, v, t, T, [] { __syncthreads(); },
+        [](bool b) { return __syncthreads_or(b) != 0; });
   } else {
     if (!team_cluster<D>(g, A, Q, Cl, s, k, v, t, T)) return;  // uniform: nothing to exchange
   }
@@ -449,7 +451,7 @@ hipError_t launch_gauss_houdayer(const Geo& g, void* spins, const int4* Jg, int6
   if (multi && g.N > kMultiMaxSites) return hipErrorInvalidValue;
   // A, Q and the cluster words (6 NW), or for the multi-cluster move A and the
   // team scratch (which begins with Q and C)
-  const size_t words = multi ? 2 * (size_t)g.NW + (size_t)multi_scratch_words(g.N, g.NR, g.NW)
+  const size_t words = multi ? 2 * (size_t)g.NW + (size_t)multi_scratch_words(g)
                              : 6 * (size_t)g.NW;
   const size_t lds = sizeof(uint32_t) * words;
   const unsigned blocks = (unsigned)(g.S * g.NT);

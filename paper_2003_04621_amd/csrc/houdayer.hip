@@ -121,7 +121,9 @@ __global__ void __launch_bounds__(256) k_houdayer_multi(Geo g, void* spins,
   __syncthreads();
   for (int i = t; i < 2 * NW; i += T) Q[i] ^= A[i];
   __syncthreads();
-  multi_cluster_words<D>(g, Q, Cl, scr, s, k, v, t, T, [] { __syncthreads(); });
+  multi_cluster_words<D>(
+      g, Q, Cl, scr, s, k, v, t, T, [] { __syncthreads(); },
+      [](bool b) { return __syncthreads_or(b) != 0; });
 
   const uint32_t* jw0 = jw + (size_t)s * 2 * 2 * D * NW;
   int dl = 0;
@@ -153,7 +155,7 @@ hipError_t launch_houdayer_multi(const Geo& g, void* spins, const uint32_t* jw, 
                                  hipStream_t st) {
   if (g.N > kMultiMaxSites) return hipErrorInvalidValue;
   const int threads = 256;
-  const size_t lds = sizeof(uint32_t) * (2 * (size_t)g.NW + multi_scratch_words(g.N, g.NR, g.NW));
+  const size_t lds = sizeof(uint32_t) * (2 * (size_t)g.NW + multi_scratch_words(g));
   const unsigned blocks = (unsigned)(g.S * g.NT);
   const void* k = g.d == 3 ? (const void*)k_houdayer_multi<3> : (const void*)k_houdayer_multi<2>;
   if (lds > 65536) {

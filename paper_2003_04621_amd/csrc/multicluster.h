@@ -6,28 +6,34 @@
 // the Philox output for counter (m / 128, v, k, 6 << 28 | sample) is set (bit
 // j = bit j mod 32 of word j / 32).
 //
-// Connected components by union-find over the runs of q = -1 sites along x0,
-// by a team of threads (one wavefront in the fused step, one workgroup in the
-// per-pair kernel), with a 32-bit parent label per run in LDS, kept at the
-// run's lowest site (natural site order):
+// Connected components over the runs of q = -1 sites along x0, by a team of
+// threads (one wavefront in the fused step, one workgroup in the per-pair
+// kernel), with a 16-bit label per run in LDS:
 //   1. each row's q = -1 sites form runs along x0 (periodically), found with
-//      bit operations on the row's 64-bit mask; a run is named by its lowest
-//      site (its start, or x0 = 0 for the run that wraps through x0 = L - 1)
-//      and starts as its own root;
-//   2. every pair of runs overlapping along x1 (or x2) is united once, at the
-//      first site of each overlap segment: the two roots are found (following
-//      parents, each step also pointing the run passed at its grandparent)
-//      and the larger is hooked under the smaller with an LDS atomic minimum;
-//      if it had been hooked meanwhile, its new parent's root is united next;
-//   3. every run takes its root, which is then its component's lowest site
-//      (parents only ever point to lower runs of the same component, and
-//      nothing hooks a component's lowest run);
-//   4. the coins of all sites (one Philox call per 128 sites) and, for each
-//      run, the coin of its root give the exchanged runs, whose bit masks
-//      make the exchanged colour words.
-// Concurrent finds and hooks only ever replace a parent by a lower ancestor
-// in the same component, so every value read is valid and every find ends.
-// All work is per run, not per site: a row of L sites holds at most L/2 runs.
+//      bit operations on the row's 64-bit mask; a row's runs are numbered in
+//      the order of their lowest sites (the run that wraps through x0 = L - 1
+//      contains x0 = 0 and comes first).  The label of run r of row R lies at
+//      index R S + r, which is also the run's name, so names order runs by their
+//      lowest sites and a label is an address.  Every run starts as its own
+//      label;
+//   2. every overlap segment of two rows adjacent along x1 (or x2) joins two
+//      runs.  A run's first segment with the row before it along x1 sets its
+//      label to that run; the other segments are edges, listed in LDS;
+//   3. rounds until no edge joins two labels: every run takes its label's
+//      root; then every edge whose runs have labels lo < hi points hi at lo.
+//      Four runs or edges are in flight per thread.  A label only ever points
+//      to a lower name of the same component and every round that joins labels
+//      leaves fewer roots, whoever wins a concurrent store, so the rounds end,
+//      with each run labelled by its component's lowest run;
+//   4. the coins of all sites (one Philox call per 128 sites); each root run
+//      keeps the coin of its lowest site in its label's top bit, each run takes
+//      its root's, and the starts of the exchanged runs added to the row's mask
+//      carry through exactly those runs, which makes the exchanged colour words.
+// Bound by the instructions of the rounds (3) and their LDS latency at the
+// wavefronts per CU that the scratch areas allow (ten at 2D L = 64; six with a
+// 32-bit label per site): whole steps at 2D L = 64, 500 samples x 2 x 24, 206 ->
+// 127 us against uniting edge by edge with root searches, 3D L = 12, 100 x 2 x 20,
+// 96 -> 72 us.
 #pragma once
 #include "device.h"
 
@@ -38,11 +44,18 @@ constexpr uint32_t kTagHouMulti = 6u;
 // Sites a team's labels can name (the per-pair kernel's LDS holds them).
 constexpr int kMultiMaxSites = 32768;
 
+// A row of L <= 64 sites holds at most L/2 runs.  Places for a row's runs and,
+// per direction, its edges (multiples of four), and the labels' row stride S: an
+// odd number of words, so that the rows' labels start in different LDS banks.
+__host__ __device__ constexpr int multi_row_places(int L) { return (L / 2 + 3) & ~3; }
+__host__ __device__ constexpr int multi_row_stride(int L) { return (multi_row_places(L) & ~3) + 2; }
+
 // LDS words of one team's scratch for geometry g: overlap and cluster words
 // (2 NW each), row masks (64-bit per row), coins (one bit per site, 128-bit
-// blocks) and labels (32-bit per site).
-__host__ __device__ constexpr int multi_scratch_words(int N, int NR, int NW) {
-  return 4 * NW + 2 * NR + 4 * ((N + 127) / 128) + N;
+// blocks), labels, edges and edge counts (16-bit).
+__host__ __device__ constexpr int multi_scratch_words(const Geo& g) {
+  return 4 * g.NW + 2 * g.NR + 4 * ((g.N + 127) / 128) + g.NR * multi_row_stride(g.L) / 2 +
+         (g.NR * (g.d - 1) * (multi_row_places(g.L) + 1) + 1) / 2;
 }
 
 // Bit b of x moved to bit 2b (x < 2^32).
@@ -68,43 +81,29 @@ __device__ __forceinline__ uint32_t compress_even_bits(uint64_t x) {
 }
 
 // The runs of q = -1 sites of one row (L-bit mask m in x0 order, taken
-// periodically).  starts: bit x0 set iff x0 is q = -1 and x0 - 1 is not;
-// wrap: the start of the run through x0 = L - 1 when that run continues at
-// x0 = 0 (-1 if none).  A row that is q = -1 everywhere has no start and is
-// one run.
+// periodically).  starts: bit x0 set iff x0 is q = -1 and x0 - 1 is not; n: the
+// number of runs; wraps: the last start's run continues at x0 = 0.  A row that
+// is q = -1 everywhere has no start and is one run.
 struct RowRuns {
   uint64_t m, starts;
-  int wrap;
+  int n;
+  bool wraps;
 };
 
 __device__ __forceinline__ RowRuns row_runs(uint64_t m, int L, uint64_t full) {
   RowRuns r;
   r.m = m;
   r.starts = m & ~(((m << 1) | (m >> (L - 1))) & full);
-  r.wrap = (m != full && (m & 1ull) && ((m >> (L - 1)) & 1ull)) ? 63 - __clzll((long long)r.starts)
-                                                                 : -1;
+  r.n = r.starts ? __popcll(r.starts) : (m ? 1 : 0);
+  r.wraps = r.starts && (m & 1ull) && ((m >> (L - 1)) & 1ull);
   return r;
 }
 
-// Name (lowest x0) of the run holding q = -1 site x0.
-__device__ __forceinline__ int run_name(const RowRuns& r, int x0) {
-  const uint64_t le = r.starts & ((2ull << x0) - 1ull);  // x0 = 63: every bit
-  if (!le) return 0;  // no start at or below x0: the wrapping (or whole-row) run
-  const int st = 63 - __clzll((long long)le);
-  return st == r.wrap ? 0 : st;
-}
-
-// Sites of the run starting at `st` (st = r.wrap: the wrapping run).
-__device__ __forceinline__ uint64_t run_mask(const RowRuns& r, int st, int L, uint64_t full) {
-  const uint64_t above = full & ~((1ull << st) - 1ull);  // x0 >= st
-  const uint64_t zeros = ~r.m & above;
-  if (zeros) return above & ((1ull << (__ffsll((long long)zeros) - 1)) - 1ull);
-  uint64_t mask = above;  // runs to x0 = L - 1
-  if (st == r.wrap) {
-    const uint64_t z = ~r.m & full;  // not empty: the row is not all q = -1
-    mask |= (1ull << (__ffsll((long long)z) - 1)) - 1ull;
-  }
-  return mask;
+// Number (in the order of lowest sites) of the run holding q = -1 site x0.
+__device__ __forceinline__ int run_rank(const RowRuns& r, int x0) {
+  const int c = __popcll(r.starts & ((2ull << x0) - 1ull));  // x0 = 63: every bit
+  if (r.wraps) return c == r.n ? 0 : c;
+  return c > 0 ? c - 1 : 0;
 }
 
 // The q = -1 sites of row R as an L-bit mask in x0 order.
@@ -128,67 +127,46 @@ __device__ __forceinline__ void rows_up(const Geo& g, int R, int* up) {
   }
 }
 
-// Root of site x: follows parents (each lower than its child; a root is its
-// own parent), pointing every site passed at its grandparent.
-__device__ __forceinline__ uint32_t uf_root(uint32_t* lab, uint32_t x) {
-  uint32_t cur = lab[x];
-  if (cur != x) {
-    uint32_t prev = x, next;
-    while (cur > (next = lab[cur])) {
-      lab[prev] = next;
-      prev = cur;
-      cur = next;
-    }
-  }
-  return cur;
-}
-
-// Unites the components of sites i and j.
-__device__ __forceinline__ void uf_unite(uint32_t* lab, uint32_t i, uint32_t j) {
-  uint32_t a = uf_root(lab, i), b = uf_root(lab, j);
-  while (a != b) {
-    if (a > b) {
-      const uint32_t t = a;
-      a = b;
-      b = t;
-    }
-    const uint32_t old = atomicMin(&lab[b], a);  // hooks b under a if b is still a root
-    if (old == b) break;
-    b = uf_root(lab, old);
-    a = uf_root(lab, a);
-  }
-}
-
 // The exchanged sites of one multi-cluster move of the pair whose overlap
 // words are Q (bit set: q = -1) as colour words C (2 NW), by the team's
-// threads t < T.  scr: the team's scratch after Q and C (row masks, coins,
-// labels; 8-byte aligned).  `sync` orders the team's LDS accesses.
-template <int D, typename Sync>
+// threads t < T.  scr: the team's scratch after Q and C (8-byte aligned).
+// `sync` orders the team's LDS accesses, `any` does so and tells whether its
+// argument is true for some thread of the team.
+template <int D, typename Sync, typename Any>
 __device__ __forceinline__ void multi_cluster_words(const Geo& g, const uint32_t* Q, uint32_t* C,
                                                     uint32_t* scr, int s, int k, uint32_t v,
-                                                    int t, int T, Sync sync) {
+                                                    int t, int T, Sync sync, Any any) {
   const int L = g.L, NR = g.NR, N = g.N, NW = g.NW;
-  const int nblk = (N + 127) / 128;
+  const int nblk = (N + 127) / 128, ME = multi_row_places(L), S = multi_row_stride(L);
   uint64_t* qr = reinterpret_cast<uint64_t*>(scr);
   uint32_t* coin = scr + 2 * NR;
-  uint32_t* lab = coin + 4 * nblk;
+  uint16_t* lab = reinterpret_cast<uint16_t*>(coin + 4 * nblk);
+  uint16_t* edge = lab + NR * S;                // edge e of row R, direction j at (j ME + e) NR + R
+  uint16_t* edges = edge + (D - 1) * ME * NR;   // number of them at j NR + R
   const uint64_t full = L == 64 ? ~0ull : ((1ull << L) - 1ull);
+  // four consecutive labels of a row (two words)
+  typedef uint32_t __attribute__((may_alias)) Word;
+  auto load4 = [&](int i, uint32_t (&l)[4]) {
+    const Word* w = reinterpret_cast<const Word*>(lab + i);
+    const uint32_t x = w[0], y = w[1];
+    l[0] = x & 0xFFFFu;
+    l[1] = x >> 16;
+    l[2] = y & 0xFFFFu;
+    l[3] = y >> 16;
+  };
+  auto store4 = [&](int i, const uint32_t (&l)[4]) {
+    Word* w = reinterpret_cast<Word*>(lab + i);
+    w[0] = l[0] | (l[1] << 16);
+    w[1] = l[2] | (l[3] << 16);
+  };
 
-  // 1. row masks; every run its own root, kept at its lowest site; coins
+  // 1. row masks; every run its own label; coins
   for (int R = t; R < NR; R += T) {
     const uint64_t m = row_q_mask(g, Q, R);
     qr[R] = m;
-    if (!m) continue;
-    const RowRuns rr = row_runs(m, L, full);
-    const uint32_t base = (uint32_t)(R * L);
-    if (!rr.starts) {
-      lab[base] = base;  // the whole row is one run
-      continue;
-    }
-    for (uint64_t rest = rr.starts; rest; rest &= rest - 1ull) {
-      const int st = __ffsll((long long)rest) - 1;
-      const uint32_t name = base + (uint32_t)(st == rr.wrap ? 0 : st);
-      lab[name] = name;
+    for (int r = 0; r < ME; r += 4) {  // unused places too
+      const uint32_t i = (uint32_t)(R * S + r);
+      store4((int)i, {i, i + 1u, i + 2u, i + 3u});
     }
   }
   for (int blk = t; blk < nblk; blk += T) {
@@ -201,68 +179,140 @@ __device__ __forceinline__ void multi_cluster_words(const Geo& g, const uint32_t
   }
   sync();
 
-  // 2. unite the runs that overlap along x1 (and x2), once per overlap segment
+  // 2. one edge per segment of overlap along x1 (and x2), except those that set
+  // the upper run's label (only row R's thread writes those of the row above);
+  // edge = the runs' numbers, the lower row's in the low byte
   for (int R = t; R < NR; R += T) {
     const uint64_t m = qr[R];
-    if (!m) continue;
     const RowRuns rr = row_runs(m, L, full);
     int up[D - 1];
     rows_up(g, R, up);
 #pragma unroll
     for (int j = 0; j < D - 1; ++j) {
+      uint16_t* er = edge + j * ME * NR + R;
       const uint64_t mu = qr[up[j]];
       const uint64_t e = m & mu;
-      if (!e) continue;
       const RowRuns ru = row_runs(mu, L, full);
       // first site of each segment (cyclically); a full overlap is one segment
       uint64_t first = e & ~(((e << 1) | (e >> (L - 1))) & full);
       if (e == full) first = 1ull;
+      uint32_t set = j == 0 && up[j] > R ? 0u : ~0u;  // runs above that have their label
+      int n = 0;
+      uint32_t ed = 0;
       for (; first; first &= first - 1ull) {
         const int x0 = (int)__ffsll((long long)first) - 1;
-        uf_unite(lab, (uint32_t)(R * L + run_name(rr, x0)), (uint32_t)(up[j] * L + run_name(ru, x0)));
+        const uint32_t ra = (uint32_t)run_rank(rr, x0), rb = (uint32_t)run_rank(ru, x0);
+        if (!((set >> rb) & 1u)) {
+          set |= 1u << rb;
+          lab[up[j] * S + rb] = (uint16_t)(R * S + ra);
+          continue;
+        }
+        ed = ra | (rb << 8);
+        er[n * NR] = (uint16_t)ed;
+        ++n;
+      }
+      edges[j * NR + R] = (uint16_t)n;
+      // the last one again up to a multiple of four: no checks when they are read
+      for (; n & 3; ++n) er[n * NR] = (uint16_t)ed;
+    }
+  }
+  sync();
+
+  // 3. take roots and join the labels of every edge, until nothing joins
+  for (;;) {
+    for (int R = t; R < NR; R += T) {
+      const int n = row_runs(qr[R], L, full).n;
+      for (int r0 = 0; r0 < n; r0 += 4) {
+        uint32_t l[4], p[4];
+        load4(R * S + r0, l);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) p[i] = lab[l[i]];
+        // every thread stores what it has reached, so the distances double
+        while (p[0] != l[0] || p[1] != l[1] || p[2] != l[2] || p[3] != l[3]) {
+          store4(R * S + r0, p);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) l[i] = p[i];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) p[i] = lab[l[i]];
+        }
+      }
+    }
+    sync();
+    bool joined = false;
+    for (int R = t; R < NR; R += T) {
+      int up[D - 1];
+      rows_up(g, R, up);
+#pragma unroll
+      for (int j = 0; j < D - 1; ++j) {
+        const uint16_t* er = edge + j * ME * NR + R;
+        const int n = edges[j * NR + R];
+        const uint16_t *low = lab + R * S, *high = lab + up[j] * S;
+        for (int e0 = 0; e0 < n; e0 += 4) {
+          uint32_t ed[4], la[4], lb[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) ed[i] = er[(e0 + i) * NR];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            la[i] = low[ed[i] & 0xFFu];
+            lb[i] = high[ed[i] >> 8];
+          }
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (la[i] != lb[i]) {
+              lab[max(la[i], lb[i])] = (uint16_t)min(la[i], lb[i]);
+              joined = true;
+            }
+        }
+      }
+    }
+    if (!any(joined)) break;
+  }
+
+  // 4. the roots' coins, then the exchanged sites as colour words
+  for (int R = t; R < NR; R += T) {
+    const RowRuns rr = row_runs(qr[R], L, full);
+    uint64_t rest = rr.starts;
+    for (int r = 0; r < rr.n; ++r) {
+      const uint32_t name = (uint32_t)(R * S + r);
+      int x0 = 0;  // lowest site of run r
+      if (rr.starts && !(rr.wraps && r == 0)) {
+        x0 = (int)__ffsll((long long)rest) - 1;
+        rest &= rest - 1ull;
+      }
+      if (lab[name] == name) {
+        const uint32_t i = (uint32_t)(R * L + x0);
+        lab[name] = (uint16_t)(name | (((coin[i >> 5] >> (i & 31)) & 1u) << 15));
       }
     }
   }
   sync();
-
-  // 3. every run takes its root
-  for (int R = t; R < NR; R += T) {
-    const uint64_t m = qr[R];
-    if (!m) continue;
-    const RowRuns rr = row_runs(m, L, full);
-    const uint32_t base = (uint32_t)(R * L);
-    if (!rr.starts) {
-      lab[base] = uf_root(lab, base);
-      continue;
-    }
-    for (uint64_t rest = rr.starts; rest; rest &= rest - 1ull) {
-      const int st = __ffsll((long long)rest) - 1;
-      const uint32_t name = base + (uint32_t)(st == rr.wrap ? 0 : st);
-      lab[name] = uf_root(lab, name);
-    }
-  }
-  sync();
-
-  // 4. exchanged sites: the runs whose root's coin is set, as colour words
   for (int w = t; w < NW; w += T) {
     const WordNb q = word_nb(g, w);
     uint32_t out[2] = {0u, 0u};
     for (int f = 0; f < g.P; ++f) {
       const int R = word_row(g, q, f);
       const uint64_t m = qr[R];
-      if (!m) continue;
       const RowRuns rr = row_runs(m, L, full);
-      const uint32_t base = (uint32_t)(R * L);
+      uint32_t take = 0;  // bit r: run r is exchanged
+      for (int r0 = 0; r0 < rr.n; r0 += 4) {
+        uint32_t l[4];
+        load4(R * S + r0, l);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) take |= (uint32_t)(lab[l[i] & 0x7FFFu] >> 15) << (r0 + i);
+      }
       uint64_t X = 0;
       if (!rr.starts) {
-        const uint32_t root = lab[base];
-        if ((coin[root >> 5] >> (root & 31)) & 1u) X = full;
+        X = take ? full : 0ull;
       } else {
-        for (uint64_t rest = rr.starts; rest; rest &= rest - 1ull) {
-          const int st = __ffsll((long long)rest) - 1;
-          const uint32_t root = lab[base + (uint32_t)(st == rr.wrap ? 0 : st)];
-          if ((coin[root >> 5] >> (root & 31)) & 1u) X |= run_mask(rr, st, L, full);
+        uint64_t St = 0;  // starts of the exchanged runs
+        uint32_t bits = take;
+        if (rr.wraps) {
+          if (take & 1u) St = 1ull | (1ull << (63 - __clzll((long long)rr.starts)));
+          bits >>= 1;
         }
+        for (uint64_t rest = rr.starts; bits; bits >>= 1, rest &= rest - 1ull)
+          if (bits & 1u) St |= rest & (0ull - rest);
+        X = m & ~(m + St);
       }
       if (!X) continue;
       const int p0 = row_parity(g, R);  // colour of the even-x0 sites

@@ -83,3 +83,37 @@ def test_step_clusters_match_oracle(pt, d, L, S, NT, layout, steps):
     assert (pt.pt_get_energies(job) == ref.energies()).all()
     same(pt, job, ref)
     pt.pt_destroy(job)
+
+
+# rows with the most runs a row can hold (alternating sites), whole-row and
+# wrapping runs, row counts that are no multiple of the wavefront, and
+# workgroups with fewer wavefronts than scratch areas
+@pytest.mark.parametrize("threads", [0, 256])
+@pytest.mark.parametrize("d,L,S,NT", [(2, 4, 2, 3), (2, 10, 2, 2), (2, 26, 2, 3), (2, 50, 1, 12), (2, 64, 1, 9),
+                                      (3, 4, 2, 2), (3, 10, 1, 3), (3, 12, 1, 6), (3, 14, 1, 2), (3, 20, 1, 2)])
+def test_multi_clusters_match_oracle(pt, d, L, S, NT, threads):
+    J = W.couplings_pm_j(S, L, d, 30 + L)
+    betas = W.geometric_betas(0.3 if d == 2 else 0.7, 2.5, NT)
+    job = pt.pt_init(S, NT, L, d, J, betas, 45 + L)
+    ref = oracle.OracleJob(S, NT, L, d, J, betas, 45 + L)
+    x = np.indices((L,) * d).sum(axis=0).reshape(-1)
+    spins = pt.pt_get_spins(job)
+    spins[:, 0] = spins[:, NT] * np.where(x % 2 == 0, -1, 1)  # checkerboard overlap
+    if NT > 2:
+        spins[:, 1] = -spins[:, NT + 1]                       # q = -1 everywhere
+        cols = (np.arange(L ** d) % L)                        # whole columns, one wrapping
+        spins[:, 2] = spins[:, NT + 2] * np.where((cols % 4 == 0) | (cols == L - 1), -1, 1)
+    pt.pt_set_spins(job, spins)
+    ref.set_spins(spins)
+    pt.pt_houdayer_multi(job)  # on those overlaps
+    ref.houdayer(multi=True)
+    assert (pt.pt_get_energies(job) == ref.energies()).all()
+    same(pt, job, ref)
+    batch = pt.pt_batch_create([job])
+    pt.pt_batch_set_config(batch, threads, 2, 0)
+    pt.pt_batch_run(batch, 6, houdayer=True, multi=True, measure=True)
+    ref.mcs(6, houdayer=True, multi=True, measure=True)
+    assert (pt.pt_get_energies(job) == ref.energies()).all()
+    same(pt, job, ref)
+    pt.pt_batch_destroy(batch)
+    pt.pt_destroy(job)
