@@ -282,7 +282,9 @@ int pt_set_measure_interval(pt_job *job, int32_t every);
 /* The plan pt_mcs takes for these flags, int32 [4]: mode (0 both sets per
  * workgroup, 1 the same with Houdayer, 2 one set per workgroup, 3 split
  * sample, -1 per-step kernels), workgroups per sample, configurations per
- * workgroup, and LDS bytes per workgroup (0 for mode -1).  A Gaussian job
+ * workgroup, and LDS bytes per workgroup (0 for mode -1).  Where a job's
+ * samples need fewer workgroups than the GPU has CUs, pt_mcs may spread each
+ * over more workgroups than the plan says, with the same results.  A Gaussian job
  * reports mode 0 for its fused steps (with or without Houdayer moves) and -1
  * for the per-step kernels.  Host only. */
 int pt_get_plan(pt_job *job, uint32_t flags, int32_t *out4);

@@ -62,6 +62,8 @@ struct pt_batch {
   size_t stage_cap = 0;
   hipEvent_t stage_ev = nullptr, last_ev = nullptr;
   std::vector<FusedArgs> args;  // host copy of the uploaded launch arguments
+  bool may_spread = false;  // the one-job batch behind pt_mcs (spread_job)
+  SplitPlan spread;         // the built work list's spread plan (parts 0: none)
 };
 
 namespace {
@@ -72,6 +74,19 @@ namespace {
 // the other one's exit would make room for.
 std::mutex g_split_mu;
 hipEvent_t g_split_ev[64] = {};
+hipStream_t g_split_stream[64] = {};  // of the last such launch
+
+// Whether a launch holding split samples is in flight on another stream of
+// the current device.
+bool split_busy_elsewhere(hipStream_t st) {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return false;
+  std::lock_guard<std::mutex> lk(g_split_mu);
+  if (!g_split_ev[dev] || g_split_stream[dev] == st) return false;
+  const hipError_t e = hipEventQuery(g_split_ev[dev]);
+  (void)hipGetLastError();
+  return e == hipErrorNotReady;
+}
 
 template <typename F>
 hipError_t ordered_split_launch(hipStream_t st, F&& launch) {
@@ -84,6 +99,7 @@ hipError_t ordered_split_launch(hipStream_t st, F&& launch) {
   if (e == hipSuccess) e = hipStreamWaitEvent(st, g_split_ev[dev], 0);
   if (e == hipSuccess) e = launch();
   if (e == hipSuccess) e = hipEventRecord(g_split_ev[dev], st);
+  g_split_stream[dev] = st;
   return e;
 }
 
@@ -115,19 +131,20 @@ int job_mode(const pt_job* j, uint32_t flags, const BatchConfig& cfg) {
 
 }  // namespace
 
-// The launch arguments of job j for `mcs` fused steps in plan `mode`.
-FusedArgs job_fused_args(const pt_job* j, int mode, int mcs, uint32_t flags) {
+// The launch arguments of job j for `mcs` fused steps in plan `mode` (3: the
+// split plan `split`).
+FusedArgs job_fused_args(const pt_job* j, int mode, int mcs, uint32_t flags, const SplitPlan* split) {
   const bool hou = flags & PT_MCS_HOUDAYER, meas = flags & PT_MCS_MEASURE;
-  const FusedLayout& lay = mode == 3 ? j->split_lay : j->plan[mode];
+  const FusedLayout& lay = mode == 3 ? split->lay : j->plan[mode];
   FusedArgs A = make_fused_args(j->g, lay, j->spins, j->jw, j->E, j->sot, j->tos, j->thr, j->thrpt,
                                 j->M, j->mom, j->walk, j->trips, j->modes, j->ctr, mcs,
                                 mode == 3 ? false : hou, meas);
   A.every = j->meas_every;
   if (A.hou && (flags & PT_MCS_MULTICLUSTER)) A.hou = 2;
   if (mode == 3) {
-    A.parts = j->split_parts;
-    A.R = j->split_R;
-    A.jlds = j->split_jlds;
+    A.parts = split->parts;
+    A.R = split->R;
+    A.jlds = split->jlds;
     A.Ex = j->Ex;
     A.snap = j->snap;
     A.bar = j->bar;
@@ -231,9 +248,11 @@ struct HostWorklist {
   bool has_split = false;
 };
 
-// Work list for per-job step counts and flags (jobs with 0 steps get no item).
+// Work list for per-job step counts and flags (jobs with 0 steps get no item);
+// with `spread`, every job runs that split plan instead of its own (one job).
 int plan_worklist(const std::vector<pt_job*>& jobs, const BatchConfig& cfg, const std::vector<int>& steps,
-                  const std::vector<uint32_t>& jflags, HostWorklist& out) {
+                  const std::vector<uint32_t>& jflags, HostWorklist& out,
+                  const SplitPlan* spread = nullptr) {
   std::vector<FusedArgs>& hj = out.jobs;
   std::vector<BatchItem>& hi = out.items;
   std::vector<BatchItem> split;
@@ -248,12 +267,13 @@ int plan_worklist(const std::vector<pt_job*>& jobs, const BatchConfig& cfg, cons
     const uint32_t flags = jflags[jx];
     const bool hou = flags & PT_MCS_HOUDAYER, meas = flags & PT_MCS_MEASURE;
     const int mcs = steps[jx];
-    const int mode = job_mode(j, flags, cfg);
+    const int mode = spread ? 3 : job_mode(j, flags, cfg);
+    const SplitPlan& split_as = spread ? *spread : j->split;
     if (mode < 0) {
       // no fused plan for these flags: the job's steps run through the
       // per-step kernels beside the launch (pt_batch_run); here it only keeps
       // its index, with no steps and no items
-      hj.push_back(job_fused_args(j, 0, 0, 0u));
+      hj.push_back(job_fused_args(j, 0, 0, 0u, nullptr));
       continue;
     }
     if (mcs > 0 && meas) feat |= kFeatMeas;
@@ -262,19 +282,19 @@ int plan_worklist(const std::vector<pt_job*>& jobs, const BatchConfig& cfg, cons
     if (mcs > 0 && j->track_walk) feat |= kFeatWalk;
     if (mcs > 0 && meas && j->track_modes) feat |= kFeatModes;
     if (mode == 3) {
-      hj.push_back(job_fused_args(j, mode, mcs, flags));
-      lds_words = std::max(lds_words, (size_t)j->split_lay.words);
+      hj.push_back(job_fused_args(j, mode, mcs, flags, &split_as));
+      lds_words = std::max(lds_words, (size_t)split_as.lay.words);
       if (mcs <= 0) continue;
       // the parts of a sample are consecutive, and split samples go first so
       // that all parts are taken while every workgroup is still free
       for (int s = 0; s < j->g.S; ++s) {
-        split_groups.push_back({(double)j->split_R * j->g.N * mcs, split.size()});
-        for (int p = 0; p < j->split_parts; ++p) split.push_back(BatchItem{(int)jx, s, p, 0});
+        split_groups.push_back({(double)split_as.R * j->g.N * mcs, split.size()});
+        for (int p = 0; p < split_as.parts; ++p) split.push_back(BatchItem{(int)jx, s, p, 0});
       }
       continue;
     }
     const int nsets = mode == 2 ? 1 : 2;
-    hj.push_back(job_fused_args(j, mode, mcs, flags));
+    hj.push_back(job_fused_args(j, mode, mcs, flags, nullptr));
     lds_words = std::max(lds_words, (size_t)j->plan[mode].words);
     if (mcs <= 0) continue;
     const double c = (double)nsets * j->g.NT * j->g.N * mcs;
@@ -301,7 +321,7 @@ int plan_worklist(const std::vector<pt_job*>& jobs, const BatchConfig& cfg, cons
     std::vector<BatchItem> sorted;
     sorted.reserve(split.size());
     for (const auto& gr : split_groups) {
-      const size_t end = gr.second + (size_t)jobs[split[gr.second].job]->split_parts;
+      const size_t end = gr.second + (size_t)hj[(size_t)split[gr.second].job].parts;
       for (size_t i = gr.second; i < end; ++i) sorted.push_back(split[i]);
     }
     split.swap(sorted);
@@ -351,7 +371,8 @@ int upload_worklist(pt_batch* b, const FusedArgs* args, size_t nj, const BatchIt
 // device buffers (grown as needed).
 int build_worklist_ex(pt_batch* b, const std::vector<int>& steps, const std::vector<uint32_t>& jflags) {
   HostWorklist wl;
-  if (int rc = plan_worklist(b->jobs, b->cfg, steps, jflags, wl)) return rc;
+  if (int rc = plan_worklist(b->jobs, b->cfg, steps, jflags, wl, b->spread.parts ? &b->spread : nullptr))
+    return rc;
   const std::vector<FusedArgs>& hj = wl.jobs;
   const std::vector<BatchItem>& hi = wl.items;
   const size_t lds_words = wl.lds_words;
@@ -395,6 +416,34 @@ int build_worklist_ex(pt_batch* b, const std::vector<int>& steps, const std::vec
   return PT_OK;
 }
 
+// The finer split of a job that pt_mcs runs when its own plan leaves CUs idle
+// (parts 0: none): with S samples on fewer workgroups than CUs, the 2 N_T
+// configurations of each are spread over up to ncu / S parts that meet once
+// per step, as samples too large for one workgroup do.  A part keeps at least
+// kSpreadFlips attempted flips per step and a sample four times that, so that
+// the sweep saved outweighs the meeting (about 3 us) and the scratch; at least
+// twice the parts the plan has, or with a plan that is split already (and
+// meets anyway) more of them; not where another stream's split launch is in
+// flight.  Measured steps, the plan's workgroups against the spread (us): 3D
+// L = 16, 16 x 2 x 32: 36.0 / 10.3; 100 x 2 x 32: 36.2 / 23.8; L = 20, 17 x 2 x
+// 25: 76 / 14.7; L = 48, 5 x 2 x 20: 135 / 22.9; 2D L = 64, 8 x 2 x 24: 24.7 /
+// 9.6; at the line, 3D L = 8, 8 x 2 x 32: 10.8 / 9.3.
+constexpr double kSpreadFlips = 8192;
+SplitPlan spread_job(pt_job* j, uint32_t flags, int ncu) {
+  SplitPlan none, plan;
+  if (flags & PT_MCS_HOUDAYER) return none;
+  const Geo& g = j->g;
+  const int mode = job_mode(j, flags, BatchConfig{});
+  const double flips = (double)g.nslot * g.N;
+  if (mode < 0 || flips < 4 * kSpreadFlips) return none;
+  const int has = mode == 3 ? j->split.parts : mode == 2 ? 2 : 1;
+  const int p = std::min({ncu / g.S, kMaxParts, g.nslot, g.NW / 4, (int)std::min(flips / kSpreadFlips, 1e6)});
+  if (p < (mode == 3 ? has + 1 : 2 * has)) return none;
+  if (!split_plan(g, plan, j->track_walk, j->track_modes, p) || plan.parts <= has || !j->split_scratch())
+    return none;
+  return plan;
+}
+
 int build_worklist(pt_batch* b, int mcs, uint32_t flags) {
   std::vector<int> every(b->jobs.size());  // the work list carries each job's interval
   std::vector<uint32_t> epoch(b->jobs.size());  // and its buffers and layout
@@ -418,6 +467,7 @@ int build_worklist(pt_batch* b, int mcs, uint32_t flags) {
   b->built_epoch = epoch;
   const std::vector<int> steps(b->jobs.size(), mcs);
   const std::vector<uint32_t> fl(b->jobs.size(), flags);
+  b->spread = b->may_spread ? spread_job(b->jobs[0], flags, b->ncu) : SplitPlan{};
   if (int rc = build_worklist_ex(b, steps, fl)) return rc;
   b->built = true;
   b->built_mcs = mcs;
@@ -586,9 +636,10 @@ int set_layout_all(pt_batch* b, int layout) {
 // ---------------------------------------------------------------------------
 // Internal entry points for the request server: one launch over a changing
 // set of resident jobs with per-job step counts and flags.
-pt_batch* batch_new(hipStream_t st) {
+pt_batch* batch_new(hipStream_t st, bool may_spread) {
   pt_batch* b = new (std::nothrow) pt_batch();
   if (!b) return nullptr;
+  b->may_spread = may_spread;
   b->stream = st;
   int dev = 0, ncu = 0;
   if (hipGetDevice(&dev) == hipSuccess &&
@@ -615,6 +666,13 @@ int batch_run_job(pt_batch* b, pt_job* job, int mcs, uint32_t flags) {
   }
   b->stream = job->stream;
   if (int rc = build_worklist(b, mcs, flags)) return rc;
+  if (b->spread.parts && split_busy_elsewhere(b->stream)) {
+    // split launches run one after another: a program that keeps several
+    // streams busy runs its jobs side by side, one workgroup per sample
+    b->may_spread = false;
+    b->built = false;
+    if (int rc = build_worklist(b, mcs, flags)) return rc;
+  }
   return run_once(b, false);
 }
 
@@ -706,8 +764,8 @@ void job_items(const pt_job* j, uint32_t flags, int& items, double& item_flips) 
   const int mode = job_mode(j, flags, BatchConfig{});
   const double lat = (double)j->g.N;
   if (mode == 3) {
-    items = j->g.S * j->split_parts;
-    item_flips = lat * j->split_R;
+    items = j->g.S * j->split.parts;
+    item_flips = lat * j->split.R;
   } else if (mode == 2) {
     items = j->g.S * 2;
     item_flips = lat * j->g.NT;

@@ -2,6 +2,7 @@
 // reset and counter advance kernels, LDS plans of resident and split samples,
 // launch arguments, and the launch of the persistent batch kernel whose
 // device code is in fused_device.h.
+#include <algorithm>
 #include <map>
 #include <mutex>
 #include <utility>
@@ -19,7 +20,18 @@ __global__ void k_batch_reset(const FusedArgs* __restrict__ jobs, uint32_t* queu
   }
   const FusedArgs& A = jobs[blockIdx.x - 1];
   if (A.parts == 0) return;
-  for (int i = threadIdx.x; i < A.g.S; i += blockDim.x) A.bar[i] = 0u;
+  for (int i = threadIdx.x; i < A.g.S; i += blockDim.x) A.bar[(size_t)i * kBarStride] = 0u;
+}
+
+__global__ void k_clear_bar(uint32_t* bar, int words, int at, uint64_t host_fault) {
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < words; i += gridDim.x * blockDim.x)
+    bar[i] = i == at + 1 ? (uint32_t)host_fault : i == at + 2 ? (uint32_t)(host_fault >> 32) : 0u;
+}
+hipError_t launch_clear_bar(uint32_t* bar, int S, uint32_t* host_fault, hipStream_t st) {
+  const int words = (int)bar_words(S);
+  hipLaunchKernelGGL(k_clear_bar, dim3((unsigned)std::min(64, (words + 255) / 256)), dim3(256), 0, st, bar,
+                     words, S * kBarStride, (uint64_t)reinterpret_cast<uintptr_t>(host_fault));
+  return hipGetLastError();
 }
 
 // Advances every job's counters by its own number of steps in this launch.
@@ -90,8 +102,8 @@ bool fused_plan(const Geo& g, bool hou, int nsets, int waves, FusedLayout& lay, 
   return off <= budget;
 }
 
-bool split_plan(const Geo& g, FusedLayout& lay, int& parts, int& R, int& jlds, bool walk,
-                bool modes) {
+bool split_plan(const Geo& g, SplitPlan& plan, bool walk, bool modes, int least) {
+  FusedLayout& lay = plan.lay;
   const int waves = 16;  // plane counters for up to 16 wavefronts
   const size_t mcnt = modes ? (size_t)waves * 3 * g.L : 0;
   const size_t mwords = modes ? 2 * (size_t)g.NT * (g.L / 2 + 1) : 0;
@@ -108,13 +120,14 @@ bool split_plan(const Geo& g, FusedLayout& lay, int& parts, int& R, int& jlds, b
     if (fixed >= budget) continue;
     const size_t rmax = std::min<size_t>((budget - fixed) / W2, (size_t)g.nslot);
     if (rmax < 1 || (jl && rmax < std::min(g.nslot, 8))) continue;
-    const int p = (int)((g.nslot + rmax - 1) / rmax);
+    const int p = std::max((int)((g.nslot + rmax - 1) / rmax), std::min(least, g.nslot));
     // the parts' moment increments ([p][N_T][8] 64-bit words) are combined
     // through one parity half of the published-configuration scratch
     if (p > kMaxParts || (size_t)p * 8 > W2) continue;
-    R = (g.nslot + p - 1) / p;
-    parts = (g.nslot + R - 1) / R;
-    jlds = jl;
+    const int R = (g.nslot + p - 1) / p;
+    plan.R = R;
+    plan.parts = (g.nslot + R - 1) / R;
+    plan.jlds = jl;
     size_t off = 0;
     auto take = [&](size_t words, size_t align) {
       off = (off + align - 1) / align * align;

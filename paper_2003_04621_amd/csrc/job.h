@@ -13,6 +13,11 @@
 int pt_fail(int code, const std::string& msg);
 const char* pt_error_text();
 
+// A zeroed word of pinned host memory for a job's split launches to report a lost
+// barrier in (null if there is none to be had), and its return.
+uint32_t* fault_word_take();
+void fault_word_give(uint32_t* w);
+
 // One job: S samples x 2 replica sets x N_T temperatures.  Pointers are device
 // memory allocated through the hooks captured at creation.
 struct pt_job {
@@ -42,18 +47,20 @@ struct pt_job {
   bool track_stats = false;
   int64_t* stats = nullptr;  // [S][NT][kNStat]
   // fused-step LDS plans: both sets without / with Houdayer, one set, (3
-  // unused: split samples have split_lay), both sets with multi-cluster
+  // unused: split samples have `split`), both sets with multi-cluster
   // Houdayer moves
   ptsg::FusedLayout plan[5];
   bool fused_ok[5] = {false, false, false, false, false};
-  // split-sample plan (samples whose sets do not fit one workgroup) and its
-  // scratch: published energies / configurations and barrier counters
-  ptsg::FusedLayout split_lay{};
+  // split-sample plan (samples whose sets do not fit one workgroup; split_ok)
+  // and the scratch of split launches: published energies / configurations and
+  // barrier counters (allocated at creation for such samples, for others by
+  // the first pt_mcs that spreads them, split_scratch)
+  ptsg::SplitPlan split{};
   bool split_ok = false;
-  int split_parts = 0, split_R = 0, split_jlds = 0;
   int32_t* Ex = nullptr;     // [S][2][2NT]
   uint32_t* snap = nullptr;  // [S][2][2NT][2NW]
-  uint32_t* bar = nullptr;   // [S] barrier counters + fault word
+  uint32_t* bar = nullptr;   // [bar_words(S)] barrier counters and fault word
+  uint32_t* hfault = nullptr;  // the fault word's copy in pinned host memory
   // Gaussian couplings (pt_init_gauss): integer units, 64-bit energies, the
   // per-group coupling data of gauss.h and the inverse temperatures; thr,
   // thrpt, jw and E stay null for such a job
@@ -101,7 +108,34 @@ struct pt_job {
       return;
     }
   }
+  // Clears the barrier words, with the address of the host's fault word.
+  hipError_t clear_bar(uint32_t* words) {
+    if (!hfault) hfault = fault_word_take();
+    return ptsg::launch_clear_bar(words, g.S, hfault, stream);
+  }
+  // Allocates the scratch of split launches if the job has none; false (with
+  // none) if the device has no room.  Waits for the device once: the buffers
+  // may have been in use on another stream than the job's.
+  bool split_scratch() {
+    if (bar) return true;
+    const size_t per = (size_t)g.S * 2 * g.nslot;
+    void* p[3] = {dalloc(sizeof(int32_t) * per), dalloc(sizeof(uint32_t) * per * 2 * g.NW),
+                  dalloc(sizeof(uint32_t) * ptsg::bar_words(g.S))};
+    if (!p[0] || !p[1] || !p[2] || hipDeviceSynchronize() != hipSuccess ||
+        clear_bar((uint32_t*)p[2]) != hipSuccess || hipStreamSynchronize(stream) != hipSuccess) {
+      (void)hipGetLastError();
+      for (void* q : p)
+        if (q) dfree(q);
+      return false;
+    }
+    Ex = (int32_t*)p[0];
+    snap = (uint32_t*)p[1];
+    bar = (uint32_t*)p[2];
+    return true;
+  }
   void release() {
+    if (hfault) fault_word_give(hfault);
+    hfault = nullptr;
     for (void* p : allocs) {
       if (free_fn)
         free_fn(p, alloc_ctx);
@@ -114,7 +148,7 @@ struct pt_job {
 
 // Batch internals used by the request server (batch.hip).
 struct pt_batch;
-pt_batch* batch_new(hipStream_t st);
+pt_batch* batch_new(hipStream_t st, bool may_spread = false);
 int batch_round(pt_batch* b, const std::vector<pt_job*>& jobs, const std::vector<int>& steps,
                 const std::vector<uint32_t>& flags);
 void batch_free(pt_batch* b);
@@ -128,7 +162,8 @@ int batch_run_job(pt_batch* b, pt_job* job, int mcs, uint32_t flags);
 int batch_run_job_noalloc(pt_job* job, int mcs, uint32_t flags, int* nitems);
 // The launch arguments of job j for `mcs` fused steps in plan `mode` (as
 // job_plan_mode returns it) with pt_mcs flags `flags`.
-ptsg::FusedArgs job_fused_args(const pt_job* j, int mode, int mcs, uint32_t flags);
+ptsg::FusedArgs job_fused_args(const pt_job* j, int mode, int mcs, uint32_t flags,
+                               const ptsg::SplitPlan* split);
 // Threads per workgroup and workgroups per CU of a persistent launch of the
 // batch kernel (d, feat) with lds_bytes of LDS per workgroup over nitems items
 // on ncu CUs; cfg_threads > 0 fixes the workgroup size.  PT_EINVAL if no

@@ -100,8 +100,8 @@ struct FusedArgs {
   FusedLayout lay;
   // Split samples (parts > 0): part p of a sample holds slots [p R, p R + R),
   // couplings in LDS iff jlds.  Ex [S][2][nslot] and snap [S][2][nslot][2NW]
-  // are the parity-buffered published energies and configurations, bar [S+1]
-  // the per-sample barrier counters followed by the job's fault word.
+  // are the parity-buffered published energies and configurations, bar
+  // [bar_words(S)] the per-sample barrier counters and the job's fault word.
   int parts, R, jlds;
   int32_t* Ex;
   uint32_t* snap;
@@ -126,11 +126,23 @@ constexpr int kMaxParts = 64;
 bool fused_plan(const Geo& g, bool houdayer, int nsets, int waves, FusedLayout& lay,
                 bool walk = false, bool modes = false, bool multi = false);
 
-// Plans a split sample: the fewest parts (<= kMaxParts) whose R slots fit one
-// workgroup's LDS, with the couplings in LDS when that still leaves room for
-// min(2 N_T, 8) slots.  False if even one slot does not fit.
-bool split_plan(const Geo& g, FusedLayout& lay, int& parts, int& R, int& jlds, bool walk = false,
-                bool modes = false);
+// Barrier words of a job's split launches: sample s counts at s kBarStride (a
+// cache line each, so that the samples' waits do not meet at one memory
+// address), the job's fault word follows at S kBarStride, then two words with
+// the address of its copy in pinned host memory (0: none).
+constexpr int kBarStride = 32;
+constexpr size_t bar_words(int S) { return (size_t)(S + 1) * kBarStride; }
+// Clears them and writes the address of the fault word's host copy.
+hipError_t launch_clear_bar(uint32_t* bar, int S, uint32_t* host_fault, hipStream_t st);
+
+// Plans a split sample: the fewest parts (at least `least`, at most kMaxParts)
+// whose R slots fit one workgroup's LDS, with the couplings in LDS when that
+// still leaves room for min(2 N_T, 8) slots.  False if even one slot does not fit.
+struct SplitPlan {
+  FusedLayout lay{};
+  int parts = 0, R = 0, jlds = 0;
+};
+bool split_plan(const Geo& g, SplitPlan& plan, bool walk = false, bool modes = false, int least = 1);
 
 FusedArgs make_fused_args(const Geo& g, const FusedLayout& lay, void* spins, const uint32_t* jw,
                           int32_t* E, int32_t* sot, int32_t* tos, const uint32_t* thr,

@@ -5,6 +5,7 @@
 
 #include <cmath>
 #include <limits>
+#include <mutex>
 #include <cstdio>
 #include <cstring>
 #include <new>
@@ -29,6 +30,34 @@ int pt_fail(int code, const std::string& msg) {
   return code;
 }
 const char* pt_error_text() { return g_err.c_str(); }
+
+// Pages of pinned host words, 1024 jobs each, kept for the process (a job that
+// splits holds one word).
+namespace {
+std::mutex g_fault_mu;
+std::vector<uint32_t*> g_fault_free;
+}  // namespace
+
+uint32_t* fault_word_take() {
+  std::lock_guard<std::mutex> lk(g_fault_mu);
+  if (g_fault_free.empty()) {
+    void* page = nullptr;
+    if (hipHostMalloc(&page, 4096, hipHostMallocPortable) != hipSuccess) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+    for (int i = 1024; i-- > 0;) g_fault_free.push_back(static_cast<uint32_t*>(page) + i);
+  }
+  uint32_t* w = g_fault_free.back();
+  g_fault_free.pop_back();
+  *w = 0u;
+  return w;
+}
+
+void fault_word_give(uint32_t* w) {
+  std::lock_guard<std::mutex> lk(g_fault_mu);
+  g_fault_free.push_back(w);
+}
 
 namespace {
 
@@ -71,8 +100,7 @@ void plan_job(pt_job* job) {
   job->fused_ok[1] = fused_plan(g, true, 2, 16, job->plan[1], w, md);
   job->fused_ok[2] = fused_plan(g, false, 1, 16, job->plan[2], w, md);
   job->fused_ok[4] = fused_plan(g, true, 2, 16, job->plan[4], w, md, true);
-  job->split_ok = !job->fused_ok[0] && split_plan(g, job->split_lay, job->split_parts,
-                                                   job->split_R, job->split_jlds, w, md);
+  job->split_ok = !job->fused_ok[0] && split_plan(g, job->split, w, md);
 }
 
 // pt_get_plan's report for a planned job.
@@ -93,9 +121,9 @@ void plan_report(const pt_job* job, uint32_t flags, int32_t* out4) {
   if (mode < 0) {
     out4[1] = out4[2] = out4[3] = 0;
   } else if (mode == 3) {
-    out4[1] = job->split_parts;
-    out4[2] = job->split_R;
-    out4[3] = 4 * job->split_lay.words;
+    out4[1] = job->split.parts;
+    out4[2] = job->split.R;
+    out4[3] = 4 * job->split.lay.words;
   } else {
     out4[1] = mode == 2 ? 2 : 1;
     out4[2] = mode == 2 ? g.NT : g.nslot;
@@ -120,35 +148,54 @@ int check_job(pt_job* job) {
   return PT_OK;
 }
 
-// Copies device memory to the caller's host memory behind the job's queued
-// work and waits for it: one call where there was an asynchronous copy to
-// pageable memory, which waits for its staging, and a wait for the stream
-// (a small getter 22 -> 14 us, on a split job 42 -> 26).  A stream under capture
-// takes the two calls, which fail there.
-hipError_t read_back(const pt_job* job, void* dst, const void* src, size_t bytes) {
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (job->stream) {
-    const hipError_t e = hipStreamIsCapturing(job->stream, &cap);
-    if (e != hipSuccess) return e;
-  }
-  if (cap == hipStreamCaptureStatusNone)
-    return hipMemcpyWithStream(dst, src, bytes, hipMemcpyDeviceToHost, job->stream);
-  const hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, job->stream);
-  return e == hipSuccess ? hipStreamSynchronize(job->stream) : e;
+// Fails if a split sample's barrier gave up (the job's state is then
+// unusable), given the fault word.
+int fault_result(pt_job* job, uint32_t fault) {
+  if (!fault) return PT_OK;
+  job->poisoned = true;
+  return pt_fail(PT_EDEVICE, "a split sample's workgroups lost contact (barrier timed out)");
 }
 
-// Waits for the job's stream and fails if a split sample's barrier gave up
-// (the job's state is then unusable).
+// Copies device memory to the caller's host memory behind the job's queued
+// work, waits for it and checks the job's fault word.  One call where there was
+// an asynchronous copy to pageable memory, which waits for its staging, and a
+// wait for the stream, and the fault word from its copy in host memory where it
+// was copied in the same way first (a small getter 22 -> 14 us, on a split job 42
+// -> 14).  A stream under capture takes the two calls, which fail there.
+int read_back(pt_job* job, void* dst, const void* src, size_t bytes) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  hipError_t e = job->stream ? hipStreamIsCapturing(job->stream, &cap) : hipSuccess;
+  auto copy = [&](void* to, const void* from, size_t n) {
+    if (cap == hipStreamCaptureStatusNone)
+      return hipMemcpyWithStream(to, from, n, hipMemcpyDeviceToHost, job->stream);
+    const hipError_t ec = hipMemcpyAsync(to, from, n, hipMemcpyDeviceToHost, job->stream);
+    return ec == hipSuccess ? hipStreamSynchronize(job->stream) : ec;
+  };
+  uint32_t fault = 0;
+  if (e == hipSuccess) e = copy(dst, src, bytes);
+  if (e == hipSuccess && job->bar) {
+    if (job->hfault)
+      fault = __atomic_load_n(job->hfault, __ATOMIC_ACQUIRE);
+    else
+      e = copy(&fault, job->bar + (size_t)job->g.S * kBarStride, sizeof(fault));
+  }
+  if (e != hipSuccess) return device_error(job, e, "pt_get_*");
+  return fault_result(job, fault);
+}
+
+#define PT_READ(job, dst, src, bytes)                          \
+  do {                                                         \
+    if (int rc_ = read_back(job, dst, src, bytes)) return rc_; \
+  } while (0)
+
+// Waits for the job's stream and checks its fault word.
 int check_fault(pt_job* job) {
   if (!job->bar) return PT_OK;
   uint32_t fault = 0;
-  const hipError_t e = read_back(job, &fault, job->bar + job->g.S, sizeof(fault));
+  if (!job->hfault) return read_back(job, &fault, job->bar + (size_t)job->g.S * kBarStride, sizeof(fault));
+  const hipError_t e = hipStreamSynchronize(job->stream);
   if (e != hipSuccess) return device_error(job, e, "pt_get_*");
-  if (fault) {
-    job->poisoned = true;
-    return pt_fail(PT_EDEVICE, "a split sample's workgroups lost contact (barrier timed out)");
-  }
-  return PT_OK;
+  return fault_result(job, __atomic_load_n(job->hfault, __ATOMIC_ACQUIRE));
 }
 
 // Row of field f of word w (host copy of the device word geometry).
@@ -319,7 +366,7 @@ int job_create(pt_job** out, int32_t samples, int32_t replicas, int32_t L, int32
     const size_t W2 = 2 * (size_t)g.NW, per = (size_t)samples * 2 * g.nslot;
     job->Ex = (int32_t*)job->dalloc(sizeof(int32_t) * per);
     job->snap = (uint32_t*)job->dalloc(sizeof(uint32_t) * per * W2);
-    job->bar = (uint32_t*)job->dalloc(sizeof(uint32_t) * ((size_t)samples + 1));
+    job->bar = (uint32_t*)job->dalloc(sizeof(uint32_t) * bar_words(samples));
     split_mem = job->Ex && job->snap && job->bar;
   }
   if (!job->spins || !job->jw || !job->E || !job->sot || !job->tos || !job->thr || !job->thrpt ||
@@ -374,7 +421,7 @@ int job_create(pt_job** out, int32_t samples, int32_t replicas, int32_t L, int32
     step(hipMemsetAsync(job->walk, 0, sizeof(int32_t) * 2 * (size_t)nlat, st));
     step(hipMemsetAsync(job->trips, 0, sizeof(uint64_t) * 32 * 3 * (size_t)samples, st));
   }
-  if (job->bar) step(hipMemsetAsync(job->bar, 0, sizeof(uint32_t) * ((size_t)samples + 1), st));
+  if (job->bar) step(job->clear_bar(job->bar));
   step(launch_pack_couplings(g, J8, job->jw, st));
   step(launch_init_spins(g, job->spins, st));
   step(launch_energy(g, job->spins, job->jw, job->E, st));
@@ -503,11 +550,10 @@ int pt_table_len(const double* betas, int NT, int d, long N) {
 
 size_t split_scratch_bytes(const Geo& g, bool walk, bool modes) {
   FusedLayout lay;
-  int parts, R, jlds;
-  if (fused_plan(g, false, 2, 16, lay, walk, modes) || !split_plan(g, lay, parts, R, jlds, walk, modes))
-    return 0;
+  SplitPlan split;
+  if (fused_plan(g, false, 2, 16, lay, walk, modes) || !split_plan(g, split, walk, modes)) return 0;
   const size_t per = (size_t)g.S * 2 * g.nslot;
-  return sizeof(int32_t) * per + sizeof(uint32_t) * per * 2 * g.NW + sizeof(uint32_t) * (g.S + 1);
+  return sizeof(int32_t) * per + sizeof(uint32_t) * per * 2 * g.NW + sizeof(uint32_t) * bar_words(g.S);
 }
 
 size_t job_device_bytes(int S, int NT, int L, int d, int flags, const double* betas) {
@@ -710,7 +756,7 @@ PT_API int pt_mcs(pt_job* job, int32_t n, uint32_t flags) {
   // both sets per workgroup, one set per workgroup (no overlap needed), or
   // the sample split over several workgroups (no Houdayer move)
   if (!job->gauss && !(flags & PT_MCS_PLAIN) && job_is_resident(job, flags)) {
-    if (!job->self_batch) job->self_batch = batch_new(job->stream);
+    if (!job->self_batch) job->self_batch = batch_new(job->stream, true);
     if (!job->self_batch) return pt_fail(PT_ENOMEM, "pt_mcs: host allocation failed");
     const int chunk = 500;
     for (int done = 0; done < n; done += chunk) {
@@ -795,10 +841,9 @@ PT_API int pt_job_bytes(int32_t samples, int32_t replicas, int32_t L, int32_t di
 // ---------------------------------------------------------------------------
 PT_API int pt_get_counters(pt_job* job, uint64_t* out) {
   if (int rc = check_job(job)) return rc;
-  if (int rc = check_fault(job)) return rc;
   if (!out) return pt_fail(PT_EINVAL, "null output");
   DevCounters c;
-  PT_HIP(job, read_back(job, &c, job->ctr, sizeof(c)));
+  PT_READ(job, &c, job->ctr, sizeof(c));
   out[0] = c.t;
   out[1] = c.u;
   out[2] = c.v;
@@ -808,15 +853,14 @@ PT_API int pt_get_counters(pt_job* job, uint64_t* out) {
 
 PT_API int pt_get_spins(pt_job* job, int8_t* out) {
   if (int rc = check_job(job)) return rc;
-  if (int rc = check_fault(job)) return rc;
   if (!out) return pt_fail(PT_EINVAL, "null output");
   const Geo& g = job->g;
   if (g.layout == kLayoutPacked) {
     std::vector<uint32_t> tmp(job->spin_bytes() / sizeof(uint32_t));
-    PT_HIP(job, read_back(job, tmp.data(), job->spins, job->spin_bytes()));
+    PT_READ(job, tmp.data(), job->spins, job->spin_bytes());
     unpack_host(g, tmp.data(), out);
   } else {
-    PT_HIP(job, read_back(job, out, job->spins, job->spin_bytes()));
+    PT_READ(job, out, job->spins, job->spin_bytes());
   }
   return PT_OK;
 }
@@ -886,33 +930,30 @@ PT_API int pt_set_layout(pt_job* job, uint32_t layout) {
 PT_API int pt_get_energies(pt_job* job, int32_t* out) {
   if (int rc = check_job(job)) return rc;
   if (job->gauss) return pt_fail(PT_EINVAL, "Gaussian energies are 64-bit: use pt_get_energies64");
-  if (int rc = check_fault(job)) return rc;
   if (!out) return pt_fail(PT_EINVAL, "null output");
   const size_t n = (size_t)job->g.S * job->g.nslot;
-  PT_HIP(job, read_back(job, out, job->E, sizeof(int32_t) * n));
+  PT_READ(job, out, job->E, sizeof(int32_t) * n);
   return PT_OK;
 }
 
 PT_API int pt_get_maps(pt_job* job, int32_t* slot_of_temp, int32_t* temp_of_slot) {
   if (int rc = check_job(job)) return rc;
-  if (int rc = check_fault(job)) return rc;
   const size_t n = sizeof(int32_t) * (size_t)job->g.S * 2 * job->g.NT;
   if (slot_of_temp)
-    PT_HIP(job, read_back(job, slot_of_temp, job->sot, n));
+    PT_READ(job, slot_of_temp, job->sot, n);
   if (temp_of_slot)
-    PT_HIP(job, read_back(job, temp_of_slot, job->tos, n));
-  if (!slot_of_temp && !temp_of_slot) PT_HIP(job, hipStreamSynchronize(job->stream));
+    PT_READ(job, temp_of_slot, job->tos, n);
+  if (!slot_of_temp && !temp_of_slot) return check_fault(job);
   return PT_OK;
 }
 
 PT_API int pt_get_moments(pt_job* job, int64_t* out) {
   if (int rc = check_job(job)) return rc;
   if (job->gauss) return pt_fail(PT_EINVAL, "Gaussian jobs keep 128-bit E^2 sums: use pt_get_moments8");
-  if (int rc = check_fault(job)) return rc;
   if (!out) return pt_fail(PT_EINVAL, "null output");
   const size_t n = (size_t)job->g.S * job->g.NT;
   std::vector<int64_t> m(8 * n);
-  PT_HIP(job, read_back(job, m.data(), job->mom, sizeof(int64_t) * m.size()));
+  PT_READ(job, m.data(), job->mom, sizeof(int64_t) * m.size());
   for (size_t i = 0; i < n; ++i)
     for (int c = 0; c < 7; ++c) out[i * 7 + c] = m[i * 8 + c];
   return PT_OK;
@@ -920,25 +961,23 @@ PT_API int pt_get_moments(pt_job* job, int64_t* out) {
 
 PT_API int pt_get_energies64(pt_job* job, int64_t* out) {
   if (int rc = check_job(job)) return rc;
-  if (int rc = check_fault(job)) return rc;
   if (!out) return pt_fail(PT_EINVAL, "null output");
   const size_t n = (size_t)job->g.S * job->g.nslot;
   if (job->gauss) {
-    PT_HIP(job, read_back(job, out, job->E64, sizeof(int64_t) * n));
+    PT_READ(job, out, job->E64, sizeof(int64_t) * n);
     return PT_OK;
   }
   std::vector<int32_t> e32(n);
-  PT_HIP(job, read_back(job, e32.data(), job->E, sizeof(int32_t) * n));
+  PT_READ(job, e32.data(), job->E, sizeof(int32_t) * n);
   for (size_t i = 0; i < n; ++i) out[i] = e32[i];
   return PT_OK;
 }
 
 PT_API int pt_get_moments8(pt_job* job, int64_t* out) {
   if (int rc = check_job(job)) return rc;
-  if (int rc = check_fault(job)) return rc;
   if (!out) return pt_fail(PT_EINVAL, "null output");
   const size_t n = (size_t)job->g.S * job->g.NT;
-  PT_HIP(job, read_back(job, out, job->mom, sizeof(int64_t) * 8 * n));
+  PT_READ(job, out, job->mom, sizeof(int64_t) * 8 * n);
   if (!job->gauss)
     for (size_t i = 0; i < n; ++i) out[i * 8 + 7] = 0;  // +-J: E^2 sums fit 64 bits
   return PT_OK;
@@ -984,20 +1023,20 @@ PT_API int pt_gauss_accept_host(uint32_t r, double b, int64_t u) {
 PT_API int pt_get_walk(pt_job* job, int32_t* label, uint32_t* begin, uint64_t* trips) {
   if (int rc = check_job(job)) return rc;
   if (!job->track_walk) return pt_fail(PT_EINVAL, "the job was created without PT_TRACK_WALK");
-  if (int rc = check_fault(job)) return rc;
   const Geo& g = job->g;
   const size_t lat = (size_t)g.S * g.nslot;
   if (label || begin) {
     std::vector<int32_t> w(2 * lat);
-    PT_HIP(job, read_back(job, w.data(), job->walk, sizeof(int32_t) * w.size()));
+    PT_READ(job, w.data(), job->walk, sizeof(int32_t) * w.size());
     for (size_t i = 0; i < lat; ++i) {
       if (label) label[i] = w[2 * i];
       if (begin) begin[i] = (uint32_t)w[2 * i + 1];
     }
   }
   if (trips) {
-    PT_HIP(job, read_back(job, trips, job->trips, sizeof(uint64_t) * 32 * 3 * (size_t)g.S));
+    PT_READ(job, trips, job->trips, sizeof(uint64_t) * 32 * 3 * (size_t)g.S);
   }
+  if (!label && !begin && !trips) return check_fault(job);
   return PT_OK;
 }
 
@@ -1047,20 +1086,18 @@ PT_API int pt_tunnel_summary(const uint64_t* trips, int32_t rows, uint64_t passe
 
 PT_API int pt_get_stats(pt_job* job, int64_t* out) {
   if (int rc = check_job(job)) return rc;
-  if (int rc = check_fault(job)) return rc;
   if (!out) return pt_fail(PT_EINVAL, "null output");
   if (!job->track_stats) return pt_fail(PT_EINVAL, "the job was not created with PT_TRACK_STATS");
-  PT_HIP(job, read_back(job, out, job->stats, sizeof(int64_t) * (size_t)job->g.S * job->g.NT * kNStat));
+  PT_READ(job, out, job->stats, sizeof(int64_t) * (size_t)job->g.S * job->g.NT * kNStat);
   return PT_OK;
 }
 
 PT_API int pt_get_modes(pt_job* job, int64_t* out) {
   if (int rc = check_job(job)) return rc;
   if (!job->track_modes) return pt_fail(PT_EINVAL, "the job was created without PT_TRACK_MODES");
-  if (int rc = check_fault(job)) return rc;
   if (!out) return pt_fail(PT_EINVAL, "null output");
   const Geo& g = job->g;
-  PT_HIP(job, read_back(job, out, job->modes, sizeof(int64_t) * (size_t)g.S * g.NT * (g.L / 2 + 1)));
+  PT_READ(job, out, job->modes, sizeof(int64_t) * (size_t)g.S * g.NT * (g.L / 2 + 1));
   return PT_OK;
 }
 
