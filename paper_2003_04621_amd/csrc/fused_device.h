@@ -70,20 +70,29 @@ __device__ __forceinline__ void exchange_prepare(const FusedArgs& A, uint32_t* l
 // j of row (c, k), c-major, (N_T + 31) / 32 words a row.
 template <typename F>
 __device__ __forceinline__ void exchange_decide(int NT, int c_lo, int nsets, uint32_t* acc, F&& decide) {
-  const int tid = threadIdx.x, T = blockDim.x, NB = (NT + 31) & ~31;
-  const int lane = tid & 63, total = nsets * (NT - 1) * NB;  // a multiple of 32
-  uint32_t* accs = acc + (size_t)c_lo * (NT - 1) * (NB >> 5);
-  for (int base = tid - lane; base < total; base += T) {  // uniform per wavefront
-    const int i = base + lane;
-    bool ok = false;
-    if (i < total) {
-      const int row = i / NB, j = i - row * NB;
-      const int cl = row / (NT - 1), k = row - cl * (NT - 1), c = c_lo + cl;
-      if (j <= k) ok = decide(c, k, j);
+  // a half-wavefront per row (ladders of up to 32) or a wavefront: the row's
+  // set and step need no division
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwave = blockDim.x >> 6;
+  const int rows = nsets * (NT - 1), WB = (NT + 31) >> 5;
+  uint32_t* accs = acc + (size_t)c_lo * (NT - 1) * WB;
+  if (WB == 1) {
+    for (int r0 = 2 * wave; r0 < rows; r0 += 2 * nwave) {
+      const int row = r0 + (lane >> 5), j = lane & 31;
+      const int cl = row >= NT - 1 ? 1 : 0, k = row - cl * (NT - 1);
+      const bool ok = row < rows && j <= k && decide(c_lo + cl, k, j);
+      const uint64_t bits = __ballot(ok);
+      if (j == 0 && row < rows) accs[row] = lane ? (uint32_t)(bits >> 32) : (uint32_t)bits;
     }
-    const uint64_t bits = __ballot(ok);
-    if (lane == 0) accs[base >> 5] = (uint32_t)bits;
-    if (lane == 32 && base + 32 < total) accs[(base >> 5) + 1] = (uint32_t)(bits >> 32);
+  } else {
+    for (int row = wave; row < rows; row += nwave) {
+      const int cl = row >= NT - 1 ? 1 : 0, k = row - cl * (NT - 1);
+      for (int b = 0; b < WB; b += 2) {
+        const int j = 32 * b + lane;
+        const uint64_t bits = __ballot(j <= k && decide(c_lo + cl, k, j));
+        if (lane == 0) accs[row * WB + b] = (uint32_t)bits;
+        if (lane == 32 && b + 1 < WB) accs[row * WB + b + 1] = (uint32_t)(bits >> 32);
+      }
+    }
   }
 }
 
