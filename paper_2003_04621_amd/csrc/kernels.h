@@ -41,10 +41,11 @@ hipError_t launch_sweep(const Geo& g, void* spins, const uint32_t* jw, int32_t* 
 
 // One replica-exchange pass numbered ctr->u, followed by the replica-walk
 // bookkeeping of walk_observe (walk [S][2NT][2], trips [S][32][3]; both null
-// for a job that does not keep it).
+// for a job that does not keep it).  Advances ctr->t by dt and ctr->v by dv.
 hipError_t launch_exchange(const Geo& g, const int32_t* E, int32_t* sot, int32_t* tos,
                            const uint32_t* thrpt, int M, int32_t* walk, uint64_t* trips,
-                           DevCounters* ctr, int64_t* stats, hipStream_t st);
+                           DevCounters* ctr, int64_t* stats, hipStream_t st, uint32_t dt = 0,
+                           uint32_t dv = 0);
 
 // One Houdayer pass numbered ctr->v.
 hipError_t launch_houdayer(const Geo& g, void* spins, const uint32_t* jw, int32_t* E,
@@ -56,10 +57,12 @@ hipError_t launch_houdayer_multi(const Geo& g, void* spins, const uint32_t* jw, 
 
 // One measurement; mom is int64 [S][NT][8]; modes (null: not kept) int64
 // [S][NT][L/2+1] receives each temperature's mode_autocorr sums.  With
-// every > 1 nothing happens unless measures_at(ctr->t + 1, every).
+// every > 1 nothing happens unless measures_at(ctr->t + 1, every).  With
+// `last` it ends a step whose exchange has advanced ctr->t already (the
+// measured sweep is ctr->t) and advances ctr->u and, if it measures, n_meas.
 hipError_t launch_measure(const Geo& g, const void* spins, const int32_t* E,
                           const int32_t* sot, int64_t* mom, int64_t* modes, DevCounters* ctr,
-                          int every, hipStream_t st);
+                          int every, hipStream_t st, bool last = false);
 
 // Advances the device counters by `step` (one thread; enqueued after the
 // kernels that read them).

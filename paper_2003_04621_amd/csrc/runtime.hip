@@ -711,11 +711,17 @@ int mcs_per_step(pt_job* job, int32_t n, uint32_t flags) {
         PT_HIP(job, launch_houdayer_multi(g, job->spins, job->jw, job->E, job->sot, job->ctr, job->stats, st));
       else if (hou)
         PT_HIP(job, launch_houdayer(g, job->spins, job->jw, job->E, job->sot, job->ctr, job->stats, st));
+      // the exchange and the measurement advance the counters that they do not
+      // read themselves (one launch less per step)
       PT_HIP(job, launch_exchange(g, job->E, job->sot, job->tos, job->thrpt, job->M, job->walk,
-                                  job->trips, job->ctr, job->stats, st));
-      if (meas)
+                                  job->trips, job->ctr, job->stats, st, 1u, hou ? 1u : 0u));
+      if (meas) {
         PT_HIP(job, launch_measure(g, job->spins, job->E, job->sot, job->mom, job->modes, job->ctr,
-                                   job->meas_every, st));
+                                   job->meas_every, st, true));
+        continue;
+      }
+      PT_HIP(job, launch_advance(job->ctr, CounterStep{0, 1, 0, 0}, st));
+      continue;
     }
     PT_HIP(job, launch_advance(job->ctr, adv, st));
   }

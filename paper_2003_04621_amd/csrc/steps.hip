@@ -2,6 +2,7 @@
 // packing, energy recompute (Eq. (1)), replica exchange (Eq. (5)) and the
 // measurement of Eqs. (3)-(4).
 #include "device.h"
+#include "exchange_ops.h"
 #include "kernels.h"
 #include "rowops.h"
 
@@ -200,14 +201,68 @@ hipError_t launch_energy(const Geo& g, const void* spins, const uint32_t* jw, in
 }
 
 // ---------------------------------------------------------------------------
-// replica exchange, one lane per (sample, replica set); ascending k; then
-// the set's replica-walk bookkeeping if the job keeps it (walk not null)
+// replica exchange, then the replica-walk bookkeeping if the job keeps it
+// (walk not null).  Ladders of up to 64 temperatures: a workgroup of two
+// wavefronts per sample decides every (set, k, carried position) at once and
+// follows the chain by ballots; bound by the latency of its few dependent
+// loads (24 samples x 20 temperatures: 8.5 us with the launch, where one lane
+// per set walking the pass through global memory took 11.5).  Longer ladders
+// take that serial form: the chain of the other holds a set's positions in the
+// lanes of one wavefront.
 // ---------------------------------------------------------------------------
+__global__ void __launch_bounds__(128) k_exchange_rows(Geo g, const int32_t* __restrict__ E,
+                                                       int32_t* __restrict__ sot,
+                                                       int32_t* __restrict__ tos,
+                                                       const uint32_t* __restrict__ thrpt, int M,
+                                                       int32_t* __restrict__ walk,
+                                                       uint64_t* __restrict__ trips, DevCounters* ctr,
+                                                       int64_t* __restrict__ stats, uint32_t dt,
+                                                       uint32_t dv) {
+  constexpr int kMax = 64;
+  __shared__ int32_t El[2 * kMax], m0[2 * kMax], so[2 * kMax], to[2 * kMax];
+  __shared__ uint32_t rpt[2 * kMax], acc[2 * (kMax - 1) * 2];
+  const uint32_t u = load_counter(&ctr->u);
+  const int s = blockIdx.x, NT = g.NT, NS = 2 * NT, tid = threadIdx.x;
+  for (int i = tid; i < NS; i += 128) {
+    El[i] = E[(size_t)s * NS + i];
+    m0[i] = sot[(size_t)s * NS + i];
+    const int c = i >= NT ? 1 : 0, k = i - c * NT;
+    rpt[i] = philox10(Ctr4{(uint32_t)k, u, (uint32_t)c, (kTagPT << 28) | (uint32_t)s}, g.key0, g.key1).x;
+  }
+  __syncthreads();
+  exchange_decide(NT, 0, 2, acc, [&](int c, int k, int j) {
+    const int32_t D = El[c * NT + m0[c * NT + k + 1]] - El[c * NT + m0[c * NT + j]];
+    if (D <= 0) return true;
+    const int m = D >> 1;
+    return m < M && rpt[c * NT + k] < thrpt[(size_t)k * M + m];
+  });
+  __syncthreads();
+  exchange_chain<true>(NT, 0, 2, so, to, m0, acc, walk ? walk + (size_t)s * 2 * NS : nullptr,
+                       walk ? trips + (size_t)s * 32 * 3 : nullptr, u + 1u);
+  __syncthreads();
+  for (int i = tid; i < NS; i += 128) {
+    sot[(size_t)s * NS + i] = so[i];
+    tos[(size_t)s * NS + i] = to[i];
+    // an accepting step puts the configuration from above at k
+    const int k = i >= NT ? i - NT : i;
+    if (stats && k + 1 < NT && so[i] == m0[i + 1])  // both replica sets of the sample count here
+      atomicAdd(reinterpret_cast<unsigned long long*>(stats + ((size_t)s * NT + k) * kNStat + 1), 1ull);
+  }
+  if (s == 0 && tid == 0) {
+    ctr->t += dt;
+    ctr->v += dv;
+  }
+}
+
 __global__ void k_exchange(Geo g, const int32_t* __restrict__ E, int32_t* __restrict__ sot,
                            int32_t* __restrict__ tos, const uint32_t* __restrict__ thrpt, int M,
                            int32_t* __restrict__ walk, uint64_t* __restrict__ trips,
-                           DevCounters* ctr, int64_t* __restrict__ stats) {
+                           DevCounters* ctr, int64_t* __restrict__ stats, uint32_t dt, uint32_t dv) {
   const uint32_t u = load_counter(&ctr->u);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    ctr->t += dt;
+    ctr->v += dv;
+  }
   const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx < (long)g.S * 2) {
     const int s = (int)(idx >> 1), c = (int)(idx & 1);
@@ -247,10 +302,16 @@ __global__ void k_exchange(Geo g, const int32_t* __restrict__ E, int32_t* __rest
 
 hipError_t launch_exchange(const Geo& g, const int32_t* E, int32_t* sot, int32_t* tos,
                            const uint32_t* thrpt, int M, int32_t* walk, uint64_t* trips,
-                           DevCounters* ctr, int64_t* stats, hipStream_t st) {
-  const long lanes = (long)g.S * 2;
-  hipLaunchKernelGGL(k_exchange, dim3((unsigned)((lanes + 255) / 256)), dim3(256), 0, st, g, E, sot,
-                     tos, thrpt, M, walk, trips, ctr, stats);
+                           DevCounters* ctr, int64_t* stats, hipStream_t st, uint32_t dt,
+                           uint32_t dv) {
+  if (g.NT <= 64) {
+    hipLaunchKernelGGL(k_exchange_rows, dim3((unsigned)g.S), dim3(128), 0, st, g, E, sot, tos, thrpt, M,
+                       walk, trips, ctr, stats, dt, dv);
+  } else {
+    const long lanes = (long)g.S * 2;
+    hipLaunchKernelGGL(k_exchange, dim3((unsigned)((lanes + 255) / 256)), dim3(256), 0, st, g, E, sot,
+                       tos, thrpt, M, walk, trips, ctr, stats, dt, dv);
+  }
   return hipGetLastError();
 }
 
@@ -297,8 +358,13 @@ __device__ __forceinline__ void plane_counts_packed(const Geo& g, const uint32_t
 
 __global__ void __launch_bounds__(256) k_measure(Geo g, const void* spins, const int32_t* __restrict__ E,
                                                  const int32_t* __restrict__ sot, int64_t* mom,
-                                                 int64_t* modes, DevCounters* ctr, int every) {
-  if (!measures_at(load_counter(&ctr->t) + 1u, (uint32_t)every)) return;  // uniform
+                                                 int64_t* modes, DevCounters* ctr, int every, int last) {
+  const bool now = measures_at(load_counter(&ctr->t) + (last ? 0u : 1u), (uint32_t)every);
+  if (last && blockIdx.x == 0 && threadIdx.x == 0) {
+    ctr->u += 1u;
+    if (now) ctr->n_meas += 1u;
+  }
+  if (!now) return;  // uniform
   __shared__ int red;
   __shared__ int32_t cnt[3 * 64];
   const int pair = blockIdx.x;  // s*NT + k
@@ -321,20 +387,28 @@ __global__ void __launch_bounds__(256) k_measure(Geo g, const void* spins, const
     const int MH = g.L / 2 + 1;
     if ((int)threadIdx.x < MH) modes[(size_t)pair * MH + threadIdx.x] += mode_autocorr(g, cnt, threadIdx.x);
   }
+  // the two lattices as words; only the sign bits count in the int8 layout
+  const size_t bytes = g.layout == kLayoutPacked ? 8 * (size_t)g.NW : (size_t)g.N;
+  const uint32_t bits = g.layout == kLayoutPacked ? ~0u : 0x80808080u;
+  const char* base = static_cast<const char*>(spins) + (size_t)s * g.nslot * bytes;
+  const char *pa = base + (size_t)a * bytes, *pb = base + (size_t)b * bytes;
   int neg = 0;
-  if (g.layout == kLayoutPacked) {
-    const uint32_t* sa = static_cast<const uint32_t*>(spins) + ((size_t)s * g.nslot + a) * 2 * g.NW;
-    const uint32_t* sb = static_cast<const uint32_t*>(spins) + ((size_t)s * g.nslot + b) * 2 * g.NW;
-    for (int w = threadIdx.x; w < 2 * g.NW; w += blockDim.x) neg += __popc(sa[w] ^ sb[w]);
+  if (bytes % 16 == 0) {
+    // (lattices then start 16-byte aligned) 3D L = 32, 480 pairs: 6.5 us,
+    // 15.2 by single words
+    const uint4 *sa = reinterpret_cast<const uint4*>(pa), *sb = reinterpret_cast<const uint4*>(pb);
+#pragma unroll 4
+    for (int i = threadIdx.x; i < (int)(bytes / 16); i += blockDim.x) {
+      const uint4 x = sa[i], y = sb[i];
+      neg += __popc((x.x ^ y.x) & bits) + __popc((x.y ^ y.y) & bits) + __popc((x.z ^ y.z) & bits) +
+             __popc((x.w ^ y.w) & bits);
+    }
   } else {
-    const uint32_t* sa = reinterpret_cast<const uint32_t*>(static_cast<const int8_t*>(spins) +
-                                                           ((size_t)s * g.nslot + a) * g.N);
-    const uint32_t* sb = reinterpret_cast<const uint32_t*>(static_cast<const int8_t*>(spins) +
-                                                           ((size_t)s * g.nslot + b) * g.N);
-    for (int w = threadIdx.x; w < g.N / 4; w += blockDim.x)
-      neg += __popc((sa[w] ^ sb[w]) & 0x80808080u);
+    const uint32_t *sa = reinterpret_cast<const uint32_t*>(pa), *sb = reinterpret_cast<const uint32_t*>(pb);
+    for (int i = threadIdx.x; i < (int)(bytes / 4); i += blockDim.x) neg += __popc((sa[i] ^ sb[i]) & bits);
   }
-  atomicAdd(&red, neg);
+  neg = wave_total(neg);  // (every lane is here)
+  if ((threadIdx.x & 63) == 0) atomicAdd(&red, neg);
   __syncthreads();
   if (threadIdx.x == 0) {
     const int64_t Q = (int64_t)g.N - 2 * (int64_t)red;
@@ -356,9 +430,9 @@ __global__ void __launch_bounds__(256) k_measure(Geo g, const void* spins, const
 
 hipError_t launch_measure(const Geo& g, const void* spins, const int32_t* E, const int32_t* sot,
                           int64_t* mom, int64_t* modes, DevCounters* ctr, int every,
-                          hipStream_t st) {
+                          hipStream_t st, bool last) {
   hipLaunchKernelGGL(k_measure, dim3((unsigned)(g.S * g.NT)), dim3(256), 0, st, g, spins, E, sot, mom,
-                     modes, ctr, every);
+                     modes, ctr, every, last ? 1 : 0);
   return hipGetLastError();
 }
 

@@ -117,3 +117,35 @@ def test_multi_clusters_match_oracle(pt, d, L, S, NT, threads):
     same(pt, job, ref)
     pt.pt_batch_destroy(batch)
     pt.pt_destroy(job)
+
+
+# per-step exchange and measurement: ladders of one and two decision words and
+# of more than a wavefront, lattices of 16-byte and 4-byte rows of loads
+@pytest.mark.parametrize("d,L,S,NT,layout", [(3, 8, 3, 32, 0), (2, 6, 3, 33, 0), (2, 10, 2, 64, 1), (2, 6, 2, 70, 1),
+                                             (3, 6, 300, 2, 0), (3, 32, 1, 3, 0), (2, 64, 2, 17, 1)])
+def test_per_step_exchange_and_measure_match_oracle(pt, d, L, S, NT, layout):
+    J = W.couplings_pm_j(S, L, d, 70 + L)
+    betas = W.geometric_betas(0.6, 2.0, NT)
+    job = pt.pt_init(S, NT, L, d, J, betas, 13 + L, layout=layout, walk=True, modes=True)
+    ref = oracle.OracleJob(S, NT, L, d, J, betas, 13 + L)
+    ref.enable_modes()
+    for n, meas, every in ((4, True, 1), (3, False, 1), (5, True, 2), (1, True, 3)):
+        pt.pt_set_measure_interval(job, every)
+        ref.set_measure_every(every)
+        pt.pt_mcs(job, n, measure=meas, plain=True)
+        ref.mcs(n, measure=meas)
+        assert pt.pt_get_counters(job) == ref.counters()
+        same(pt, job, ref)
+    pt.pt_exchange(job)
+    pt.pt_measure(job)
+    ref.exchange()
+    ref.measure()
+    assert pt.pt_get_counters(job) == ref.counters()
+    same(pt, job, ref)
+    gm, rm = pt.pt_get_moments(job), ref.moments()
+    for k in rm:
+        assert (np.asarray(gm[k]) == np.asarray(rm[k]).astype(np.asarray(gm[k]).dtype)).all(), k
+    for a, b in zip(pt.pt_get_walk(job), ref.walk()):
+        assert (a == b).all()
+    assert (pt.pt_get_modes(job) == ref.modes()).all()
+    pt.pt_destroy(job)
