@@ -394,8 +394,15 @@ int build_worklist_ex(pt_batch* b, const std::vector<int>& steps, const std::vec
     b->cap_items = (int)hi.size();
   }
   if (!b->d_queue) {
-    e = hipMalloc((void**)&b->d_queue, 256);
+    uint32_t* q = nullptr;
+    e = hipMalloc((void**)&q, kQueueBytes);
     if (e != hipSuccess) return pt_fail(PT_ENOMEM, "pt_batch_run: device allocation failed");
+    e = launch_clear_queue(q, b->stream);
+    if (e != hipSuccess) {
+      (void)hipFree(q);
+      return pt_fail(PT_EDEVICE, std::string("pt_batch_run: ") + hipGetErrorString(e));
+    }
+    b->d_queue = q;
   }
   if (int rc = upload_worklist(b, hj.data(), hj.size(), hi.data(), hi.size())) return rc;
   b->args = hj;
@@ -679,10 +686,10 @@ int batch_run_job(pt_batch* b, pt_job* job, int mcs, uint32_t flags) {
 // ---- the work list in library-held device memory (pt_mcs_noalloc) ---------
 namespace {
 // Library-held scratch of pt_mcs_noalloc, one copy per GPU for the life of
-// the process: the work-queue counter (first 256 bytes), then the job's
-// launch arguments, then the work items.  In host code `scratch` only names
+// the process: the work-queue counters, then the job's launch arguments, then
+// the work items.  In host code `scratch` only names
 // the symbol; the device address comes from hipGetSymbolAddress.
-constexpr size_t kScratchArgsAt = 256;
+constexpr size_t kScratchArgsAt = kQueueBytes;
 constexpr size_t kScratchItemsAt = (kScratchArgsAt + sizeof(FusedArgs) + 255) / 256 * 256;
 constexpr size_t kScratchMaxItems = PT_NOALLOC_MAX_ITEMS;
 constexpr size_t kScratchBytes = kScratchItemsAt + kScratchMaxItems * sizeof(BatchItem);
@@ -743,8 +750,12 @@ int batch_run_job_noalloc(pt_job* job, int mcs, uint32_t flags, int* nitems_out)
   if (int rc = launch_shape(d, wl.feat, lds_bytes, nitems, ncu, 0, &threads, &per_cu)) return rc;
   const int blocks = std::max(1, std::min(ncu * per_cu, nitems));
   // pageable host sources: each copy has read its source when it returns,
-  // and it is ordered on the stream before the launch that reads it
-  e = hipMemcpyAsync(d_jobs, wl.jobs.data(), sizeof(FusedArgs), hipMemcpyHostToDevice, job->stream);
+  // and it is ordered on the stream before the launch that reads it.  The
+  // queue's zeros come along: a caller's mistake with this shared scratch
+  // does not outlive the call that it spoils.
+  unsigned char head[kScratchArgsAt + sizeof(FusedArgs)] = {};
+  std::memcpy(head + kScratchArgsAt, wl.jobs.data(), sizeof(FusedArgs));
+  e = hipMemcpyAsync(base, head, sizeof(head), hipMemcpyHostToDevice, job->stream);
   if (e == hipSuccess)
     e = hipMemcpyAsync(d_items, wl.items.data(), sizeof(BatchItem) * wl.items.size(),
                        hipMemcpyHostToDevice, job->stream);

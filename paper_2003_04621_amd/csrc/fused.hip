@@ -1,5 +1,4 @@
-// fused.hip -- host side of the fused Monte Carlo step kernels: the queue
-// reset and counter advance kernels, LDS plans of resident and split samples,
+// fused.hip -- host side of the fused Monte Carlo step kernels: LDS plans of resident and split samples,
 // launch arguments, and the launch of the persistent batch kernel whose
 // device code is in fused_device.h.
 #include <algorithm>
@@ -10,18 +9,6 @@
 #include "fused_device.h"
 
 namespace ptsg {
-
-// Clears the queue and the barrier counters of every split job (block j
-// serves job j - 1).
-__global__ void k_batch_reset(const FusedArgs* __restrict__ jobs, uint32_t* queue) {
-  if (blockIdx.x == 0) {
-    if (threadIdx.x == 0) *queue = 0u;
-    return;
-  }
-  const FusedArgs& A = jobs[blockIdx.x - 1];
-  if (A.parts == 0) return;
-  for (int i = threadIdx.x; i < A.g.S; i += blockDim.x) A.bar[(size_t)i * kBarStride] = 0u;
-}
 
 __global__ void k_clear_bar(uint32_t* bar, int words, int at, uint64_t host_fault) {
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < words; i += gridDim.x * blockDim.x)
@@ -34,17 +21,12 @@ hipError_t launch_clear_bar(uint32_t* bar, int S, uint32_t* host_fault, hipStrea
   return hipGetLastError();
 }
 
-// Advances every job's counters by its own number of steps in this launch.
-__global__ void k_batch_advance(const FusedArgs* __restrict__ jobs, int njobs) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= njobs) return;
-  const FusedArgs& A = jobs[j];
-  DevCounters* c = const_cast<DevCounters*>(A.ctr);
-  const uint32_t n = (uint32_t)A.nmcs, t0 = c->t, e = (uint32_t)A.every;
-  c->t += n;
-  c->u += n;
-  if (A.hou) c->v += n;
-  if (A.meas) c->n_meas += e > 1u ? (t0 + n) / e - t0 / e : n;
+__global__ void k_clear_queue(uint32_t* queue) {
+  if (threadIdx.x < kQueueBytes / 4) queue[threadIdx.x] = 0u;
+}
+hipError_t launch_clear_queue(uint32_t* queue, hipStream_t st) {
+  hipLaunchKernelGGL(k_clear_queue, dim3(1), dim3(64), 0, st, queue);
+  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
@@ -250,11 +232,8 @@ hipError_t batch_residency(int d, int feat, int threads, size_t lds_bytes, int* 
 hipError_t launch_batch(int d, int feat, const FusedArgs* jobs, int njobs, const BatchItem* items,
                         int nitems, uint32_t* queue, int blocks, int threads, size_t lds_bytes,
                         hipStream_t st) {
-  hipLaunchKernelGGL(k_batch_reset, dim3((unsigned)njobs + 1), dim3(256), 0, st, jobs, queue);
   hipLaunchKernelGGL(batch_kernel(d, feat), dim3(blocks), dim3(threads), lds_bytes, st, jobs, items,
-                     nitems, queue);
-  hipLaunchKernelGGL(k_batch_advance, dim3((unsigned)((njobs + 255) / 256)), dim3(256), 0, st, jobs,
-                     njobs);
+                     nitems, queue, njobs);
   return hipGetLastError();
 }
 

@@ -158,8 +158,13 @@ FusedArgs make_fused_args(const Geo& g, const FusedLayout& lay, void* spins, con
 // modes); the launch runs the kernel compiled for exactly that set.
 constexpr int kFeatHou = 1, kFeatMeas = 2, kFeatSplit = 4, kFeatWalk = 8, kFeatModes = 16;
 
-// Persistent batch: resets the queue, runs every item to its job's nmcs, then
-// advances each job's counters.  `jobs` and `items` are device arrays.
+// Persistent batch: runs every item to its job's nmcs, then advances each
+// job's counters.  `jobs` and `items` are device arrays; `queue` (kQueueBytes)
+// counts the items taken in its first word and the workgroups done in word
+// kQueueDone, both zero before a launch, as launch_clear_queue makes them once
+// and every launch leaves them.
+constexpr int kQueueBytes = 256, kQueueDone = 32;  // (a cache line apart)
+hipError_t launch_clear_queue(uint32_t* queue, hipStream_t st);
 // prepare_batch sets the kernel's dynamic LDS limit and reports its VGPRs
 // per lane.
 hipError_t prepare_batch(int d, int feat, size_t lds_bytes, int* vgprs);

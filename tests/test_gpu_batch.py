@@ -277,3 +277,31 @@ def test_tuner_restores_walk_and_modes(pt):
         matches_oracle(pt, j, r)
         assert (pt.pt_get_modes(j) == r.modes()).all()
     assert sum(int(pt.pt_get_walk(j)[2][..., 0].sum()) for j in jobs) > 0
+
+
+@pytest.mark.parametrize("graph", [False, True])
+def test_more_jobs_than_threads_advance_together(pt, graph):
+    """The last workgroup of a launch advances every job and clears the launch's counts."""
+    n = 300  # more than a 256-thread workgroup
+    jobs, refs = [], []
+    for i in range(n):
+        L, NT = (4, 2) if i % 3 else (6, 3)
+        J = W.couplings_pm_j(1, L, 2, 400 + i)
+        betas = W.geometric_betas(0.5, 2.0, NT)
+        jobs.append(pt.pt_init(1, NT, L, 2, J, betas, 31 + i))
+        refs.append(oracle.OracleJob(1, NT, L, 2, J, betas, 31 + i))
+    batch = pt.pt_batch_create(jobs)
+    pt.pt_batch_set_config(batch, 256, 2, 0)
+    for steps in (2, 1, 3):
+        pt.pt_batch_run(batch, steps, graph=graph)
+        pt.pt_mcs(jobs[7], 1)
+        for i, ref in enumerate(refs):
+            ref.mcs(steps)
+        refs[7].mcs(1)
+    for job, ref in zip(jobs, refs):
+        assert pt.pt_get_counters(job) == ref.counters()
+        assert (pt.pt_get_spins(job) == ref.spins()).all()
+        assert (pt.pt_get_energies(job) == ref.energies()).all()
+    pt.pt_batch_destroy(batch)
+    for job in jobs:
+        pt.pt_destroy(job)
