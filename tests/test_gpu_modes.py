@@ -135,3 +135,23 @@ def test_modes_are_opt_in_and_checkpointed(pt):
     same_modes(pt, c, ref, "restored")
     assert pt.pt_plan_query(3, 32, 24, measure=True, modes=True)["mode"] == 3  # split samples
     assert pt.pt_plan_query(3, 32, 24, measure=True)["mode"] == 3
+
+
+@pytest.mark.parametrize("d,L,NT", [(3, 4, 3), (3, 10, 4), (3, 14, 3), (3, 18, 2), (3, 20, 3), (3, 24, 2), (3, 28, 2),
+                                    (3, 40, 2), (3, 44, 2), (3, 56, 2), (3, 64, 2), (2, 4, 3), (2, 6, 18), (2, 30, 3),
+                                    (2, 32, 3), (2, 34, 3), (2, 50, 3), (2, 62, 3)])
+def test_fused_modes_at_every_kind_of_size(pt, d, L, NT):
+    """Column counts of one and several chunks of words, plane counts shared by 2, 4, 8 and 16
+    lanes, and one or two passes over the axes' pairs of planes."""
+    say(f"modes {d}D L={L} NT={NT}")
+    S, seed = 2, 50 + L
+    J = W.couplings_pm_j(S, L, d, 60 + L)
+    betas = W.geometric_betas(0.4, 1.6, NT)
+    job = pt.pt_init(S, NT, L, d, J, betas, seed, layout=(L // 2) & 1, modes=True)
+    ref = oracle.OracleJob(S, NT, L, d, J, betas, seed)
+    ref.enable_modes()
+    for n in (2, 1):
+        pt.pt_mcs(job, n, measure=True)
+        ref.mcs(n, measure=True)
+        same_modes(pt, job, ref, f"{d}D L={L} after {n}")
+    pt.pt_destroy(job)
