@@ -132,7 +132,7 @@ __global__ void __launch_bounds__(512) k_gsweep(Geo g, void* spins, const int4* 
                                                 const double* __restrict__ beta,
                                                 const float* __restrict__ cz,
                                                 const DevCounters* __restrict__ ctr, int nsweeps,
-                                                int CH, int nchunk) {
+                                                int CH, int nchunk, int out) {
   extern __shared__ __align__(16) uint32_t lds_s[];
   const int T = blockDim.x, t = threadIdx.x;
   const int NW = g.NW, NGc = gauss_groups(g);
@@ -206,7 +206,9 @@ __global__ void __launch_bounds__(512) k_gsweep(Geo g, void* spins, const int4* 
       __syncthreads();
     }
   }
-  for (int l = 0; l < nl; ++l) store_lattice(g, spins, lat0 + l, W + (size_t)l * 2 * NW, t, T);
+  Geo go = g;
+  go.layout = out;
+  for (int l = 0; l < nl; ++l) store_lattice(go, spins, lat0 + l, W + (size_t)l * 2 * NW, t, T);
   for (int l = t; l < nl; l += T) E64[lat0 + l] += (int64_t)El[l];
 }
 
@@ -321,19 +323,8 @@ __global__ void __launch_bounds__(256) k_gmeasure(Geo g, const void* spins, cons
   const int b = g.NT + sot[((size_t)s * 2 + 1) * g.NT + k];
   if (threadIdx.x == 0) red = 0;
   __syncthreads();
-  int neg = 0;
-  if (g.layout == kLayoutPacked) {
-    const uint32_t* sa = static_cast<const uint32_t*>(spins) + ((size_t)s * g.nslot + a) * 2 * g.NW;
-    const uint32_t* sb = static_cast<const uint32_t*>(spins) + ((size_t)s * g.nslot + b) * 2 * g.NW;
-    for (int w = threadIdx.x; w < 2 * g.NW; w += blockDim.x) neg += __popc(sa[w] ^ sb[w]);
-  } else {
-    const uint32_t* sa = reinterpret_cast<const uint32_t*>(static_cast<const int8_t*>(spins) +
-                                                           ((size_t)s * g.nslot + a) * g.N);
-    const uint32_t* sb = reinterpret_cast<const uint32_t*>(static_cast<const int8_t*>(spins) +
-                                                           ((size_t)s * g.nslot + b) * g.N);
-    for (int w = threadIdx.x; w < g.N / 4; w += blockDim.x) neg += __popc((sa[w] ^ sb[w]) & 0x80808080u);
-  }
-  atomicAdd(&red, neg);
+  const int neg = wave_total(differing_sites(g, spins, s, a, b));
+  if ((threadIdx.x & 63) == 0) atomicAdd(&red, neg);
   __syncthreads();
   if (threadIdx.x == 0) {
     const int64_t Q = (int64_t)g.N - 2 * (int64_t)red;
@@ -416,7 +407,7 @@ void gauss_sweep_shape(const Geo& g, int& threads, int& CH, int& nchunk, size_t&
 
 hipError_t launch_gauss_sweep(const Geo& g, void* spins, const int4* Jg, int64_t* E64,
                               const int32_t* tos, const double* beta, const float* cz,
-                              const DevCounters* ctr, int n, hipStream_t st) {
+                              const DevCounters* ctr, int n, hipStream_t st, int out) {
   int threads, CH, nchunk;
   size_t lds;
   gauss_sweep_shape(g, threads, CH, nchunk, lds);
@@ -424,11 +415,11 @@ hipError_t launch_gauss_sweep(const Geo& g, void* spins, const int4* Jg, int64_t
   if (g.d == 3) {
     if (hipError_t e = allow_lds(k_gsweep<3>, lds)) return e;
     hipLaunchKernelGGL(k_gsweep<3>, dim3(blocks), dim3(threads), lds, st, g, spins, Jg, E64, tos, beta,
-                       cz, ctr, n, CH, nchunk);
+                       cz, ctr, n, CH, nchunk, out < 0 ? g.layout : out);
   } else {
     if (hipError_t e = allow_lds(k_gsweep<2>, lds)) return e;
     hipLaunchKernelGGL(k_gsweep<2>, dim3(blocks), dim3(threads), lds, st, g, spins, Jg, E64, tos, beta,
-                       cz, ctr, n, CH, nchunk);
+                       cz, ctr, n, CH, nchunk, out < 0 ? g.layout : out);
   }
   return hipGetLastError();
 }

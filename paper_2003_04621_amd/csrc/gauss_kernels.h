@@ -17,7 +17,7 @@ hipError_t launch_gauss_energy(const Geo& g, const void* spins, const int4* Jg, 
 // double [NT], cz float [NT] = gauss_cz(beta).
 hipError_t launch_gauss_sweep(const Geo& g, void* spins, const int4* Jg, int64_t* E64,
                               const int32_t* tos, const double* beta, const float* cz,
-                              const DevCounters* ctr, int n, hipStream_t st);
+                              const DevCounters* ctr, int n, hipStream_t st, int out = -1);
 // Launch shape of the sweep: threads per block, temperatures per block, blocks
 // per (sample, set), dynamic LDS bytes.
 void gauss_sweep_shape(const Geo& g, int& threads, int& CH, int& nchunk, size_t& lds);

@@ -34,10 +34,11 @@ hipError_t launch_energy(const Geo& g, const void* spins, const uint32_t* jw, in
 constexpr int kNStat = 24;
 
 // n checkerboard Metropolis sweeps starting at sweep number ctr->t (stats:
-// null, or the diagnostics above).
+// null, or the diagnostics above).  The spins are read in g's layout and
+// written in layout `out` (-1: the same).
 hipError_t launch_sweep(const Geo& g, void* spins, const uint32_t* jw, int32_t* E,
                         const int32_t* tos, const uint32_t* thr, DevCounters* ctr, int n,
-                        int64_t* stats, hipStream_t st);
+                        int64_t* stats, hipStream_t st, int out = -1);
 
 // One replica-exchange pass numbered ctr->u, followed by the replica-walk
 // bookkeeping of walk_observe (walk [S][2NT][2], trips [S][32][3]; both null

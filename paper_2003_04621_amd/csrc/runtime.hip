@@ -690,15 +690,23 @@ int check_mcs(pt_job* job, int32_t n, uint32_t flags) {
 // exactly one kernel, so a single advance per step keeps the numbering of
 // the separate entry points.
 int mcs_per_step(pt_job* job, int32_t n, uint32_t flags) {
-  const Geo& g = job->g;
   hipStream_t st = job->stream;
   const bool hou = flags & PT_MCS_HOUDAYER, meas = flags & PT_MCS_MEASURE;
   const bool multi = flags & PT_MCS_MULTICLUSTER;
   const CounterStep adv{1, 1, hou ? 1u : 0u, meas ? 1u : 0u, (uint32_t)job->meas_every};
+  // An int8 job's spins stay packed in place between the steps: the first
+  // sweep stores them so, the last one as int8 again, each reading what the
+  // step before left (the sweep loads a whole lattice before it stores it).
+  // Ten steps of 3D L = 32, 24 samples x 20 temperatures, with Houdayer moves
+  // and measurement: 878 -> 729 us (a sweep 32 -> 24 us, a move 36 -> 29).
+  const bool stage = n > 1 && job->g.layout == kLayoutInt8;
   for (int i = 0; i < n; ++i) {
+    Geo g = job->g, in = job->g;
+    if (stage && i > 0) in.layout = kLayoutStaged;
+    if (stage && i + 1 < n) g.layout = kLayoutStaged;
     if (job->gauss) {
-      PT_HIP(job, launch_gauss_sweep(g, job->spins, job->gJ, job->E64, job->tos, job->gbeta, job->gcz,
-                                     job->ctr, 1, st));
+      PT_HIP(job, launch_gauss_sweep(in, job->spins, job->gJ, job->E64, job->tos, job->gbeta, job->gcz,
+                                     job->ctr, 1, st, g.layout));
       if (hou)
         PT_HIP(job, launch_gauss_houdayer(g, job->spins, job->gJ, job->E64, job->sot, job->ctr, multi, st));
       PT_HIP(job, launch_gauss_exchange(g, job->E64, job->sot, job->tos, job->gbeta, job->ctr, st));
@@ -706,7 +714,8 @@ int mcs_per_step(pt_job* job, int32_t n, uint32_t flags) {
         PT_HIP(job, launch_gauss_measure(g, job->spins, job->E64, job->sot, job->mom, job->ctr,
                                          job->meas_every, st));
     } else {
-      PT_HIP(job, launch_sweep(g, job->spins, job->jw, job->E, job->tos, job->thr, job->ctr, 1, job->stats, st));
+      PT_HIP(job, launch_sweep(in, job->spins, job->jw, job->E, job->tos, job->thr, job->ctr, 1, job->stats, st,
+                               g.layout));
       if (hou && multi)
         PT_HIP(job, launch_houdayer_multi(g, job->spins, job->jw, job->E, job->sot, job->ctr, job->stats, st));
       else if (hou)

@@ -376,9 +376,10 @@ __global__ void __launch_bounds__(256) k_measure(Geo g, const void* spins, const
     for (int i = threadIdx.x; i < 3 * g.L; i += blockDim.x) cnt[i] = 0;
   __syncthreads();
   if (modes) {
-    if (g.layout == kLayoutPacked) {
-      const uint32_t* base = static_cast<const uint32_t*>(spins) + (size_t)s * g.nslot * 2 * g.NW;
-      plane_counts_packed(g, base + (size_t)a * 2 * g.NW, base + (size_t)b * 2 * g.NW, cnt);
+    if (g.layout != kLayoutInt8) {
+      const size_t stride = lattice_stride(g) / 4;
+      const uint32_t* base = static_cast<const uint32_t*>(spins) + (size_t)s * g.nslot * stride;
+      plane_counts_packed(g, base + (size_t)a * stride, base + (size_t)b * stride, cnt);
     } else {
       const int8_t* base = static_cast<const int8_t*>(spins) + (size_t)s * g.nslot * g.N;
       plane_counts_int8(g, base + (size_t)a * g.N, base + (size_t)b * g.N, cnt);
@@ -387,27 +388,7 @@ __global__ void __launch_bounds__(256) k_measure(Geo g, const void* spins, const
     const int MH = g.L / 2 + 1;
     if ((int)threadIdx.x < MH) modes[(size_t)pair * MH + threadIdx.x] += mode_autocorr(g, cnt, threadIdx.x);
   }
-  // the two lattices as words; only the sign bits count in the int8 layout
-  const size_t bytes = g.layout == kLayoutPacked ? 8 * (size_t)g.NW : (size_t)g.N;
-  const uint32_t bits = g.layout == kLayoutPacked ? ~0u : 0x80808080u;
-  const char* base = static_cast<const char*>(spins) + (size_t)s * g.nslot * bytes;
-  const char *pa = base + (size_t)a * bytes, *pb = base + (size_t)b * bytes;
-  int neg = 0;
-  if (bytes % 16 == 0) {
-    // (lattices then start 16-byte aligned) 3D L = 32, 480 pairs: 6.5 us,
-    // 15.2 by single words
-    const uint4 *sa = reinterpret_cast<const uint4*>(pa), *sb = reinterpret_cast<const uint4*>(pb);
-#pragma unroll 4
-    for (int i = threadIdx.x; i < (int)(bytes / 16); i += blockDim.x) {
-      const uint4 x = sa[i], y = sb[i];
-      neg += __popc((x.x ^ y.x) & bits) + __popc((x.y ^ y.y) & bits) + __popc((x.z ^ y.z) & bits) +
-             __popc((x.w ^ y.w) & bits);
-    }
-  } else {
-    const uint32_t *sa = reinterpret_cast<const uint32_t*>(pa), *sb = reinterpret_cast<const uint32_t*>(pb);
-    for (int i = threadIdx.x; i < (int)(bytes / 4); i += blockDim.x) neg += __popc((sa[i] ^ sb[i]) & bits);
-  }
-  neg = wave_total(neg);  // (every lane is here)
+  const int neg = wave_total(differing_sites(g, spins, s, a, b));
   if ((threadIdx.x & 63) == 0) atomicAdd(&red, neg);
   __syncthreads();
   if (threadIdx.x == 0) {

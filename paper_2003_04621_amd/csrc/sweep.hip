@@ -14,7 +14,7 @@ __global__ void __launch_bounds__(256) k_sweep(Geo g, void* spins, const uint32_
                                                const int32_t* __restrict__ tos,
                                                const uint32_t* __restrict__ thr,
                                                DevCounters* ctr, int nsweeps, int T, int LPB,
-                                               int64_t* stats) {
+                                               int64_t* stats, int out) {
   extern __shared__ uint32_t lds[];
   int* red = reinterpret_cast<int*>(lds);  // [LPB] energy changes, then [LPB] flip counts
   uint32_t* W0 = lds + 2 * LPB;
@@ -53,7 +53,9 @@ __global__ void __launch_bounds__(256) k_sweep(Geo g, void* spins, const uint32_
     }
   }
   if (active) {
-    store_lattice(g, spins, (size_t)lat, W, t, T);
+    Geo go = g;
+    go.layout = out;
+    store_lattice(go, spins, (size_t)lat, W, t, T);
     atomicAdd(&red[li], dE);
     if (stats && nf) atomicAdd(&red[LPB + li], nf);
   }
@@ -77,7 +79,8 @@ void sweep_shape(const Geo& g, int& T, int& LPB, int& threads, size_t& lds) {
 
 hipError_t launch_sweep(const Geo& g, void* spins, const uint32_t* jw, int32_t* E,
                         const int32_t* tos, const uint32_t* thr, DevCounters* ctr, int n,
-                        int64_t* stats, hipStream_t st) {
+                        int64_t* stats, hipStream_t st, int out) {
+  if (out < 0) out = g.layout;
   int T, LPB, threads;
   size_t lds;
   sweep_shape(g, T, LPB, threads, lds);
@@ -87,12 +90,12 @@ hipError_t launch_sweep(const Geo& g, void* spins, const uint32_t* jw, int32_t* 
     if (lds > 65536)
       { const hipError_t ea = hipFuncSetAttribute((const void*)k_sweep<3>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); if (ea != hipSuccess) return ea; }
     hipLaunchKernelGGL(k_sweep<3>, dim3(blocks), dim3(threads), lds, st, g, spins, jw, E, tos, thr,
-                       ctr, n, T, LPB, stats);
+                       ctr, n, T, LPB, stats, out);
   } else {
     if (lds > 65536)
       { const hipError_t ea = hipFuncSetAttribute((const void*)k_sweep<2>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); if (ea != hipSuccess) return ea; }
     hipLaunchKernelGGL(k_sweep<2>, dim3(blocks), dim3(threads), lds, st, g, spins, jw, E, tos, thr,
-                       ctr, n, T, LPB, stats);
+                       ctr, n, T, LPB, stats, out);
   }
   return hipGetLastError();
 }

@@ -149,3 +149,27 @@ def test_per_step_exchange_and_measure_match_oracle(pt, d, L, S, NT, layout):
         assert (a == b).all()
     assert (pt.pt_get_modes(job) == ref.modes()).all()
     pt.pt_destroy(job)
+
+
+# the spins of an int8 job between the steps of one call: sizes whose packed
+# words fill their int8 bytes, whose lattices do and do not start 16-byte
+# aligned, one and several words per thread
+@pytest.mark.parametrize("d,L,S,NT,multi", [(2, 4, 3, 3, False), (2, 6, 5, 3, True), (2, 14, 3, 4, False),
+                                            (2, 50, 2, 3, True), (2, 64, 2, 3, False), (3, 4, 3, 3, True),
+                                            (3, 6, 3, 3, False), (3, 16, 2, 3, True), (3, 28, 1, 2, False)])
+def test_int8_jobs_step_as_packed_ones(pt, d, L, S, NT, multi):
+    J = W.couplings_pm_j(S, L, d, 80 + L)
+    betas = W.geometric_betas(0.5, 2.0, NT)
+    job = pt.pt_init(S, NT, L, d, J, betas, 17 + L, layout=0, modes=True)
+    ref = oracle.OracleJob(S, NT, L, d, J, betas, 17 + L)
+    ref.enable_modes()
+    for n, hou in ((2, False), (1, True), (4, True), (3, False)):
+        pt.pt_mcs(job, n, houdayer=hou, measure=True, plain=True, multi=multi and hou)
+        ref.mcs(n, houdayer=hou, measure=True, multi=multi and hou)
+        assert (pt.pt_get_energies(job) == ref.energies()).all()
+        same(pt, job, ref)
+        assert (pt.pt_get_modes(job) == ref.modes()).all()
+        gm, rm = pt.pt_get_moments(job), ref.moments()
+        for k in rm:
+            assert (np.asarray(gm[k]) == np.asarray(rm[k]).astype(np.asarray(gm[k]).dtype)).all(), k
+    pt.pt_destroy(job)
