@@ -160,10 +160,12 @@ __device__ void gauss_houdayer_resident(const Geo& g, uint32_t* W, int64_t* El, 
 
 // The same for a 2D sample: the cluster is found in registers, one row per
 // lane (rows_cluster), pairs from the hottest down; the energy change sums,
-// over the cluster's boundary bonds from this row's colour-0 sites (a few per
-// row), the bond's -2n from its coupling group with the sign of replica a
-// across it.  Ends with a workgroup barrier, after which the pair counter is
-// cleared.
+// over the cluster's boundary bonds from this row's colour-0 sites, the bond's
+// -2n from its coupling group with the sign of replica a across it.  Four
+// groups a lane are loaded at once (one at a time waited for the L2 at each;
+// eight spill) and added without branches: 2D L = 64, 500 samples x 2 x 24, the
+// moves of a step 55 -> 45 us.  Ends with a workgroup barrier, after which the
+// pair counter is cleared.
 template <int LS>
 __device__ void gauss_houdayer_rows(const Geo& gw, uint32_t* W, int64_t* El, const int32_t* sotl,
                                     const int4* __restrict__ J0, int s, uint32_t v, uint32_t* hctr) {
@@ -201,22 +203,29 @@ __device__ void gauss_houdayer_rows(const Geo& gw, uint32_t* W, int64_t* El, con
     nc[3] = row_prev<LS>(lr, c1);
     na[2] = row_next<LS>(lr, a1);
     na[3] = row_prev<LS>(lr, a1);
-    int64_t dl = 0;
+    // (-2n of a bond is at most 2^20 in size, a row has 128: 32 bits hold the
+    // sum; a subtracted bond adds its complement, and one from the count)
+    int32_t dl = 0;
 #pragma unroll
     for (int dir = 0; dir < 4; ++dir) {
-      const uint32_t X = c0 ^ nc[dir];  // bonds leaving the cluster
-      const uint32_t U = a0 ^ na[dir];  // replica a antiparallel across them
-      for (uint32_t grp = X; grp;) {
-        const int q = __builtin_ctz(grp) >> 2;  // group of four sites of the row
-        const uint32_t xb = (X >> (4 * q)) & 0xFu, ub = (U >> (4 * q)) & 0xFu;
-        grp &= ~(0xFu << (4 * q));
-        const int4 m = J0[(size_t)dir * NGc + g0 + NW * q];
+      const uint32_t X = c0 ^ nc[dir];             // bonds leaving the cluster
+      const uint32_t M = X & ~(a0 ^ na[dir]);      // replica a parallel across them
+      dl += __popc(M);
+#pragma unroll 1
+      for (int q0 = 0; 4 * q0 < g.H; q0 += 4) {    // groups of four sites, four loads in flight
+        int4 m[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-          if ((xb >> j) & 1u) dl += ((ub >> j) & 1u) ? lane_of(m, j) : -lane_of(m, j);
+        for (int i = 0; i < 4; ++i) {
+          m[i] = int4{0, 0, 0, 0};
+          if ((X >> (4 * (q0 + i))) & 0xFu) m[i] = J0[(size_t)dir * NGc + g0 + NW * (q0 + i)];
+        }
+        const uint32_t x4 = X >> (4 * q0), m4 = M >> (4 * q0);
+#pragma unroll
+        for (int j = 0; j < 16; ++j)
+          dl += (lane_of(m[j >> 2], j & 3) & __builtin_amdgcn_sbfe(x4, j, 1)) ^ __builtin_amdgcn_sbfe(m4, j, 1);
       }
     }
-    const int64_t delta = wave_sum64(dl);
+    const int64_t delta = wave_sum64((int64_t)dl);
     rows_exchange<LS>(lr, NW, Wa, Wb, ab, c0, c1);
     if (lane == 0) {
       El[a] += delta;
