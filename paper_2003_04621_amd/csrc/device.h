@@ -194,9 +194,10 @@ struct DevCounters {
   uint32_t pad[4];
 };
 
-// Counters are read by the kernels at their start and advanced afterwards by
-// k_advance, a one-thread kernel enqueued behind them on the same stream (a
-// per-block atomic on one address serialises tens of thousands of blocks).
+// Counters are read by the kernels at their start and advanced behind them: by
+// the last workgroup of a fused launch, by a per-step kernel that does not read
+// the counter it advances, or by k_advance, a one-thread kernel on the same
+// stream.
 struct CounterStep {
   uint32_t dt, du, dv, dm;
   // measurement interval (0 or 1: dm as given); with every > 1 the dt sweeps

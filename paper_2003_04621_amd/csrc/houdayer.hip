@@ -9,7 +9,7 @@
 // delta = 2 (#boundary bonds - 2 #unsatisfied boundary bonds), counted on
 // colour-0 words where every bond has one end.  Bound by the rounds of the
 // fill (an LDS round trip and a workgroup barrier each): 3D L = 32, 480 pairs:
-// 78 -> 37 us from whole runs along x0, a word per thread held in registers with
+// 78 -> 37 us (29 from packed spins) from whole runs along x0, a word per thread held in registers with
 // one barrier per round, and a seed search by wavefront scans (it was serial).
 #include "device.h"
 #include "houdayer_ops.h"
