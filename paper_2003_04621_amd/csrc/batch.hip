@@ -464,8 +464,10 @@ int build_worklist(pt_batch* b, int mcs, uint32_t flags) {
   if (same && b->built_mcs > 0 && mcs > 0) {
     // only the step count differs: the items, their order and the launch
     // shape stay, and the kernels read the count from the launch arguments
-    // in device memory (a captured graph stays valid too)
-    for (FusedArgs& a : b->args) a.nmcs = mcs;
+    // in device memory (a captured graph stays valid too); a job without a
+    // fused plan keeps its zero (its steps and counters run beside the launch)
+    for (FusedArgs& a : b->args)
+      if (a.nmcs > 0) a.nmcs = mcs;
     if (int rc = upload_worklist(b, b->args.data(), b->args.size(), nullptr, 0)) return rc;
     b->built_mcs = mcs;
     return PT_OK;
