@@ -199,6 +199,7 @@ class Job:
         self.walk, self.modes = bool(walk), bool(modes)
         self.gauss = False
         self.N = L ** dim
+        self.hooks = _hooks  # the job frees its memory through these, whatever is set later
         _live_jobs.add(self)
 
     def __del__(self):
