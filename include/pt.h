@@ -258,8 +258,10 @@ int pt_mcs(pt_job *job, int32_t n, uint32_t flags);
 /* pt_mcs that allocates no device memory, for callers that cannot allocate
  * (code under stream capture, tight serving loops, harnesses that forbid
  * hipMalloc).  Same arguments, steps and results as pt_mcs, bit for bit.
- * pt_mcs keeps each job's work list, queue counter and launch state in device
- * memory it allocates on first use; this entry point instead writes them to
+ * pt_mcs keeps each job's work list, queue counter and launch state (and, where
+ * it spreads the samples, see pt_get_plan, what their workgroups meet through)
+ * in device memory it allocates on first use, with hipMalloc and beyond
+ * pt_job_bytes; this entry point instead writes them to
  * a static scratch array of the library (about 1 MiB per GPU, held from the
  * first call on that GPU until the process ends) and needs nothing else (the
  * per-step kernels it takes when no fused plan fits, and the fused steps of

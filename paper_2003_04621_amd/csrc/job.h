@@ -53,14 +53,15 @@ struct pt_job {
   bool fused_ok[5] = {false, false, false, false, false};
   // split-sample plan (samples whose sets do not fit one workgroup; split_ok)
   // and the scratch of split launches: published energies / configurations and
-  // barrier counters (allocated at creation for such samples, for others by
-  // the first pt_mcs that spreads them, split_scratch)
+  // barrier counters (allocated at creation for such samples, for others in
+  // spread_mem by the first pt_mcs that spreads them, split_scratch)
   ptsg::SplitPlan split{};
   bool split_ok = false;
   int32_t* Ex = nullptr;     // [S][2][2NT]
   uint32_t* snap = nullptr;  // [S][2][2NT][2NW]
   uint32_t* bar = nullptr;   // [bar_words(S)] barrier counters and fault word
   uint32_t* hfault = nullptr;  // the fault word's copy in pinned host memory
+  void* spread_mem = nullptr;
   // Gaussian couplings (pt_init_gauss): integer units, 64-bit energies, the
   // per-group coupling data of gauss.h and the inverse temperatures; thr,
   // thrpt, jw and E stay null for such a job
@@ -113,29 +114,38 @@ struct pt_job {
     if (!hfault) hfault = fault_word_take();
     return ptsg::launch_clear_bar(words, g.S, hfault, stream);
   }
-  // Allocates the scratch of split launches if the job has none; false (with
-  // none) if the device has no room.  Waits for the device once: the buffers
-  // may have been in use on another stream than the job's.
+  // The scratch of split launches, if the job has none: launch state like the
+  // work list of pt_mcs, so from hipMalloc and not through the hooks, and cleared
+  // by work queued on the stream (new memory has no earlier user to wait for: a
+  // first pt_mcs beside 83 ms of another stream's work returns in 0.1 ms; with
+  // memory of the hooks and the wait for the device that it needs, 83).  False
+  // (with none) if the device has no room.
   bool split_scratch() {
     if (bar) return true;
-    const size_t per = (size_t)g.S * 2 * g.nslot;
-    void* p[3] = {dalloc(sizeof(int32_t) * per), dalloc(sizeof(uint32_t) * per * 2 * g.NW),
-                  dalloc(sizeof(uint32_t) * ptsg::bar_words(g.S))};
-    if (!p[0] || !p[1] || !p[2] || hipDeviceSynchronize() != hipSuccess ||
-        clear_bar((uint32_t*)p[2]) != hipSuccess || hipStreamSynchronize(stream) != hipSuccess) {
+    const size_t per = (size_t)g.S * 2 * g.nslot, snap_words = per * 2 * g.NW;
+    const size_t words = snap_words + per + ptsg::bar_words(g.S);
+    void* p = nullptr;
+    if (hipMalloc(&p, sizeof(uint32_t) * words) != hipSuccess) {
       (void)hipGetLastError();
-      for (void* q : p)
-        if (q) dfree(q);
       return false;
     }
-    Ex = (int32_t*)p[0];
-    snap = (uint32_t*)p[1];
-    bar = (uint32_t*)p[2];
+    uint32_t* w = (uint32_t*)p;
+    if (clear_bar(w + snap_words + per) != hipSuccess) {
+      (void)hipGetLastError();
+      (void)hipFree(p);
+      return false;
+    }
+    spread_mem = p;
+    snap = w;
+    Ex = (int32_t*)(w + snap_words);
+    bar = w + snap_words + per;
     return true;
   }
   void release() {
     if (hfault) fault_word_give(hfault);
     hfault = nullptr;
+    if (spread_mem) (void)hipFree(spread_mem);
+    spread_mem = nullptr;
     for (void* p : allocs) {
       if (free_fn)
         free_fn(p, alloc_ctx);
