@@ -286,10 +286,14 @@ int pt_set_measure_interval(pt_job *job, int32_t every);
  * sample, -1 per-step kernels), workgroups per sample, configurations per
  * workgroup, and LDS bytes per workgroup (0 for mode -1).  Where a job's
  * samples need fewer workgroups than the GPU has CUs, pt_mcs may spread each
- * over more workgroups than the plan says, with the same results.  A Gaussian job
+ * over more workgroups than the plan says, with the same results
+ * (pt_get_launch tells).  A Gaussian job
  * reports mode 0 for its fused steps (with or without Houdayer moves) and -1
  * for the per-step kernels.  Host only. */
 int pt_get_plan(pt_job *job, uint32_t flags, int32_t *out4);
+/* The form the job's last pt_mcs or pt_mcs_noalloc call took, as pt_get_plan
+ * reports a plan; mode -2 before the first.  Host only. */
+int pt_get_launch(pt_job *job, int32_t *out4);
 
 /* The same report for a job of this shape before it exists (host only, no
  * device call): a plan depends on dim, L and replicas, not on samples, and on

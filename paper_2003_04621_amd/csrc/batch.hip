@@ -682,6 +682,10 @@ int batch_run_job(pt_batch* b, pt_job* job, int mcs, uint32_t flags) {
     b->built = false;
     if (int rc = build_worklist(b, mcs, flags)) return rc;
   }
+  if (b->spread.parts) {
+    const int32_t as[4] = {3, b->spread.parts, b->spread.R, 4 * b->spread.lay.words};
+    std::copy(as, as + 4, job->ran);
+  }
   return run_once(b, false);
 }
 

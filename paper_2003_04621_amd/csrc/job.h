@@ -72,6 +72,8 @@ struct pt_job {
   double* gbeta = nullptr;   // [NT]
   float* gcz = nullptr;      // [NT]
   bool poisoned = false;
+  // the form of the last pt_mcs / pt_mcs_noalloc call (pt_get_launch)
+  int32_t ran[4] = {-2, 0, 0, 0};
   // bumped when device buffers held by launch arguments change (pt_set_layout)
   uint32_t epoch = 0;
   struct pt_batch* self_batch = nullptr;  // one-job batch behind pt_mcs

@@ -691,6 +691,7 @@ int check_mcs(pt_job* job, int32_t n, uint32_t flags) {
 // the separate entry points.
 int mcs_per_step(pt_job* job, int32_t n, uint32_t flags) {
   hipStream_t st = job->stream;
+  plan_report(job, flags | PT_MCS_PLAIN, job->ran);
   const bool hou = flags & PT_MCS_HOUDAYER, meas = flags & PT_MCS_MEASURE;
   const bool multi = flags & PT_MCS_MULTICLUSTER;
   const CounterStep adv{1, 1, hou ? 1u : 0u, meas ? 1u : 0u, (uint32_t)job->meas_every};
@@ -749,6 +750,7 @@ bool gauss_fused_ok(const pt_job* job, uint32_t flags) {
 int mcs_gauss_fused(pt_job* job, int32_t n, uint32_t flags) {
   const bool hou = flags & PT_MCS_HOUDAYER, meas = flags & PT_MCS_MEASURE;
   const int chunk = 500;
+  plan_report(job, flags, job->ran);
   for (int done = 0; done < n; done += chunk) {
     const uint32_t m = (uint32_t)((n - done) < chunk ? (n - done) : chunk);
     PT_HIP(job, launch_gauss_fused(job->g, job->spins, job->gJ, job->E64, job->sot, job->tos,
@@ -774,6 +776,7 @@ PT_API int pt_mcs(pt_job* job, int32_t n, uint32_t flags) {
     if (!job->self_batch) job->self_batch = batch_new(job->stream, true);
     if (!job->self_batch) return pt_fail(PT_ENOMEM, "pt_mcs: host allocation failed");
     const int chunk = 500;
+    plan_report(job, flags, job->ran);
     for (int done = 0; done < n; done += chunk) {
       const int m = (n - done) < chunk ? (n - done) : chunk;
       const int rc = batch_run_job(job->self_batch, job, m,
@@ -794,6 +797,7 @@ PT_API int pt_mcs_noalloc(pt_job* job, int32_t n, uint32_t flags) {
   if (job->gauss || (flags & PT_MCS_PLAIN) || !job_is_resident(job, flags))
     return mcs_per_step(job, n, flags);  // per-step kernels use no scratch
   const int chunk = 500;
+  plan_report(job, flags, job->ran);
   for (int done = 0; done < n; done += chunk) {
     const int m = (n - done) < chunk ? (n - done) : chunk;
     const int rc = batch_run_job_noalloc(job, m, flags & (PT_MCS_HOUDAYER | PT_MCS_MEASURE | PT_MCS_MULTICLUSTER),
@@ -814,6 +818,13 @@ PT_API int pt_get_plan(pt_job* job, uint32_t flags, int32_t* out4) {
   if ((flags & PT_MCS_MULTICLUSTER) && !(flags & PT_MCS_HOUDAYER))
     return pt_fail(PT_EINVAL, "PT_MCS_MULTICLUSTER needs PT_MCS_HOUDAYER");
   plan_report(job, flags, out4);
+  return PT_OK;
+}
+
+PT_API int pt_get_launch(pt_job* job, int32_t* out4) {
+  if (int rc = check_job(job)) return rc;
+  if (!out4) return pt_fail(PT_EINVAL, "null output");
+  std::memcpy(out4, job->ran, sizeof(job->ran));
   return PT_OK;
 }
 

@@ -34,7 +34,7 @@ _CODES = {PT_EINVAL: "PT_EINVAL", PT_ENOMEM: "PT_ENOMEM", PT_EDEVICE: "PT_EDEVIC
 EXPORTS = [
     "pt_init", "pt_init_ex", "pt_sweep", "pt_exchange", "pt_houdayer", "pt_houdayer_multi",
     "pt_measure", "pt_mcs", "pt_mcs_noalloc",
-    "pt_get_plan", "pt_plan_query", "pt_job_bytes", "pt_observables", "pt_destroy", "pt_get_spins", "pt_set_spins",
+    "pt_get_plan", "pt_get_launch", "pt_plan_query", "pt_job_bytes", "pt_observables", "pt_destroy", "pt_get_spins", "pt_set_spins",
     "pt_set_layout", "pt_get_layout", "pt_get_energies",
     "pt_get_maps", "pt_get_counters", "pt_get_moments", "pt_get_walk", "pt_tunnel_summary",
     "pt_get_modes", "pt_correlation_length", "pt_get_stats",
@@ -89,7 +89,7 @@ def lib():
             "pt_init_ex": [C.POINTER(P), I32, I32, I32, I32, P, P, U64, U32],
             "pt_sweep": [P, I32], "pt_exchange": [P], "pt_houdayer": [P], "pt_houdayer_multi": [P],
             "pt_measure": [P],
-            "pt_mcs": [P, I32, U32], "pt_mcs_noalloc": [P, I32, U32], "pt_get_plan": [P, U32, P], "pt_plan_query": [I32, I32, I32, U32, P],
+            "pt_mcs": [P, I32, U32], "pt_mcs_noalloc": [P, I32, U32], "pt_get_plan": [P, U32, P], "pt_get_launch": [P, P], "pt_plan_query": [I32, I32, I32, U32, P],
             "pt_job_bytes": [I32, I32, I32, I32, U32, P, P], "pt_observables": [P, P, P, P], "pt_destroy": [P],
             "pt_get_spins": [P, P], "pt_set_spins": [P, P], "pt_get_energies": [P, P],
             "pt_set_layout": [P, U32], "pt_get_layout": [P, P],
@@ -354,6 +354,14 @@ def pt_get_plan(job: Job, houdayer=False, measure=False, plain=False, multi=Fals
     flags = _step_flags(houdayer, measure, plain, multi)
     out = np.zeros(4, np.int32)
     _check(lib().pt_get_plan(job.h, flags, _p(out)))
+    return dict(mode=int(out[0]), parts=int(out[1]), per_part=int(out[2]), lds_bytes=int(out[3]))
+
+
+def pt_get_launch(job: Job) -> dict:
+    """The form the job's last pt_mcs or pt_mcs_noalloc call took, as
+    pt_get_plan's report (mode -2 before the first)."""
+    out = np.zeros(4, np.int32)
+    _check(lib().pt_get_launch(job.h, _p(out)))
     return dict(mode=int(out[0]), parts=int(out[1]), per_part=int(out[2]), lds_bytes=int(out[3]))
 
 

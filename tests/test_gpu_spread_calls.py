@@ -5,6 +5,7 @@ import pytest
 
 import oracle
 from paper_2003_04621_amd import workloads as W
+from test_gpu_spread import SHAPES
 
 pytestmark = pytest.mark.gpu
 
@@ -70,3 +71,42 @@ def test_first_call_only_enqueues(pt):
     same(pt, job, ref)
     pt.pt_destroy(job)
     pt.pt_destroy(warm)
+
+
+def cus():
+    import torch
+    return torch.cuda.get_device_properties(0).multi_processor_count
+
+
+@pytest.mark.parametrize("d,L,S,NT,layout,walk,modes", SHAPES)
+@pytest.mark.parametrize("meas", [False, True])
+def test_the_shapes_of_the_spread_tests_spread(pt, d, L, S, NT, layout, walk, modes, meas):
+    job, _ = make(pt, d, L, S, NT, layout=layout, walk=walk, modes=modes)
+    assert pt.pt_get_launch(job)["mode"] == -2
+    plan = pt.pt_get_plan(job, measure=meas)
+    pt.pt_mcs(job, 1, measure=meas)
+    ran = pt.pt_get_launch(job)
+    assert ran["mode"] == 3 and ran["parts"] > plan["parts"] and S * ran["parts"] <= cus(), (plan, ran)
+    assert ran["parts"] * ran["per_part"] >= 2 * NT > (ran["parts"] - 1) * ran["per_part"]
+    pt.pt_mcs_noalloc(job, 1, measure=meas)
+    assert pt.pt_get_launch(job) == plan
+    pt.pt_mcs(job, 1, measure=meas, plain=True)
+    assert pt.pt_get_launch(job)["mode"] == -1
+    pt.pt_destroy(job)
+
+
+# just outside the rule: too few attempted flips per step, too few words for two
+# parts, samples on more than half the CUs, Houdayer moves; and just inside it
+@pytest.mark.parametrize("d,L,samples,NT,houdayer,parts", [
+    (3, 8, 8, 31, False, 1), (3, 8, 8, 32, False, 2), (2, 16, 8, 96, False, 1), (2, 64, 4, 4, False, 2), (2, 64, 4, 3, False, 1),
+    (3, 16, "half", 32, False, 2), (3, 16, "more", 32, False, 1), (3, 16, 4, 32, True, 1)])
+def test_where_spreading_begins(pt, d, L, samples, NT, houdayer, parts):
+    S = {"half": cus() // 2, "more": cus() // 2 + 1}.get(samples, samples)
+    job, _ = make(pt, d, L, S, NT)
+    pt.pt_mcs(job, 1, measure=True, houdayer=houdayer)
+    ran, plan = pt.pt_get_launch(job), pt.pt_get_plan(job, measure=True, houdayer=houdayer)
+    if parts == 1:
+        assert ran == plan
+    else:
+        assert ran["parts"] >= parts
+    pt.pt_destroy(job)
