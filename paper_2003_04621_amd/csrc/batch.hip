@@ -25,6 +25,16 @@ struct BatchConfig {
   int order = 0;       // 0: largest items first, 1: job order
 };
 
+// One launch over the uploaded work list: its jobs and items, the LDS of its
+// largest plan, the kinds of work in it (kFeat*) and its grid.
+struct BatchLaunch {
+  int job0 = 0, njobs = 0, item0 = 0, nitems = 0;
+  size_t lds_bytes = 0;
+  int feat = 0;
+  bool has_split = false;
+  int threads = 0, per_cu = 0, blocks = 0;  // per_cu: workgroups resident per CU
+};
+
 struct pt_batch {
   std::vector<pt_job*> jobs;
   int d = 3;
@@ -36,9 +46,8 @@ struct pt_batch {
   BatchItem* d_items = nullptr;
   uint32_t* d_queue = nullptr;
   int cap_jobs = 0, cap_items = 0;
-  int nitems = 0;
-  size_t lds_bytes = 0;
-  int blocks = 0;
+  BatchLaunch own;   // every job in its own plan
+  BatchLaunch wide;  // the spread form beside it (no items: none)
   bool built = false;
   int built_mcs = -1;
   uint32_t built_flags = 0;
@@ -51,10 +60,6 @@ struct pt_batch {
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   bool graph_ok = false;
-  bool has_split = false;  // the work list holds split samples
-  int feat = 0;            // kinds of work in the work list (kFeat*)
-  int threads = 0;         // threads per workgroup of the built launch
-  int per_cu = 0;          // workgroups of that size resident per CU
   // pinned staging of the work list (the upload is then truly asynchronous)
   // and the events ordering its reuse: stage_ev after the last upload from
   // it, last_ev after the last launch reading the device work list
@@ -63,7 +68,7 @@ struct pt_batch {
   hipEvent_t stage_ev = nullptr, last_ev = nullptr;
   std::vector<FusedArgs> args;  // host copy of the uploaded launch arguments
   bool may_spread = false;  // the one-job batch behind pt_mcs (spread_job)
-  SplitPlan spread;         // the built work list's spread plan (parts 0: none)
+  SplitPlan spread;         // the plan of `wide` (parts 0: none)
 };
 
 namespace {
@@ -75,6 +80,11 @@ namespace {
 std::mutex g_split_mu;
 hipEvent_t g_split_ev[64] = {};
 hipStream_t g_split_stream[64] = {};  // of the last such launch
+
+bool under_capture(hipStream_t st) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  return st && (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone);
+}
 
 // Whether a launch holding split samples is in flight on another stream of
 // the current device.
@@ -367,21 +377,50 @@ int upload_worklist(pt_batch* b, const FusedArgs* args, size_t nj, const BatchIt
   return PT_OK;
 }
 
+// The grid of launch L over the jobs' own dimension.
+int shape_launch(pt_batch* b, const HostWorklist& wl, int job0, int item0, BatchLaunch& L) {
+  L = BatchLaunch{};
+  L.job0 = job0;
+  L.njobs = (int)wl.jobs.size();
+  L.item0 = item0;
+  L.nitems = (int)wl.items.size();
+  L.lds_bytes = wl.lds_words * 4;
+  L.feat = wl.feat;
+  L.has_split = wl.has_split;
+  const hipError_t e = prepare_batch(b->d, L.feat, L.lds_bytes, nullptr);
+  if (e != hipSuccess) return pt_fail(PT_EDEVICE, std::string("pt_batch_run: ") + hipGetErrorString(e));
+  if (int rc = launch_shape(b->d, L.feat, L.lds_bytes, L.nitems, b->ncu, b->cfg.threads, &L.threads,
+                            &L.per_cu))
+    return rc;
+  L.blocks = std::max(1, std::min(b->ncu * L.per_cu, L.nitems));
+  return PT_OK;
+}
+
 // Work list for per-job step counts and flags, uploaded to the batch's own
-// device buffers (grown as needed).
+// device buffers (grown as needed); behind it that of the spread form, if
+// b->spread is one, so that each call can take either.
 int build_worklist_ex(pt_batch* b, const std::vector<int>& steps, const std::vector<uint32_t>& jflags) {
   HostWorklist wl;
-  if (int rc = plan_worklist(b->jobs, b->cfg, steps, jflags, wl, b->spread.parts ? &b->spread : nullptr))
-    return rc;
-  const std::vector<FusedArgs>& hj = wl.jobs;
-  const std::vector<BatchItem>& hi = wl.items;
-  const size_t lds_words = wl.lds_words;
-  const int feat = wl.feat;
-  b->has_split = wl.has_split;
+  if (int rc = plan_worklist(b->jobs, b->cfg, steps, jflags, wl)) return rc;
+  std::vector<FusedArgs>& hj = wl.jobs;
+  std::vector<BatchItem>& hi = wl.items;
+  BatchLaunch own, wide;
+  if (int rc = shape_launch(b, wl, 0, 0, own)) return rc;
+  if (b->spread.parts) {
+    HostWorklist ws;
+    if (int rc = plan_worklist(b->jobs, b->cfg, steps, jflags, ws, &b->spread)) return rc;
+    if (shape_launch(b, ws, (int)hj.size(), (int)hi.size(), wide) == PT_OK) {
+      hj.insert(hj.end(), ws.jobs.begin(), ws.jobs.end());
+      hi.insert(hi.end(), ws.items.begin(), ws.items.end());
+    } else {
+      wide = BatchLaunch{};
+    }
+  }
   hipError_t e = hipSuccess;
   if ((int)hj.size() > b->cap_jobs) {
     if (b->d_jobs) (void)hipFree(b->d_jobs);
     b->d_jobs = nullptr;
+    b->cap_jobs = 0;
     e = hipMalloc((void**)&b->d_jobs, sizeof(FusedArgs) * hj.size());
     if (e != hipSuccess) return pt_fail(PT_ENOMEM, "pt_batch_run: device allocation failed");
     b->cap_jobs = (int)hj.size();
@@ -389,6 +428,7 @@ int build_worklist_ex(pt_batch* b, const std::vector<int>& steps, const std::vec
   if ((int)hi.size() > b->cap_items) {
     if (b->d_items) (void)hipFree(b->d_items);
     b->d_items = nullptr;
+    b->cap_items = 0;
     e = hipMalloc((void**)&b->d_items, sizeof(BatchItem) * hi.size());
     if (e != hipSuccess) return pt_fail(PT_ENOMEM, "pt_batch_run: device allocation failed");
     b->cap_items = (int)hi.size();
@@ -406,18 +446,8 @@ int build_worklist_ex(pt_batch* b, const std::vector<int>& steps, const std::vec
   }
   if (int rc = upload_worklist(b, hj.data(), hj.size(), hi.data(), hi.size())) return rc;
   b->args = hj;
-  b->nitems = (int)hi.size();
-  b->lds_bytes = lds_words * 4;
-  b->feat = feat;
-  e = prepare_batch(b->d, feat, b->lds_bytes, nullptr);
-  if (e != hipSuccess) return pt_fail(PT_EDEVICE, std::string("pt_batch_run: ") + hipGetErrorString(e));
-  int threads = 0, per_cu = 0;
-  if (int rc = launch_shape(b->d, feat, b->lds_bytes, b->nitems, b->ncu, b->cfg.threads, &threads,
-                            &per_cu))
-    return rc;
-  b->threads = threads;
-  b->per_cu = per_cu;
-  b->blocks = std::max(1, std::min(b->ncu * per_cu, b->nitems));
+  b->own = own;
+  b->wide = wide;
   b->built = false;
   drop_graph(b);
   return PT_OK;
@@ -476,7 +506,7 @@ int build_worklist(pt_batch* b, int mcs, uint32_t flags) {
   b->built_epoch = epoch;
   const std::vector<int> steps(b->jobs.size(), mcs);
   const std::vector<uint32_t> fl(b->jobs.size(), flags);
-  b->spread = b->may_spread ? spread_job(b->jobs[0], flags, b->ncu) : SplitPlan{};
+  b->spread = b->may_spread && !under_capture(b->stream) ? spread_job(b->jobs[0], flags, b->ncu) : SplitPlan{};
   if (int rc = build_worklist_ex(b, steps, fl)) return rc;
   b->built = true;
   b->built_mcs = mcs;
@@ -485,14 +515,18 @@ int build_worklist(pt_batch* b, int mcs, uint32_t flags) {
   return PT_OK;
 }
 
-int run_once(pt_batch* b, bool use_graph) {
-  if (b->nitems == 0) return PT_OK;
+hipError_t enqueue(pt_batch* b, const BatchLaunch& L, hipStream_t st) {
+  return launch_batch(b->d, L.feat, b->d_jobs + L.job0, L.njobs, b->d_items + L.item0, L.nitems, b->d_queue,
+                      L.blocks, L.threads, L.lds_bytes, st);
+}
+
+// One launch of the built list, in its spread form with `wide`.
+int run_once(pt_batch* b, bool use_graph, bool wide = false) {
+  const BatchLaunch& L = wide ? b->wide : b->own;
+  if (L.nitems == 0) return PT_OK;
   if (!use_graph) {
-    auto launch = [&] {
-      return launch_batch(b->d, b->feat, b->d_jobs, (int)b->jobs.size(), b->d_items, b->nitems,
-                          b->d_queue, b->blocks, b->threads, b->lds_bytes, b->stream);
-    };
-    hipError_t e = b->has_split ? ordered_split_launch(b->stream, launch) : launch();
+    auto launch = [&] { return enqueue(b, L, b->stream); };
+    hipError_t e = L.has_split ? ordered_split_launch(b->stream, launch) : launch();
     if (e == hipSuccess && b->last_ev) e = hipEventRecord(b->last_ev, b->stream);
     if (e != hipSuccess) return pt_fail(PT_EDEVICE, std::string("pt_batch_run: ") + hipGetErrorString(e));
     return PT_OK;
@@ -502,9 +536,7 @@ int run_once(pt_batch* b, bool use_graph) {
     if (!b->cap_stream) e = hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipStreamBeginCapture(b->cap_stream, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
-      const hipError_t el = launch_batch(b->d, b->feat, b->d_jobs, (int)b->jobs.size(), b->d_items,
-                                         b->nitems, b->d_queue, b->blocks, b->threads,
-                                         b->lds_bytes, b->cap_stream);
+      const hipError_t el = enqueue(b, L, b->cap_stream);
       hipGraph_t g = nullptr;
       e = hipStreamEndCapture(b->cap_stream, &g);
       if (e == hipSuccess && el != hipSuccess) e = el;
@@ -522,7 +554,7 @@ int run_once(pt_batch* b, bool use_graph) {
     b->graph_ok = true;
   }
   auto replay = [&] { return hipGraphLaunch(b->exec, b->stream); };
-  hipError_t e = b->has_split ? ordered_split_launch(b->stream, replay) : replay();
+  hipError_t e = L.has_split ? ordered_split_launch(b->stream, replay) : replay();
   if (e == hipSuccess && b->last_ev) e = hipEventRecord(b->last_ev, b->stream);
   if (e != hipSuccess) return pt_fail(PT_EDEVICE, std::string("pt_batch_run: ") + hipGetErrorString(e));
   return PT_OK;
@@ -675,18 +707,22 @@ int batch_run_job(pt_batch* b, pt_job* job, int mcs, uint32_t flags) {
   }
   b->stream = job->stream;
   if (int rc = build_worklist(b, mcs, flags)) return rc;
-  if (b->spread.parts && split_busy_elsewhere(b->stream)) {
+  // a captured launch keeps to the job's own plan: the order among split
+  // launches is kept by an event from outside the capture, and a replay would
+  // not take part in it
+  bool wide = b->wide.nitems && !under_capture(b->stream);
+  if (wide && split_busy_elsewhere(b->stream)) {
     // split launches run one after another: a program that keeps several
     // streams busy runs its jobs side by side, one workgroup per sample
     b->may_spread = false;
-    b->built = false;
-    if (int rc = build_worklist(b, mcs, flags)) return rc;
+    b->wide = BatchLaunch{};
+    wide = false;
   }
-  if (b->spread.parts) {
+  if (wide) {
     const int32_t as[4] = {3, b->spread.parts, b->spread.R, 4 * b->spread.lay.words};
     std::copy(as, as + 4, job->ran);
   }
-  return run_once(b, false);
+  return run_once(b, false, wide);
 }
 
 // ---- the work list in library-held device memory (pt_mcs_noalloc) ---------
@@ -893,7 +929,7 @@ PT_API int pt_batch_run(pt_batch* b, int32_t mcs, uint32_t flags) {
 
 PT_API int pt_batch_get_config(pt_batch* b, int32_t* cfg3) {
   if (!b || !cfg3) return pt_fail(PT_EINVAL, "null argument");
-  cfg3[0] = b->cfg.threads == 0 && b->built ? b->threads : b->cfg.threads;
+  cfg3[0] = b->cfg.threads == 0 && b->built ? b->own.threads : b->cfg.threads;
   cfg3[1] = b->cfg.sets;
   cfg3[2] = b->cfg.order;
   return PT_OK;
@@ -901,9 +937,9 @@ PT_API int pt_batch_get_config(pt_batch* b, int32_t* cfg3) {
 
 PT_API int pt_batch_launch_shape(pt_batch* b, int32_t* out3) {
   if (!b || !out3) return pt_fail(PT_EINVAL, "null argument");
-  out3[0] = b->blocks;
-  out3[1] = b->threads;
-  out3[2] = b->per_cu;
+  out3[0] = b->own.blocks;
+  out3[1] = b->own.threads;
+  out3[2] = b->own.per_cu;
   return PT_OK;
 }
 

@@ -110,3 +110,39 @@ def test_where_spreading_begins(pt, d, L, samples, NT, houdayer, parts):
     else:
         assert ran["parts"] >= parts
     pt.pt_destroy(job)
+
+
+@pytest.mark.parametrize("d,L,S,NT,measure", [(3, 16, 3, 16, True), (2, 64, 2, 12, False)])
+def test_capture_of_a_warmed_up_job(pt, d, L, S, NT, measure):
+    """pt_mcs with its memory in place records into a caller's graph: replayed
+    between the program's own calls, all steps match the oracle."""
+    import torch
+    st = torch.cuda.Stream()
+    job, ref = make(pt, d, L, S, NT)
+    pt.pt_set_stream(job, st)
+    torch.cuda.synchronize()
+    plan = pt.pt_get_plan(job, measure=measure)
+    for n in (2, 3):
+        pt.pt_mcs(job, n, measure=measure)
+    assert pt.pt_get_launch(job)["parts"] > plan["parts"]
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=st):
+        pt.pt_mcs(job, 3, measure=measure)
+    assert pt.pt_get_launch(job) == plan
+    ref.mcs(5, measure=measure)
+    same(pt, job, ref)              # nothing has run yet
+    for _ in range(3):
+        with torch.cuda.stream(st):
+            graph.replay()
+        ref.mcs(3, measure=measure)
+        same(pt, job, ref)
+        pt.pt_mcs(job, 3, measure=measure)
+        assert pt.pt_get_launch(job)["parts"] > plan["parts"]
+        ref.mcs(3, measure=measure)
+        same(pt, job, ref)
+    del graph
+    pt.pt_mcs(job, 2, measure=measure)
+    ref.mcs(2, measure=measure)
+    same(pt, job, ref)
+    pt.pt_destroy(job)
