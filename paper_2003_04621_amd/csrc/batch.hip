@@ -9,6 +9,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <new>
 #include <tuple>
 #include <string>
 #include <vector>
@@ -67,7 +68,9 @@ struct pt_batch {
   size_t stage_cap = 0;
   hipEvent_t stage_ev = nullptr, last_ev = nullptr;
   std::vector<FusedArgs> args;  // host copy of the uploaded launch arguments
+  StreamUse use;            // of a caller's batch
   bool may_spread = false;  // the one-job batch behind pt_mcs (spread_job)
+  bool asked = false;       // spread_job was asked when the list was built
   SplitPlan spread;         // the plan of `wide` (parts 0: none)
 };
 
@@ -79,23 +82,10 @@ namespace {
 // the other one's exit would make room for.
 std::mutex g_split_mu;
 hipEvent_t g_split_ev[64] = {};
-hipStream_t g_split_stream[64] = {};  // of the last such launch
 
 bool under_capture(hipStream_t st) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   return st && (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone);
-}
-
-// Whether a launch holding split samples is in flight on another stream of
-// the current device.
-bool split_busy_elsewhere(hipStream_t st) {
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return false;
-  std::lock_guard<std::mutex> lk(g_split_mu);
-  if (!g_split_ev[dev] || g_split_stream[dev] == st) return false;
-  const hipError_t e = hipEventQuery(g_split_ev[dev]);
-  (void)hipGetLastError();
-  return e == hipErrorNotReady;
 }
 
 template <typename F>
@@ -109,8 +99,17 @@ hipError_t ordered_split_launch(hipStream_t st, F&& launch) {
   if (e == hipSuccess) e = hipStreamWaitEvent(st, g_split_ev[dev], 0);
   if (e == hipSuccess) e = launch();
   if (e == hipSuccess) e = hipEventRecord(g_split_ev[dev], st);
-  g_split_stream[dev] = st;
   return e;
+}
+
+// Streams held per device, each with its holders.
+struct HeldStreams {
+  std::mutex mu;
+  std::map<hipStream_t, int> dev[64];
+};
+HeldStreams& held_streams() {
+  static HeldStreams* h = new HeldStreams;  // kept: jobs may outlive static objects
+  return *h;
 }
 
 bool same_cfg(const BatchConfig& a, const BatchConfig& b) {
@@ -140,6 +139,40 @@ int job_mode(const pt_job* j, uint32_t flags, const BatchConfig& cfg) {
 }
 
 }  // namespace
+
+void StreamUse::hold(hipStream_t st) {
+  drop();
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) {
+    (void)hipGetLastError();
+    return;
+  }
+  HeldStreams& h = held_streams();
+  std::lock_guard<std::mutex> lk(h.mu);
+  try {
+    ++h.dev[dev][st];
+  } catch (const std::bad_alloc&) {
+    return;  // not held: never alone
+  }
+  dev_ = dev;
+  st_ = st;
+}
+
+void StreamUse::drop() {
+  if (dev_ < 0) return;
+  HeldStreams& h = held_streams();
+  std::lock_guard<std::mutex> lk(h.mu);
+  const auto it = h.dev[dev_].find(st_);
+  if (--it->second == 0) h.dev[dev_].erase(it);
+  dev_ = -1;
+}
+
+bool StreamUse::alone() const {
+  if (dev_ < 0) return false;
+  HeldStreams& h = held_streams();
+  std::lock_guard<std::mutex> lk(h.mu);
+  return h.dev[dev_].size() <= 1;
+}
 
 // The launch arguments of job j for `mcs` fused steps in plan `mode` (3: the
 // split plan `split`).
@@ -460,8 +493,12 @@ int build_worklist_ex(pt_batch* b, const std::vector<int>& steps, const std::vec
 // kSpreadFlips attempted flips per step and a sample four times that, so that
 // the sweep saved outweighs the meeting (about 3 us) and the scratch; at least
 // twice the parts the plan has, or with a plan that is split already (and
-// meets anyway) more of them; not where another stream's split launch is in
-// flight.  Measured steps, the plan's workgroups against the spread (us): 3D
+// meets anyway) more of them; and only while the library's live jobs and
+// batches on the device share one stream: the spread form takes up to every CU
+// at more machine time per step, and where the GPU is shared the jobs are better
+// left side by side, one workgroup per sample (3D L = 16, N_T = 32, 1500 steps of
+// 2 jobs of 100 samples on two streams 56 ms so, 61 spread; 4 jobs of 60: 56 and
+// 63).  Measured steps, the plan's workgroups against the spread (us): 3D
 // L = 16, 16 x 2 x 32: 36.0 / 10.3; 100 x 2 x 32: 36.2 / 23.8; L = 20, 17 x 2 x
 // 25: 76 / 14.7; L = 48, 5 x 2 x 20: 135 / 22.9; 2D L = 64, 8 x 2 x 24: 24.7 /
 // 9.6; at the line, 3D L = 8, 8 x 2 x 32: 10.8 / 9.3.
@@ -488,7 +525,8 @@ int build_worklist(pt_batch* b, int mcs, uint32_t flags) {
     every[i] = b->jobs[i]->meas_every;
     epoch[i] = b->jobs[i]->epoch;
   }
-  const bool same = b->built && b->built_flags == flags && same_cfg(b->built_cfg, b->cfg) &&
+  const bool ask = b->may_spread && b->jobs[0]->use.alone() && !under_capture(b->stream);
+  const bool same = b->built && (b->asked || !ask) && b->built_flags == flags && same_cfg(b->built_cfg, b->cfg) &&
                     b->built_every == every && b->built_epoch == epoch;
   if (same && b->built_mcs == mcs) return PT_OK;
   if (same && b->built_mcs > 0 && mcs > 0) {
@@ -506,7 +544,8 @@ int build_worklist(pt_batch* b, int mcs, uint32_t flags) {
   b->built_epoch = epoch;
   const std::vector<int> steps(b->jobs.size(), mcs);
   const std::vector<uint32_t> fl(b->jobs.size(), flags);
-  b->spread = b->may_spread && !under_capture(b->stream) ? spread_job(b->jobs[0], flags, b->ncu) : SplitPlan{};
+  b->spread = ask ? spread_job(b->jobs[0], flags, b->ncu) : SplitPlan{};
+  b->asked = ask;
   if (int rc = build_worklist_ex(b, steps, fl)) return rc;
   b->built = true;
   b->built_mcs = mcs;
@@ -710,14 +749,7 @@ int batch_run_job(pt_batch* b, pt_job* job, int mcs, uint32_t flags) {
   // a captured launch keeps to the job's own plan: the order among split
   // launches is kept by an event from outside the capture, and a replay would
   // not take part in it
-  bool wide = b->wide.nitems && !under_capture(b->stream);
-  if (wide && split_busy_elsewhere(b->stream)) {
-    // split launches run one after another: a program that keeps several
-    // streams busy runs its jobs side by side, one workgroup per sample
-    b->may_spread = false;
-    b->wide = BatchLaunch{};
-    wide = false;
-  }
+  const bool wide = b->wide.nitems && job->use.alone() && !under_capture(b->stream);
   if (wide) {
     const int32_t as[4] = {3, b->spread.parts, b->spread.R, 4 * b->spread.lay.words};
     std::copy(as, as + 4, job->ran);
@@ -866,6 +898,7 @@ PT_API int pt_batch_create(pt_job* const* jobs, int32_t n, pt_batch** out) {
   b->jobs.assign(jobs, jobs + n);
   b->d = d;
   b->stream = jobs[0]->stream;
+  b->use.hold(b->stream);
   int dev = 0, ncu = 0;
   if (hipGetDevice(&dev) == hipSuccess &&
       hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && ncu > 0)
@@ -878,6 +911,7 @@ PT_API int pt_batch_create(pt_job* const* jobs, int32_t n, pt_batch** out) {
 PT_API int pt_batch_set_stream(pt_batch* b, void* hip_stream) {
   if (!b) return pt_fail(PT_EINVAL, "null batch");
   b->stream = (hipStream_t)hip_stream;
+  b->use.hold(b->stream);
   drop_graph(b);
   return PT_OK;
 }

@@ -18,11 +18,29 @@ const char* pt_error_text();
 uint32_t* fault_word_take();
 void fault_word_give(uint32_t* w);
 
+// The stream that a live job or batch enqueues on, counted per device so that a
+// job can tell whether the library's work on its device has one stream.
+class StreamUse {
+ public:
+  StreamUse() = default;
+  StreamUse(const StreamUse&) = delete;
+  StreamUse& operator=(const StreamUse&) = delete;
+  ~StreamUse() { drop(); }
+  void hold(hipStream_t st);  // instead of the one held before
+  void drop();
+  bool alone() const;  // no other stream of the device is held
+
+ private:
+  int dev_ = -1;
+  hipStream_t st_ = nullptr;
+};
+
 // One job: S samples x 2 replica sets x N_T temperatures.  Pointers are device
 // memory allocated through the hooks captured at creation.
 struct pt_job {
   ptsg::Geo g{};
   hipStream_t stream = nullptr;
+  StreamUse use;             // of `stream`
   void* spins = nullptr;     // int8 [S][2NT][N] or u32 [S][2NT][2][NW]
   uint32_t* jw = nullptr;    // [S][2][2d][NW]
   int32_t* E = nullptr;      // [S][2NT]

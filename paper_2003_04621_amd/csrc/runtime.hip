@@ -317,6 +317,7 @@ int job_create(pt_job** out, int32_t samples, int32_t replicas, int32_t L, int32
   job->free_fn = free_;
   job->alloc_ctx = ctx;
   job->stream = stream;
+  job->use.hold(stream);
   job->track_walk = (flags & PT_TRACK_WALK) != 0;
   job->track_modes = (flags & PT_TRACK_MODES) != 0;
   job->track_stats = (flags & PT_TRACK_STATS) != 0;
@@ -482,6 +483,7 @@ PT_API int pt_init_gauss(pt_job** out, int32_t samples, int32_t replicas, int32_
   job->free_fn = g_free;
   job->alloc_ctx = g_ctx;
   job->gauss = true;
+  job->use.hold(job->stream);
   job->g = make_geo(samples, replicas, L, dim, (int)flags, seed);
   const Geo& g = job->g;
   const size_t maps = sizeof(int32_t) * (size_t)samples * 2 * replicas;
@@ -598,6 +600,7 @@ PT_API int pt_set_measure_interval(pt_job* job, int32_t every) {
 PT_API int pt_set_stream(pt_job* job, void* hip_stream) {
   if (int rc = check_job(job)) return rc;
   job->stream = (hipStream_t)hip_stream;
+  job->use.hold(job->stream);
   return PT_OK;
 }
 

@@ -1,5 +1,7 @@
 """What a pt_mcs call that spreads a job's few samples over more workgroups does
 besides its steps: memory, waiting, capture and other streams."""
+import gc
+
 import numpy as np
 import pytest
 
@@ -17,6 +19,11 @@ def pt():
     from paper_2003_04621_amd import pt as _pt
     _pt.lib()
     return _pt
+
+
+@pytest.fixture(autouse=True)
+def no_other_jobs():
+    gc.collect()                            # those that earlier tests dropped
 
 
 def make(pt, d, L, S, NT, seed=600, **kw):
@@ -43,6 +50,7 @@ def test_first_call_only_enqueues(pt):
     warm, _ = make(pt, 3, 16, 3, 16)        # code and per-process memory in place
     pt.pt_mcs(warm, 1, measure=True)
     pt.pt_get_energies(warm)
+    pt.pt_destroy(warm)
     sizes = []
 
     def alloc(n, ctx):
@@ -69,8 +77,8 @@ def test_first_call_only_enqueues(pt):
     assert sum(sizes) == held
     ref.mcs(4, measure=True)
     same(pt, job, ref)
+    assert pt.pt_get_launch(job)["parts"] > 1
     pt.pt_destroy(job)
-    pt.pt_destroy(warm)
 
 
 def cus():
@@ -146,3 +154,61 @@ def test_capture_of_a_warmed_up_job(pt, d, L, S, NT, measure):
     ref.mcs(2, measure=measure)
     same(pt, job, ref)
     pt.pt_destroy(job)
+
+
+def test_streams_side_by_side_keep_to_the_plan(pt):
+    """Jobs spread only while the process's jobs and batches share one stream;
+    each call decides anew, whatever ran before."""
+    import torch
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    job, ref = make(pt, 3, 16, 3, 16)
+    plan = pt.pt_get_plan(job, measure=True)
+
+    def step(spread):
+        pt.pt_mcs(job, 2, measure=True)
+        ref.mcs(2, measure=True)
+        ran = pt.pt_get_launch(job)
+        assert ran["parts"] > plan["parts"] if spread else ran == plan
+
+    pt.pt_set_stream(job, a)
+    torch.cuda.synchronize()
+    step(True)
+    other, oref = make(pt, 3, 16, 2, 16, seed=9)
+    pt.pt_set_stream(other, b)
+    torch.cuda.synchronize()
+    for _ in range(3):                      # side by side
+        step(False)
+        pt.pt_mcs(other, 3, measure=True)
+        oref.mcs(3, measure=True)
+        assert pt.pt_get_launch(other) == plan
+    torch.cuda.synchronize()
+    pt.pt_set_stream(other, a)              # one stream for both
+    step(True)
+    pt.pt_mcs(other, 3, measure=True)
+    oref.mcs(3, measure=True)
+    assert pt.pt_get_launch(other)["parts"] > 1
+    batch = pt.pt_batch_create([other])
+    step(True)
+    assert pt.lib().pt_batch_set_stream(batch.h, b.cuda_stream) == pt.PT_OK
+    torch.cuda.synchronize()
+    step(False)
+    pt.pt_batch_run(batch, 2, measure=True)
+    oref.mcs(2, measure=True)
+    torch.cuda.synchronize()
+    pt.pt_batch_destroy(batch)
+    step(True)
+    same(pt, other, oref)
+    pt.pt_destroy(other)
+    # a job that began beside another stream's spreads once that is gone
+    late, lref = make(pt, 3, 16, 3, 16, seed=11)
+    pt.pt_set_stream(late, b)
+    torch.cuda.synchronize()
+    pt.pt_mcs(late, 2, measure=True)
+    assert pt.pt_get_launch(late) == plan
+    same(pt, job, ref)
+    pt.pt_destroy(job)
+    pt.pt_mcs(late, 2, measure=True)
+    assert pt.pt_get_launch(late)["parts"] > 1
+    lref.mcs(4, measure=True)
+    same(pt, late, lref)
+    pt.pt_destroy(late)
