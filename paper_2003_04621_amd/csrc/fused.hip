@@ -70,6 +70,13 @@ bool fused_plan(const Geo& g, bool hou, int nsets, int waves, FusedLayout& lay, 
     const size_t base = (off + 1) / 2 * 2;
     int pc = waves < g.NT ? waves : g.NT;
     while (pc > 1 && base + pc * per > budget) --pc;
+    // Not with a single area: its wavefront would take every pair of the sample,
+    // where the per-step kernels give each a workgroup.  Fused / per step (us),
+    // one area: 2D L = 64, 8 x 2 x 122 2239 / 111, 768 samples 6510 / 1900; 3D
+    // L = 24, 8 x 2 x 18 2153 / 82, 768 samples 6290 / 1673.  With two or more the
+    // form with many samples is fused: 3D L = 4, 256 x 2 x 440 1317 / 1388, 2D
+    // L = 16, 256 x 2 x 500 970 / 1708.
+    if (pc < 2) return false;
     lay.PC = pc;
     lay.Qs = take(pc * per, 2);
   } else if (hou && nsets == 2) {
