@@ -288,9 +288,12 @@ int pt_set_measure_interval(pt_job *job, int32_t every);
  * samples need fewer workgroups than the GPU has CUs, pt_mcs may spread each
  * over more workgroups than the plan says, with the same results
  * (pt_get_launch tells): up to every CU of the GPU, while all live jobs and
- * batches of the process on it share one stream and that is not under capture.
- * pt_mcs_noalloc and batches keep to the plan.  A Gaussian job reports mode 0 for its fused steps (with or without Houdayer moves) and -1
- * for the per-step kernels.  Host only. */
+ * batches of the process on it share one stream and that is not under capture;
+ * pt_mcs_noalloc and batches do not.  Houdayer steps of fewer than 48 samples of
+ * the longest ladders that a workgroup holds run through the per-step kernels
+ * instead (pt_mcs and pt_mcs_noalloc).  A Gaussian job reports mode 0 for its
+ * fused steps (with or without Houdayer moves) and -1 for the per-step kernels.
+ * Host only. */
 int pt_get_plan(pt_job *job, uint32_t flags, int32_t *out4);
 /* The form the job's last pt_mcs or pt_mcs_noalloc call took, as pt_get_plan
  * reports a plan; mode -2 before the first.  Host only. */

@@ -767,10 +767,27 @@ int mcs_gauss_fused(pt_job* job, int32_t n, uint32_t flags) {
   }
   return PT_OK;
 }
+
+// Single-cluster Houdayer steps of the longest ladders, few samples: through the
+// per-step kernels, which give each pair a workgroup, although a workgroup holds
+// the sample (only since the cluster needs no LDS words: 2 per configuration word
+// and wavefront, 16 wavefronts).  Fused / per step (us): 3D L = 16, N_T = 126: 1
+// sample 217 / 75, 16 samples 219 / 112, 64 219 / 199, 256 237 / 459; 3D L = 4,
+// N_T = 445: 321 / 170, 328 / 295, 331 / 470, 334 / 1004; 2D L = 62, N_T = 130:
+// 260 / 105, 263 / 154, 270 / 274, 316 / 647.
+bool long_ladder_per_step(const pt_job* job, uint32_t flags) {
+  constexpr int kSamples = 48;
+  const Geo& g = job->g;
+  if (job->gauss || !(flags & PT_MCS_HOUDAYER) || (flags & PT_MCS_MULTICLUSTER) || g.S >= kSamples ||
+      !job->fused_ok[1] || job->plan[1].PC || (g.d == 2 && g.L == 64))
+    return false;
+  return job->plan[1].words + 16 * 4 * g.NW > (160 * 1024 - 512) / 4;
+}
 }  // namespace
 
 PT_API int pt_mcs(pt_job* job, int32_t n, uint32_t flags) {
   if (int rc = check_mcs(job, n, flags)) return rc;
+  if (long_ladder_per_step(job, flags)) return mcs_per_step(job, n, flags);
   if (gauss_fused_ok(job, flags)) return mcs_gauss_fused(job, n, flags);
   // fused through the job's one-job batch whenever a workgroup plan exists:
   // both sets per workgroup, one set per workgroup (no overlap needed), or
@@ -797,7 +814,7 @@ PT_API int pt_mcs(pt_job* job, int32_t n, uint32_t flags) {
 PT_API int pt_mcs_noalloc(pt_job* job, int32_t n, uint32_t flags) {
   if (int rc = check_mcs(job, n, flags)) return rc;
   if (gauss_fused_ok(job, flags)) return mcs_gauss_fused(job, n, flags);
-  if (job->gauss || (flags & PT_MCS_PLAIN) || !job_is_resident(job, flags))
+  if (job->gauss || (flags & PT_MCS_PLAIN) || !job_is_resident(job, flags) || long_ladder_per_step(job, flags))
     return mcs_per_step(job, n, flags);  // per-step kernels use no scratch
   const int chunk = 500;
   plan_report(job, flags, job->ran);
