@@ -202,15 +202,18 @@ hipError_t launch_energy(const Geo& g, const void* spins, const uint32_t* jw, in
 
 // ---------------------------------------------------------------------------
 // replica exchange, then the replica-walk bookkeeping if the job keeps it
-// (walk not null).  Ladders of up to 64 temperatures: a workgroup of two
-// wavefronts per sample decides every (set, k, carried position) at once and
-// follows the chain by ballots; bound by the latency of its few dependent
-// loads (24 samples x 20 temperatures: 8.5 us with the launch, where one lane
-// per set walking the pass through global memory took 11.5).  Longer ladders
-// take that serial form: the chain of the other holds a set's positions in the
-// lanes of one wavefront.
+// (walk not null).  Ladders of up to 64 temperatures: a workgroup per sample
+// decides every (set, k, carried position) at once and follows the chain by
+// ballots; bound by the latency of its dependent loads, a threshold per row of
+// decisions, so eight wavefronts share the rows.  Calls back to back, one lane per
+// set walking the pass through global memory / two wavefronts / eight (us): 3
+// samples x 32 temperatures 14.7 / 10.4 / 7.1, x 33 15.0 / 17.8 / 8.8, 1 x 64
+// 24.2 / 28.9 / 11.2, 1000 x 64 65 / 30 / 15.5 (sixteen: 16.5).  Longer ladders take
+// the first form: the chain of the other holds a set's positions in the lanes of
+// one wavefront.
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(128) k_exchange_rows(Geo g, const int32_t* __restrict__ E,
+constexpr int kExchangeThreads = 512;
+__global__ void __launch_bounds__(kExchangeThreads) k_exchange_rows(Geo g, const int32_t* __restrict__ E,
                                                        int32_t* __restrict__ sot,
                                                        int32_t* __restrict__ tos,
                                                        const uint32_t* __restrict__ thrpt, int M,
@@ -222,8 +225,8 @@ __global__ void __launch_bounds__(128) k_exchange_rows(Geo g, const int32_t* __r
   __shared__ int32_t El[2 * kMax], m0[2 * kMax], so[2 * kMax], to[2 * kMax];
   __shared__ uint32_t rpt[2 * kMax], acc[2 * (kMax - 1) * 2];
   const uint32_t u = load_counter(&ctr->u);
-  const int s = blockIdx.x, NT = g.NT, NS = 2 * NT, tid = threadIdx.x;
-  for (int i = tid; i < NS; i += 128) {
+  const int s = blockIdx.x, NT = g.NT, NS = 2 * NT, tid = threadIdx.x, T = kExchangeThreads;
+  for (int i = tid; i < NS; i += T) {
     El[i] = E[(size_t)s * NS + i];
     m0[i] = sot[(size_t)s * NS + i];
     const int c = i >= NT ? 1 : 0, k = i - c * NT;
@@ -240,7 +243,7 @@ __global__ void __launch_bounds__(128) k_exchange_rows(Geo g, const int32_t* __r
   exchange_chain<true>(NT, 0, 2, so, to, m0, acc, walk ? walk + (size_t)s * 2 * NS : nullptr,
                        walk ? trips + (size_t)s * 32 * 3 : nullptr, u + 1u);
   __syncthreads();
-  for (int i = tid; i < NS; i += 128) {
+  for (int i = tid; i < NS; i += T) {
     sot[(size_t)s * NS + i] = so[i];
     tos[(size_t)s * NS + i] = to[i];
     // an accepting step puts the configuration from above at k
@@ -305,8 +308,8 @@ hipError_t launch_exchange(const Geo& g, const int32_t* E, int32_t* sot, int32_t
                            DevCounters* ctr, int64_t* stats, hipStream_t st, uint32_t dt,
                            uint32_t dv) {
   if (g.NT <= 64) {
-    hipLaunchKernelGGL(k_exchange_rows, dim3((unsigned)g.S), dim3(128), 0, st, g, E, sot, tos, thrpt, M,
-                       walk, trips, ctr, stats, dt, dv);
+    hipLaunchKernelGGL(k_exchange_rows, dim3((unsigned)g.S), dim3(kExchangeThreads), 0, st, g, E, sot, tos,
+                       thrpt, M, walk, trips, ctr, stats, dt, dv);
   } else {
     const long lanes = (long)g.S * 2;
     hipLaunchKernelGGL(k_exchange, dim3((unsigned)((lanes + 255) / 256)), dim3(256), 0, st, g, E, sot,
