@@ -288,7 +288,8 @@ int pt_set_measure_interval(pt_job *job, int32_t every);
  * samples need fewer workgroups than the GPU has CUs, pt_mcs may spread each
  * over more workgroups than the plan says, with the same results
  * (pt_get_launch tells): up to every CU of the GPU, while all live jobs and
- * batches of the process on it share one stream and that is not under capture;
+ * batches of the process on it share one stream and that is not under capture,
+ * in calls of enough steps for it to be the faster form;
  * pt_mcs_noalloc and batches do not.  Houdayer steps of fewer than 48 samples of
  * the longest ladders that a workgroup holds run through the per-step kernels
  * instead (pt_mcs and pt_mcs_noalloc).  A Gaussian job reports mode 0 for its

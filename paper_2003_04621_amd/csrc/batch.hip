@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <map>
@@ -34,6 +35,13 @@ struct BatchLaunch {
   int feat = 0;
   bool has_split = false;
   int threads = 0, per_cu = 0, blocks = 0;  // per_cu: workgroups resident per CU
+};
+
+// A finer split of one job's samples (parts 0: none) and the least steps of a
+// call from which it is the faster form.
+struct SpreadRule {
+  SplitPlan plan;
+  int from = 1;
 };
 
 struct pt_batch {
@@ -69,8 +77,9 @@ struct pt_batch {
   hipEvent_t stage_ev = nullptr, last_ev = nullptr;
   std::vector<FusedArgs> args;  // host copy of the uploaded launch arguments
   StreamUse use;            // of a caller's batch
-  bool may_spread = false;  // the one-job batch behind pt_mcs (spread_job)
-  bool asked = false;       // spread_job was asked when the list was built
+  bool may_spread = false;  // the one-job batch behind pt_mcs (spread_rule)
+  SpreadRule rule;          // for the flags of the built list
+  bool asked = false;       // a call that spreads had the list built
   SplitPlan spread;         // the plan of `wide` (parts 0: none)
 };
 
@@ -449,33 +458,32 @@ int build_worklist_ex(pt_batch* b, const std::vector<int>& steps, const std::vec
       wide = BatchLaunch{};
     }
   }
-  hipError_t e = hipSuccess;
-  if ((int)hj.size() > b->cap_jobs) {
-    if (b->d_jobs) (void)hipFree(b->d_jobs);
-    b->d_jobs = nullptr;
-    b->cap_jobs = 0;
-    e = hipMalloc((void**)&b->d_jobs, sizeof(FusedArgs) * hj.size());
+  if ((int)hj.size() > b->cap_jobs || (int)hi.size() > b->cap_items) {
+    // queue counters, launch arguments and items in one piece; for a job that may
+    // spread, room for that form from the start (at most a workgroup per CU
+    // beside its own), since growing waits for the device
+    int cj = std::max(b->cap_jobs, (int)hj.size()), ci = std::max(b->cap_items, (int)hi.size());
+    if (b->may_spread) {
+      cj = std::max(cj, 2);
+      ci = std::max(ci, (int)hi.size() + b->ncu);
+    }
+    const size_t items_at = (kQueueBytes + sizeof(FusedArgs) * cj + 255) / 256 * 256;
+    if (b->d_queue) (void)hipFree(b->d_queue);
+    b->d_queue = nullptr;
+    b->cap_jobs = b->cap_items = 0;
+    char* mem = nullptr;
+    hipError_t e = hipMalloc((void**)&mem, items_at + sizeof(BatchItem) * ci);
     if (e != hipSuccess) return pt_fail(PT_ENOMEM, "pt_batch_run: device allocation failed");
-    b->cap_jobs = (int)hj.size();
-  }
-  if ((int)hi.size() > b->cap_items) {
-    if (b->d_items) (void)hipFree(b->d_items);
-    b->d_items = nullptr;
-    b->cap_items = 0;
-    e = hipMalloc((void**)&b->d_items, sizeof(BatchItem) * hi.size());
-    if (e != hipSuccess) return pt_fail(PT_ENOMEM, "pt_batch_run: device allocation failed");
-    b->cap_items = (int)hi.size();
-  }
-  if (!b->d_queue) {
-    uint32_t* q = nullptr;
-    e = hipMalloc((void**)&q, kQueueBytes);
-    if (e != hipSuccess) return pt_fail(PT_ENOMEM, "pt_batch_run: device allocation failed");
-    e = launch_clear_queue(q, b->stream);
+    e = launch_clear_queue(reinterpret_cast<uint32_t*>(mem), b->stream);
     if (e != hipSuccess) {
-      (void)hipFree(q);
+      (void)hipFree(mem);
       return pt_fail(PT_EDEVICE, std::string("pt_batch_run: ") + hipGetErrorString(e));
     }
-    b->d_queue = q;
+    b->d_queue = reinterpret_cast<uint32_t*>(mem);
+    b->d_jobs = reinterpret_cast<FusedArgs*>(mem + kQueueBytes);
+    b->d_items = reinterpret_cast<BatchItem*>(mem + items_at);
+    b->cap_jobs = cj;
+    b->cap_items = ci;
   }
   if (int rc = upload_worklist(b, hj.data(), hj.size(), hi.data(), hi.size())) return rc;
   b->args = hj;
@@ -502,9 +510,18 @@ int build_worklist_ex(pt_batch* b, const std::vector<int>& steps, const std::vec
 // L = 16, 16 x 2 x 32: 36.0 / 10.3; 100 x 2 x 32: 36.2 / 23.8; L = 20, 17 x 2 x
 // 25: 76 / 14.7; L = 48, 5 x 2 x 20: 135 / 22.9; 2D L = 64, 8 x 2 x 24: 24.7 /
 // 9.6; at the line, 3D L = 8, 8 x 2 x 32: 10.8 / 9.3.
+//
+// A call pays for the spread form once (more workgroups to start, in a measuring
+// call also the parts' moments brought together) and gains per step the flips
+// that a workgroup no longer makes, less a meeting of all of them; in flips of one
+// workgroup (0.125 ns each) fitted to 28 shapes of 3D L = 8 to 48 and 2D L = 28 to
+// 64, calls of 1 to 40 steps.  Measured calls of 1 / 4 / 40 steps, own plan against spread
+// (us): 2D L = 32, 60 x 2 x 24: 23.2 / 34.6, 52.6 / 61.0, 408 / 387; 3D L = 8, 100 x
+// 2 x 32: 24.3 / 35.6, 53.8 / 65.4, 413 / 427; 3D L = 24, 60 x 2 x 8: 48.3 / 42.1,
+// 147 / 83, 1331 / 575.
 constexpr double kSpreadFlips = 8192;
-SplitPlan spread_job(pt_job* j, uint32_t flags, int ncu) {
-  SplitPlan none, plan;
+SpreadRule spread_rule(const pt_job* j, uint32_t flags, int ncu) {
+  SpreadRule none, r;
   if (flags & PT_MCS_HOUDAYER) return none;
   const Geo& g = j->g;
   const int mode = job_mode(j, flags, BatchConfig{});
@@ -513,9 +530,22 @@ SplitPlan spread_job(pt_job* j, uint32_t flags, int ncu) {
   const int has = mode == 3 ? j->split.parts : mode == 2 ? 2 : 1;
   const int p = std::min({ncu / g.S, kMaxParts, g.nslot, g.NW / 4, (int)std::min(flips / kSpreadFlips, 1e6)});
   if (p < (mode == 3 ? has + 1 : 2 * has)) return none;
-  if (!split_plan(g, plan, j->track_walk, j->track_modes, p) || plan.parts <= has || !j->split_scratch())
-    return none;
-  return plan;
+  if (!split_plan(g, r.plan, j->track_walk, j->track_modes, p) || r.plan.parts <= has) return none;
+  const int parts = r.plan.parts;
+  const double gain = flips * (1.0 / has - 1.0 / parts) - (16000 + 25.0 * g.S * parts);
+  const double once = flags & PT_MCS_MEASURE ? 60000 + 3500.0 * parts : 36000 + 2500.0 * parts;
+  if (gain <= 0) return none;
+  r.from = (int)std::min(std::ceil(once / gain), 1e9);
+  return r;
+}
+
+// Whether a call of mcs steps takes the spread form (with the rule for its
+// flags in b->rule).  A captured launch keeps to the job's own plan: the order
+// among split launches is kept by an event from outside the capture, and a
+// replay would not take part in it.
+bool spreads(const pt_batch* b, int mcs) {
+  return b->may_spread && b->rule.plan.parts && mcs >= b->rule.from && b->jobs[0]->use.alone() &&
+         !under_capture(b->stream);
 }
 
 int build_worklist(pt_batch* b, int mcs, uint32_t flags) {
@@ -525,9 +555,11 @@ int build_worklist(pt_batch* b, int mcs, uint32_t flags) {
     every[i] = b->jobs[i]->meas_every;
     epoch[i] = b->jobs[i]->epoch;
   }
-  const bool ask = b->may_spread && b->jobs[0]->use.alone() && !under_capture(b->stream);
-  const bool same = b->built && (b->asked || !ask) && b->built_flags == flags && same_cfg(b->built_cfg, b->cfg) &&
-                    b->built_every == every && b->built_epoch == epoch;
+  bool same = b->built && b->built_flags == flags && same_cfg(b->built_cfg, b->cfg) &&
+              b->built_every == every && b->built_epoch == epoch;
+  if (!same && b->may_spread) b->rule = spread_rule(b->jobs[0], flags, b->ncu);
+  const bool ask = spreads(b, mcs);
+  if (ask && !b->asked) same = false;
   if (same && b->built_mcs == mcs) return PT_OK;
   if (same && b->built_mcs > 0 && mcs > 0) {
     // only the step count differs: the items, their order and the launch
@@ -544,7 +576,7 @@ int build_worklist(pt_batch* b, int mcs, uint32_t flags) {
   b->built_epoch = epoch;
   const std::vector<int> steps(b->jobs.size(), mcs);
   const std::vector<uint32_t> fl(b->jobs.size(), flags);
-  b->spread = ask ? spread_job(b->jobs[0], flags, b->ncu) : SplitPlan{};
+  b->spread = ask && b->jobs[0]->split_scratch() ? b->rule.plan : SplitPlan{};
   b->asked = ask;
   if (int rc = build_worklist_ex(b, steps, fl)) return rc;
   b->built = true;
@@ -746,10 +778,7 @@ int batch_run_job(pt_batch* b, pt_job* job, int mcs, uint32_t flags) {
   }
   b->stream = job->stream;
   if (int rc = build_worklist(b, mcs, flags)) return rc;
-  // a captured launch keeps to the job's own plan: the order among split
-  // launches is kept by an event from outside the capture, and a replay would
-  // not take part in it
-  const bool wide = b->wide.nitems && job->use.alone() && !under_capture(b->stream);
+  const bool wide = b->wide.nitems && spreads(b, mcs);
   if (wide) {
     const int32_t as[4] = {3, b->spread.parts, b->spread.R, 4 * b->spread.lay.words};
     std::copy(as, as + 4, job->ran);
@@ -866,9 +895,7 @@ void batch_free(pt_batch* b) {
   if (!b) return;
   drop_graph(b);
   if (b->cap_stream) (void)hipStreamDestroy(b->cap_stream);
-  if (b->d_jobs) (void)hipFree(b->d_jobs);
-  if (b->d_items) (void)hipFree(b->d_items);
-  if (b->d_queue) (void)hipFree(b->d_queue);
+  if (b->d_queue) (void)hipFree(b->d_queue);  // and the arguments and items behind it
   if (b->stage_ev) (void)hipEventSynchronize(b->stage_ev);
   if (b->h_stage) (void)hipHostFree(b->h_stage);
   if (b->stage_ev) (void)hipEventDestroy(b->stage_ev);

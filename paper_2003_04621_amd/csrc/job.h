@@ -142,23 +142,23 @@ struct pt_job {
   // (with none) if the device has no room.
   bool split_scratch() {
     if (bar) return true;
-    const size_t per = (size_t)g.S * 2 * g.nslot, snap_words = per * 2 * g.NW;
-    const size_t words = snap_words + per + ptsg::bar_words(g.S);
+    const size_t per = (size_t)g.S * 2 * g.nslot;
+    const size_t Ex_at = (per * 2 * g.NW + 63) / 64 * 64, bar_at = Ex_at + (per + 63) / 64 * 64;
     void* p = nullptr;
-    if (hipMalloc(&p, sizeof(uint32_t) * words) != hipSuccess) {
+    if (hipMalloc(&p, sizeof(uint32_t) * (bar_at + ptsg::bar_words(g.S))) != hipSuccess) {
       (void)hipGetLastError();
       return false;
     }
     uint32_t* w = (uint32_t*)p;
-    if (clear_bar(w + snap_words + per) != hipSuccess) {
+    if (clear_bar(w + bar_at) != hipSuccess) {
       (void)hipGetLastError();
       (void)hipFree(p);
       return false;
     }
     spread_mem = p;
     snap = w;
-    Ex = (int32_t*)(w + snap_words);
-    bar = w + snap_words + per;
+    Ex = (int32_t*)(w + Ex_at);
+    bar = w + bar_at;  // (counters in cache lines of their own)
     return true;
   }
   void release() {

@@ -92,31 +92,49 @@ def test_the_shapes_of_the_spread_tests_spread(pt, d, L, S, NT, layout, walk, mo
     job, _ = make(pt, d, L, S, NT, layout=layout, walk=walk, modes=modes)
     assert pt.pt_get_launch(job)["mode"] == -2
     plan = pt.pt_get_plan(job, measure=meas)
-    pt.pt_mcs(job, 1, measure=meas)
+    pt.pt_mcs(job, 3, measure=meas)
     ran = pt.pt_get_launch(job)
     assert ran["mode"] == 3 and ran["parts"] > plan["parts"] and S * ran["parts"] <= cus(), (plan, ran)
     assert ran["parts"] * ran["per_part"] >= 2 * NT > (ran["parts"] - 1) * ran["per_part"]
-    pt.pt_mcs_noalloc(job, 1, measure=meas)
+    pt.pt_mcs_noalloc(job, 3, measure=meas)
     assert pt.pt_get_launch(job) == plan
-    pt.pt_mcs(job, 1, measure=meas, plain=True)
+    pt.pt_mcs(job, 3, measure=meas, plain=True)
     assert pt.pt_get_launch(job)["mode"] == -1
     pt.pt_destroy(job)
 
 
 # just outside the rule: too few attempted flips per step, too few words for two
-# parts, samples on more than half the CUs, Houdayer moves; and just inside it
-@pytest.mark.parametrize("d,L,samples,NT,houdayer,parts", [
-    (3, 8, 8, 31, False, 1), (3, 8, 8, 32, False, 2), (2, 16, 8, 96, False, 1), (2, 64, 4, 4, False, 2), (2, 64, 4, 3, False, 1),
-    (3, 16, "half", 32, False, 2), (3, 16, "more", 32, False, 1), (3, 16, 4, 32, True, 1)])
-def test_where_spreading_begins(pt, d, L, samples, NT, houdayer, parts):
+# parts, samples on more than half the CUs, Houdayer moves, too few steps in the
+# call; and just inside it
+@pytest.mark.parametrize("d,L,samples,NT,steps,houdayer,parts", [
+    (3, 8, 8, 31, 300, False, 1), (3, 8, 8, 32, 300, False, 2), (2, 16, 8, 96, 300, False, 1),
+    (2, 64, 4, 4, 300, False, 2), (2, 64, 4, 3, 300, False, 1), (3, 16, "half", 32, 1, False, 2),
+    (3, 16, "more", 32, 20, False, 1), (3, 16, 4, 32, 20, True, 1), (3, 8, 8, 32, 9, False, 1),
+    (3, 8, 8, 32, 10, False, 4), (3, 16, 2, 16, 1, False, 1), (3, 16, 2, 16, 2, False, 16)])
+def test_where_spreading_begins(pt, d, L, samples, NT, steps, houdayer, parts):
     S = {"half": cus() // 2, "more": cus() // 2 + 1}.get(samples, samples)
     job, _ = make(pt, d, L, S, NT)
-    pt.pt_mcs(job, 1, measure=True, houdayer=houdayer)
-    ran, plan = pt.pt_get_launch(job), pt.pt_get_plan(job, measure=True, houdayer=houdayer)
-    if parts == 1:
-        assert ran == plan
-    else:
-        assert ran["parts"] >= parts
+    for _ in range(2):
+        pt.pt_mcs(job, steps, measure=True, houdayer=houdayer)
+        ran, plan = pt.pt_get_launch(job), pt.pt_get_plan(job, measure=True, houdayer=houdayer)
+        if parts == 1:
+            assert ran == plan
+        else:
+            assert ran["parts"] >= parts
+        pt.pt_mcs(job, 1)                   # another form and other flags between
+    pt.pt_destroy(job)
+
+
+def test_calls_of_few_and_many_steps_mix(pt):
+    """One job's calls take either form by their steps, against the oracle."""
+    job, ref = make(pt, 3, 16, 3, 9, layout=1)
+    plan = pt.pt_get_plan(job, measure=True)
+    for n in (1, 1, 4, 1, 2, 7, 7, 1, 30):
+        pt.pt_mcs(job, n, measure=True)
+        ref.mcs(n, measure=True)
+        ran = pt.pt_get_launch(job)
+        assert ran == plan if n < 2 else ran["parts"] > 1, n
+        same(pt, job, ref)
     pt.pt_destroy(job)
 
 
