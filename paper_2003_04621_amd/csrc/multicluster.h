@@ -32,8 +32,14 @@
 // Bound by the instructions of the rounds (3) and their LDS latency at the
 // wavefronts per CU that the scratch areas allow (ten at 2D L = 64; six with a
 // 32-bit label per site): whole steps at 2D L = 64, 500 samples x 2 x 24, 206 ->
-// 127 us against uniting edge by edge with root searches, 3D L = 12, 100 x 2 x 20,
-// 96 -> 72 us.
+// 127 us against uniting edge by edge with root searches.  3D rows have at most 32
+// sites, so their masks are 32-bit and their edges a byte: with 64-bit masks and
+// 16-bit edges the scratch was larger than that of site labels at half the sizes
+// and many small samples slower than with root searches (us per step, root
+// searches / 64-bit / 32-bit): L = 6, 830 x 2 x 16 67.8 / 73.9 / 67.1; L = 10, 500 x
+// 2 x 16 77.1 / 85.4 / 77.8; L = 12, 100 x 2 x 20 97.9 / 72.8 / 67.3; L = 16, 300 x
+// 2 x 24 456 / 371 / 287; still so L = 4, 1000 x 2 x 16 52.0 / 60.1 / 54.9 (64 x 2 x
+// 24 27.4 / 23.6 / 22.5).
 #pragma once
 #include "device.h"
 
@@ -46,21 +52,38 @@ constexpr int kMultiMaxSites = 32768;
 
 // A row of L <= 64 sites holds at most L/2 runs.  Places for a row's runs and,
 // per direction, its edges (multiples of four), and the labels' row stride S: an
-// odd number of words, so that the rows' labels start in different LDS banks.
+// odd number of words, so that the rows' labels start in different LDS banks
+// (L = 4: just its places).
 __host__ __device__ constexpr int multi_row_places(int L) { return (L / 2 + 3) & ~3; }
-__host__ __device__ constexpr int multi_row_stride(int L) { return (multi_row_places(L) & ~3) + 2; }
+__host__ __device__ constexpr int multi_row_stride(int L) { return multi_row_places(L) + (L > 4 ? 2 : 0); }
+
+// A row's mask and an edge (the two runs' numbers) as held in LDS: a 3D row has
+// at most 32 sites (kMultiMaxSites), so 16 runs.
+template <int D>
+struct MultiRow {
+  using Mask = uint64_t;
+  using Edge = uint16_t;
+  static constexpr int kShift = 8;
+};
+template <>
+struct MultiRow<3> {
+  using Mask = uint32_t;
+  using Edge = uint8_t;
+  static constexpr int kShift = 4;
+};
 
 // LDS words of one team's scratch for geometry g: overlap and cluster words
-// (2 NW each), row masks (64-bit per row), coins (one bit per site, 128-bit
-// blocks), labels, edges and edge counts (16-bit).
+// (2 NW each), row masks, coins (one bit per site, 128-bit blocks), labels
+// (16-bit), edges and edge counts.
 __host__ __device__ constexpr int multi_scratch_words(const Geo& g) {
-  return 4 * g.NW + 2 * g.NR + 4 * ((g.N + 127) / 128) + g.NR * multi_row_stride(g.L) / 2 +
-         (g.NR * (g.d - 1) * (multi_row_places(g.L) + 1) + 1) / 2;
+  const int mask = g.d == 3 ? (int)sizeof(MultiRow<3>::Mask) : (int)sizeof(MultiRow<2>::Mask);
+  const int edge = g.d == 3 ? (int)sizeof(MultiRow<3>::Edge) : (int)sizeof(MultiRow<2>::Edge);
+  return 4 * g.NW + g.NR * mask / 4 + 4 * ((g.N + 127) / 128) + g.NR * multi_row_stride(g.L) / 2 +
+         (g.NR * (g.d - 1) * (multi_row_places(g.L) + 1) * edge + 3) / 4;
 }
 
-// Bit b of x moved to bit 2b (x < 2^32).
-__device__ __forceinline__ uint64_t spread_bits(uint32_t x) {
-  uint64_t v = x;
+// Bit b of x moved to bit 2b, for the lower half of a row mask.
+__device__ __forceinline__ uint64_t spread_bits(uint64_t v) {
   v = (v | (v << 16)) & 0x0000FFFF0000FFFFull;
   v = (v | (v << 8)) & 0x00FF00FF00FF00FFull;
   v = (v | (v << 4)) & 0x0F0F0F0F0F0F0F0Full;
@@ -68,8 +91,15 @@ __device__ __forceinline__ uint64_t spread_bits(uint32_t x) {
   v = (v | (v << 1)) & 0x5555555555555555ull;
   return v;
 }
+__device__ __forceinline__ uint32_t spread_bits(uint32_t v) {
+  v = (v | (v << 8)) & 0x00FF00FFu;
+  v = (v | (v << 4)) & 0x0F0F0F0Fu;
+  v = (v | (v << 2)) & 0x33333333u;
+  v = (v | (v << 1)) & 0x55555555u;
+  return v;
+}
 
-// Bits 2b of x (b < 32) moved to bit b (the inverse of spread_bits).
+// Bits 2b of x moved to bit b (the inverse of spread_bits).
 __device__ __forceinline__ uint32_t compress_even_bits(uint64_t x) {
   x &= 0x5555555555555555ull;
   x = (x | (x >> 1)) & 0x3333333333333333ull;
@@ -79,41 +109,61 @@ __device__ __forceinline__ uint32_t compress_even_bits(uint64_t x) {
   x = (x | (x >> 16)) & 0x00000000FFFFFFFFull;
   return (uint32_t)x;
 }
+__device__ __forceinline__ uint32_t compress_even_bits(uint32_t x) {
+  x &= 0x55555555u;
+  x = (x | (x >> 1)) & 0x33333333u;
+  x = (x | (x >> 2)) & 0x0F0F0F0Fu;
+  x = (x | (x >> 4)) & 0x00FF00FFu;
+  x = (x | (x >> 8)) & 0x0000FFFFu;
+  return x;
+}
+
+__device__ __forceinline__ int mask_count(uint64_t m) { return __popcll(m); }
+__device__ __forceinline__ int mask_count(uint32_t m) { return __popc(m); }
+// Position of the lowest / highest bit (m != 0).
+__device__ __forceinline__ int mask_low(uint64_t m) { return (int)__ffsll((long long)m) - 1; }
+__device__ __forceinline__ int mask_low(uint32_t m) { return __ffs((int)m) - 1; }
+__device__ __forceinline__ int mask_high(uint64_t m) { return 63 - __clzll((long long)m); }
+__device__ __forceinline__ int mask_high(uint32_t m) { return 31 - __clz((int)m); }
 
 // The runs of q = -1 sites of one row (L-bit mask m in x0 order, taken
 // periodically).  starts: bit x0 set iff x0 is q = -1 and x0 - 1 is not; n: the
 // number of runs; wraps: the last start's run continues at x0 = 0.  A row that
 // is q = -1 everywhere has no start and is one run.
+template <typename M>
 struct RowRuns {
-  uint64_t m, starts;
+  M m, starts;
   int n;
   bool wraps;
 };
 
-__device__ __forceinline__ RowRuns row_runs(uint64_t m, int L, uint64_t full) {
-  RowRuns r;
+template <typename M>
+__device__ __forceinline__ RowRuns<M> row_runs(M m, int L, M full) {
+  RowRuns<M> r;
   r.m = m;
   r.starts = m & ~(((m << 1) | (m >> (L - 1))) & full);
-  r.n = r.starts ? __popcll(r.starts) : (m ? 1 : 0);
-  r.wraps = r.starts && (m & 1ull) && ((m >> (L - 1)) & 1ull);
+  r.n = r.starts ? mask_count(r.starts) : (m ? 1 : 0);
+  r.wraps = r.starts && (m & 1u) && ((m >> (L - 1)) & 1u);
   return r;
 }
 
 // Number (in the order of lowest sites) of the run holding q = -1 site x0.
-__device__ __forceinline__ int run_rank(const RowRuns& r, int x0) {
-  const int c = __popcll(r.starts & ((2ull << x0) - 1ull));  // x0 = 63: every bit
+template <typename M>
+__device__ __forceinline__ int run_rank(const RowRuns<M>& r, int x0) {
+  const int c = mask_count((M)(r.starts & (((M)2 << x0) - (M)1)));  // the top site: every bit
   if (r.wraps) return c == r.n ? 0 : c;
   return c > 0 ? c - 1 : 0;
 }
 
 // The q = -1 sites of row R as an L-bit mask in x0 order.
-__device__ __forceinline__ uint64_t row_q_mask(const Geo& g, const uint32_t* Q, int R) {
+template <typename M>
+__device__ __forceinline__ M row_q_mask(const Geo& g, const uint32_t* Q, int R) {
   int w, f;
   row_word(g, R, w, f);
   const int p0 = row_parity(g, R);  // colour of the even-x0 sites
   const uint32_t e = (Q[p0 * g.NW + w] >> (f * g.H)) & g.maskH;
   const uint32_t o = (Q[(1 - p0) * g.NW + w] >> (f * g.H)) & g.maskH;
-  return spread_bits(e) | (spread_bits(o) << 1);
+  return spread_bits((M)e) | (spread_bits((M)o) << 1);
 }
 
 // Rows next to row R in the positive x1 and (3D) x2 directions.
@@ -136,14 +186,17 @@ template <int D, typename Sync, typename Any>
 __device__ __forceinline__ void multi_cluster_words(const Geo& g, const uint32_t* Q, uint32_t* C,
                                                     uint32_t* scr, int s, int k, uint32_t v,
                                                     int t, int T, Sync sync, Any any) {
+  using Mask = typename MultiRow<D>::Mask;
+  using Edge = typename MultiRow<D>::Edge;
+  constexpr int kShift = MultiRow<D>::kShift;
   const int L = g.L, NR = g.NR, N = g.N, NW = g.NW;
   const int nblk = (N + 127) / 128, ME = multi_row_places(L), S = multi_row_stride(L);
-  uint64_t* qr = reinterpret_cast<uint64_t*>(scr);
-  uint32_t* coin = scr + 2 * NR;
+  Mask* qr = reinterpret_cast<Mask*>(scr);
+  uint32_t* coin = scr + NR * (int)(sizeof(Mask) / 4);
   uint16_t* lab = reinterpret_cast<uint16_t*>(coin + 4 * nblk);
-  uint16_t* edge = lab + NR * S;                // edge e of row R, direction j at (j ME + e) NR + R
-  uint16_t* edges = edge + (D - 1) * ME * NR;   // number of them at j NR + R
-  const uint64_t full = L == 64 ? ~0ull : ((1ull << L) - 1ull);
+  Edge* edge = reinterpret_cast<Edge*>(lab + NR * S);  // edge e of row R, direction j at (j ME + e) NR + R
+  Edge* edges = edge + (D - 1) * ME * NR;              // number of them at j NR + R
+  const Mask full = L == 8 * (int)sizeof(Mask) ? ~(Mask)0 : (((Mask)1 << L) - (Mask)1);
   // four consecutive labels of a row (two words)
   typedef uint32_t __attribute__((may_alias)) Word;
   auto load4 = [&](int i, uint32_t (&l)[4]) {
@@ -162,8 +215,7 @@ __device__ __forceinline__ void multi_cluster_words(const Geo& g, const uint32_t
 
   // 1. row masks; every run its own label; coins
   for (int R = t; R < NR; R += T) {
-    const uint64_t m = row_q_mask(g, Q, R);
-    qr[R] = m;
+    qr[R] = row_q_mask<Mask>(g, Q, R);
     for (int r = 0; r < ME; r += 4) {  // unused places too
       const uint32_t i = (uint32_t)(R * S + r);
       store4((int)i, {i, i + 1u, i + 2u, i + 3u});
@@ -181,39 +233,39 @@ __device__ __forceinline__ void multi_cluster_words(const Geo& g, const uint32_t
 
   // 2. one edge per segment of overlap along x1 (and x2), except those that set
   // the upper run's label (only row R's thread writes those of the row above);
-  // edge = the runs' numbers, the lower row's in the low byte
+  // edge = the runs' numbers, the lower row's in the low bits
   for (int R = t; R < NR; R += T) {
-    const uint64_t m = qr[R];
-    const RowRuns rr = row_runs(m, L, full);
+    const Mask m = qr[R];
+    const RowRuns<Mask> rr = row_runs(m, L, full);
     int up[D - 1];
     rows_up(g, R, up);
 #pragma unroll
     for (int j = 0; j < D - 1; ++j) {
-      uint16_t* er = edge + j * ME * NR + R;
-      const uint64_t mu = qr[up[j]];
-      const uint64_t e = m & mu;
-      const RowRuns ru = row_runs(mu, L, full);
+      Edge* er = edge + j * ME * NR + R;
+      const Mask mu = qr[up[j]];
+      const Mask e = m & mu;
+      const RowRuns<Mask> ru = row_runs(mu, L, full);
       // first site of each segment (cyclically); a full overlap is one segment
-      uint64_t first = e & ~(((e << 1) | (e >> (L - 1))) & full);
-      if (e == full) first = 1ull;
+      Mask first = e & ~(((e << 1) | (e >> (L - 1))) & full);
+      if (e == full) first = 1;
       uint32_t set = j == 0 && up[j] > R ? 0u : ~0u;  // runs above that have their label
       int n = 0;
       uint32_t ed = 0;
-      for (; first; first &= first - 1ull) {
-        const int x0 = (int)__ffsll((long long)first) - 1;
+      for (; first; first &= first - (Mask)1) {
+        const int x0 = mask_low(first);
         const uint32_t ra = (uint32_t)run_rank(rr, x0), rb = (uint32_t)run_rank(ru, x0);
         if (!((set >> rb) & 1u)) {
           set |= 1u << rb;
           lab[up[j] * S + rb] = (uint16_t)(R * S + ra);
           continue;
         }
-        ed = ra | (rb << 8);
-        er[n * NR] = (uint16_t)ed;
+        ed = ra | (rb << kShift);
+        er[n * NR] = (Edge)ed;
         ++n;
       }
-      edges[j * NR + R] = (uint16_t)n;
+      edges[j * NR + R] = (Edge)n;
       // the last one again up to a multiple of four: no checks when they are read
-      for (; n & 3; ++n) er[n * NR] = (uint16_t)ed;
+      for (; n & 3; ++n) er[n * NR] = (Edge)ed;
     }
   }
   sync();
@@ -244,7 +296,7 @@ __device__ __forceinline__ void multi_cluster_words(const Geo& g, const uint32_t
       rows_up(g, R, up);
 #pragma unroll
       for (int j = 0; j < D - 1; ++j) {
-        const uint16_t* er = edge + j * ME * NR + R;
+        const Edge* er = edge + j * ME * NR + R;
         const int n = edges[j * NR + R];
         const uint16_t *low = lab + R * S, *high = lab + up[j] * S;
         for (int e0 = 0; e0 < n; e0 += 4) {
@@ -253,8 +305,8 @@ __device__ __forceinline__ void multi_cluster_words(const Geo& g, const uint32_t
           for (int i = 0; i < 4; ++i) ed[i] = er[(e0 + i) * NR];
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            la[i] = low[ed[i] & 0xFFu];
-            lb[i] = high[ed[i] >> 8];
+            la[i] = low[ed[i] & ((1u << kShift) - 1u)];
+            lb[i] = high[ed[i] >> kShift];
           }
 #pragma unroll
           for (int i = 0; i < 4; ++i)
@@ -270,14 +322,14 @@ __device__ __forceinline__ void multi_cluster_words(const Geo& g, const uint32_t
 
   // 4. the roots' coins, then the exchanged sites as colour words
   for (int R = t; R < NR; R += T) {
-    const RowRuns rr = row_runs(qr[R], L, full);
-    uint64_t rest = rr.starts;
+    const RowRuns<Mask> rr = row_runs(qr[R], L, full);
+    Mask rest = rr.starts;
     for (int r = 0; r < rr.n; ++r) {
       const uint32_t name = (uint32_t)(R * S + r);
       int x0 = 0;  // lowest site of run r
       if (rr.starts && !(rr.wraps && r == 0)) {
-        x0 = (int)__ffsll((long long)rest) - 1;
-        rest &= rest - 1ull;
+        x0 = mask_low(rest);
+        rest &= rest - (Mask)1;
       }
       if (lab[name] == name) {
         const uint32_t i = (uint32_t)(R * L + x0);
@@ -291,8 +343,8 @@ __device__ __forceinline__ void multi_cluster_words(const Geo& g, const uint32_t
     uint32_t out[2] = {0u, 0u};
     for (int f = 0; f < g.P; ++f) {
       const int R = word_row(g, q, f);
-      const uint64_t m = qr[R];
-      const RowRuns rr = row_runs(m, L, full);
+      const Mask m = qr[R];
+      const RowRuns<Mask> rr = row_runs(m, L, full);
       uint32_t take = 0;  // bit r: run r is exchanged
       for (int r0 = 0; r0 < rr.n; r0 += 4) {
         uint32_t l[4];
@@ -300,24 +352,24 @@ __device__ __forceinline__ void multi_cluster_words(const Geo& g, const uint32_t
 #pragma unroll
         for (int i = 0; i < 4; ++i) take |= (uint32_t)(lab[l[i] & 0x7FFFu] >> 15) << (r0 + i);
       }
-      uint64_t X = 0;
+      Mask X = 0;
       if (!rr.starts) {
-        X = take ? full : 0ull;
+        X = take ? full : (Mask)0;
       } else {
-        uint64_t St = 0;  // starts of the exchanged runs
+        Mask St = 0;  // starts of the exchanged runs
         uint32_t bits = take;
         if (rr.wraps) {
-          if (take & 1u) St = 1ull | (1ull << (63 - __clzll((long long)rr.starts)));
+          if (take & 1u) St = (Mask)1 | ((Mask)1 << mask_high(rr.starts));
           bits >>= 1;
         }
-        for (uint64_t rest = rr.starts; bits; bits >>= 1, rest &= rest - 1ull)
-          if (bits & 1u) St |= rest & (0ull - rest);
+        for (Mask rest = rr.starts; bits; bits >>= 1, rest &= rest - (Mask)1)
+          if (bits & 1u) St |= rest & ((Mask)0 - rest);
         X = m & ~(m + St);
       }
       if (!X) continue;
       const int p0 = row_parity(g, R);  // colour of the even-x0 sites
       out[p0] |= compress_even_bits(X) << (f * g.H);
-      out[1 - p0] |= compress_even_bits(X >> 1) << (f * g.H);
+      out[1 - p0] |= compress_even_bits((Mask)(X >> 1)) << (f * g.H);
     }
     C[w] = out[0];
     C[NW + w] = out[1];

@@ -12,8 +12,8 @@ def fused(d, L, NT, **kw):
 # (dim, L, longest ladder with room for two areas, one with room for one)
 @pytest.mark.parametrize("d,L,two,one", [
     (2, 14, 362, 365), (2, 28, 355, 360), (2, 32, 335, 340), (2, 50, 152, 158), (2, 64, 118, 122),
-    (2, 64, 118, 127), (3, 10, 288, 296), (3, 12, 150, 160), (3, 16, 105, 119), (3, 18, 51, 67), (3, 22, 4, 11),
-    (3, 24, 7, 18), (3, 26, 1, 3), (3, 28, 1, 7)])
+    (2, 64, 118, 127), (3, 10, 292, 296), (3, 12, 157, 160), (3, 16, 115, 119), (3, 18, 61, 67), (3, 22, 8, 11),
+    (3, 24, 14, 18), (3, 26, 1, 3), (3, 28, 1, 7)])
 def test_one_scratch_area_is_no_plan(d, L, two, one):
     if two >= 2:
         assert fused(d, L, two) and fused(d, L, max(2, two // 2))
@@ -22,5 +22,5 @@ def test_one_scratch_area_is_no_plan(d, L, two, one):
 
 
 def test_the_extras_take_their_room():
-    assert fused(3, 18, 51) and not fused(3, 18, 51, walk=True, modes=True)
-    assert fused(3, 18, 40, walk=True, modes=True)
+    assert fused(3, 18, 61) and not fused(3, 18, 61, walk=True, modes=True)
+    assert fused(3, 18, 56, walk=True, modes=True)
