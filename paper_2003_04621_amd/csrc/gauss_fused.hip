@@ -356,8 +356,19 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) 
   uint32_t* W = lds + lay.W;
   const size_t lat0 = (size_t)s * g.nslot;
 
-  // ---- load the sample's state
-  for (int l = 0; l < NS; ++l) load_lattice(g, spins, lat0 + l, W + (size_t)l * W2, tid, T);
+  // ---- load the sample's state: the words of all lattices over all threads (a
+  // lattice at a time leaves most threads idle and waits for memory NS times)
+  if (g.layout == kLayoutPacked) {
+    const uint32_t* src = static_cast<const uint32_t*>(spins) + lat0 * W2;
+    for (int i = tid; i < NS * W2; i += T) W[i] = src[i];
+  } else {
+    const int8_t* src = static_cast<const int8_t*>(spins) + lat0 * g.N;
+#pragma unroll 2
+    for (int i = tid; i < NS * NW; i += T) {
+      const int l = i / NW, w = i - l * NW;
+      word_from_int8(g, src + (size_t)l * g.N, w, W[(size_t)l * W2 + w], W[(size_t)l * W2 + NW + w]);
+    }
+  }
   for (int i = tid; i < NS; i += T) {
     El[i] = E64[lat0 + i];
     sotl[i] = sot[(size_t)s * NS + i];
@@ -473,7 +484,17 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) 
   }
 
   // ---- store the sample's state
-  for (int l = 0; l < NS; ++l) store_lattice(g, spins, lat0 + l, W + (size_t)l * W2, tid, T);
+  if (g.layout == kLayoutPacked) {
+    uint32_t* dst = static_cast<uint32_t*>(spins) + lat0 * W2;
+    for (int i = tid; i < NS * W2; i += T) dst[i] = W[i];
+  } else {
+    int8_t* dst = static_cast<int8_t*>(spins) + lat0 * g.N;
+#pragma unroll 2
+    for (int i = tid; i < NS * NW; i += T) {
+      const int l = i / NW, w = i - l * NW;
+      word_to_int8(g, dst + (size_t)l * g.N, w, W[(size_t)l * W2 + w], W[(size_t)l * W2 + NW + w]);
+    }
+  }
   for (int i = tid; i < NS; i += T) {
     E64[lat0 + i] = El[i];
     sot[(size_t)s * NS + i] = sotl[i];
