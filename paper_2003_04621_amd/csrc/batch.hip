@@ -753,11 +753,7 @@ pt_batch* batch_new(hipStream_t st, bool may_spread) {
   if (!b) return nullptr;
   b->may_spread = may_spread;
   b->stream = st;
-  int dev = 0, ncu = 0;
-  if (hipGetDevice(&dev) == hipSuccess &&
-      hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && ncu > 0)
-    b->ncu = ncu;
-  (void)hipGetLastError();
+  b->ncu = device_cus();
   return b;
 }
 
@@ -891,6 +887,14 @@ void job_items(const pt_job* j, uint32_t flags, int& items, double& item_flips) 
 
 int batch_slots(const pt_batch* b) { return b->ncu; }
 
+int device_cus() {
+  int dev = 0, ncu = 0;
+  const bool ok = hipGetDevice(&dev) == hipSuccess &&
+                  hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess;
+  (void)hipGetLastError();
+  return ok && ncu > 0 ? ncu : 256;
+}
+
 void batch_free(pt_batch* b) {
   if (!b) return;
   drop_graph(b);
@@ -926,11 +930,7 @@ PT_API int pt_batch_create(pt_job* const* jobs, int32_t n, pt_batch** out) {
   b->d = d;
   b->stream = jobs[0]->stream;
   b->use.hold(b->stream);
-  int dev = 0, ncu = 0;
-  if (hipGetDevice(&dev) == hipSuccess &&
-      hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && ncu > 0)
-    b->ncu = ncu;
-  (void)hipGetLastError();
+  b->ncu = device_cus();
   *out = b;
   return PT_OK;
 }

@@ -41,8 +41,7 @@ struct GaussLayout {
 // two would not fit the LDS, else two of 512.  (One team of 256 to 512 threads
 // whatever the sample count, as before: 3D L = 10, 150 samples x 2 x 15, 55 us
 // per step against 25 us, the chip holding one wavefront per SIMD.)
-constexpr int kCUs = 256;
-int gauss_fused_threads(const Geo& g, GaussLayout& l);
+int gauss_fused_threads(const Geo& g, int cus, GaussLayout& l);
 
 GaussLayout gauss_layout(const Geo& g, int nwave) {
   GaussLayout l{};
@@ -78,10 +77,10 @@ size_t gauss_least_lds(const Geo& g) {
   return sizeof(uint32_t) * (size_t)(l.acc >= 0 ? l.sot0 : l.words);
 }
 
-int gauss_fused_threads(const Geo& g, GaussLayout& l) {
+int gauss_fused_threads(const Geo& g, int cus, GaussLayout& l) {
   const int groups = (gauss_groups(g) + 63) / 64 * 64, configs = g.d == 2 ? g.NT : 2 * g.NT;
   for (int most : {512, 1024}) {
-    if (most == 512 && g.S <= kCUs) continue;
+    if (most == 512 && g.S <= cus) continue;
     const int team = std::min(most, groups);
     const int threads = std::max(256, team * std::min(most / team, configs));
     l = gauss_layout(g, threads / 64);
@@ -507,9 +506,9 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4))) 
 template <int D, bool HOU, bool MEAS>
 hipError_t launch_gfused(const Geo& g, void* spins, const int4* Jg, int64_t* E64, int32_t* sot,
                          int32_t* tos, const double* beta, const float* cz, int64_t* mom,
-                         const DevCounters* ctr, int n, int every, hipStream_t st) {
+                         const DevCounters* ctr, int n, int every, int cus, hipStream_t st) {
   GaussLayout lay;
-  const int threads = gauss_fused_threads(g, lay);
+  const int threads = gauss_fused_threads(g, cus, lay);
   const size_t lds = sizeof(uint32_t) * (size_t)lay.words;
   auto k = k_gfused<D, HOU, MEAS>;
   if (lds > 65536) {
@@ -523,21 +522,21 @@ hipError_t launch_gfused(const Geo& g, void* spins, const int4* Jg, int64_t* E64
 
 }  // namespace
 
-size_t gauss_fused_lds(const Geo& g) {
+size_t gauss_fused_lds(const Geo& g, int cus) {
   const size_t least = gauss_least_lds(g);
   if (least > kGaussFusedMaxLds) return least;
   GaussLayout lay;
-  gauss_fused_threads(g, lay);
+  gauss_fused_threads(g, cus, lay);
   return sizeof(uint32_t) * (size_t)lay.words;
 }
 
 hipError_t launch_gauss_fused(const Geo& g, void* spins, const int4* Jg, int64_t* E64, int32_t* sot,
                               int32_t* tos, const double* beta, const float* cz, int64_t* mom,
-                              const DevCounters* ctr, int n, bool hou, bool meas, int every,
+                              const DevCounters* ctr, int n, bool hou, bool meas, int every, int cus,
                               hipStream_t st) {
-  if (gauss_fused_lds(g) > kGaussFusedMaxLds) return hipErrorInvalidValue;
+  if (gauss_fused_lds(g, cus) > kGaussFusedMaxLds) return hipErrorInvalidValue;
 #define PTSG_GF(DD, HH, MM) \
-  return launch_gfused<DD, HH, MM>(g, spins, Jg, E64, sot, tos, beta, cz, mom, ctr, n, every, st)
+  return launch_gfused<DD, HH, MM>(g, spins, Jg, E64, sot, tos, beta, cz, mom, ctr, n, every, cus, st)
   if (g.d == 3) {
     if (hou) {
       if (meas) PTSG_GF(3, true, true);

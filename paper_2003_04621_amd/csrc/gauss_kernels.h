@@ -39,10 +39,11 @@ hipError_t launch_gauss_measure(const Geo& g, const void* spins, const int64_t* 
 // hipErrorInvalidValue if the sample does not fit (gauss_fused_lds above
 // kGaussFusedMaxLds).
 constexpr size_t kGaussFusedMaxLds = 160 * 1024;
-size_t gauss_fused_lds(const Geo& g);
+// (on a device of `cus` compute units)
+size_t gauss_fused_lds(const Geo& g, int cus);
 hipError_t launch_gauss_fused(const Geo& g, void* spins, const int4* Jg, int64_t* E64, int32_t* sot,
                               int32_t* tos, const double* beta, const float* cz, int64_t* mom,
-                              const DevCounters* ctr, int n, bool hou, bool meas, int every,
+                              const DevCounters* ctr, int n, bool hou, bool meas, int every, int cus,
                               hipStream_t st);
 // Acceptance decisions of device arrays (tests): mode 0 Metropolis tiers,
 // 1 exchange tiers, 2 double-double alone.

@@ -82,8 +82,9 @@ struct pt_job {
   void* spread_mem = nullptr;
   // Gaussian couplings (pt_init_gauss): integer units, 64-bit energies, the
   // per-group coupling data of gauss.h and the inverse temperatures; thr,
-  // thrpt, jw and E stay null for such a job
+  // thrpt, jw and E stay null for such a job; the compute units of its device
   bool gauss = false;
+  int ncu = 256;
   int32_t* gJn = nullptr;    // [S][d][N] coupling units
   int4* gJ = nullptr;        // [S][2][2d+1][NGc]
   int64_t* E64 = nullptr;    // [S][2NT]
@@ -214,6 +215,8 @@ int job_plan_mode(const pt_job* j, uint32_t flags);
 void job_items(const pt_job* j, uint32_t flags, int& items, double& item_flips);
 // Compute units of the batch's device (workgroup slots of a one-per-CU plan).
 int batch_slots(const pt_batch* b);
+// Compute units of the current device (256 if it does not say).
+int device_cus();
 // Whether a job of this shape needs the split-sample scratch (its two
 // replica sets do not fit one workgroup together, but a split plan exists),
 // and how many bytes that scratch takes.

@@ -109,11 +109,11 @@ void plan_report(const pt_job* job, uint32_t flags, int32_t* out4) {
   if (job->gauss) {
     // fused: one workgroup per sample (gauss_fused.hip); else per-step kernels
     const bool fused = !(flags & (PT_MCS_PLAIN | PT_MCS_MULTICLUSTER)) &&
-                       gauss_fused_lds(g) <= kGaussFusedMaxLds;
+                       gauss_fused_lds(g, job->ncu) <= kGaussFusedMaxLds;
     out4[0] = fused ? 0 : -1;
     out4[1] = fused ? 1 : 0;
     out4[2] = fused ? g.nslot : 0;
-    out4[3] = fused ? (int32_t)gauss_fused_lds(g) : 0;
+    out4[3] = fused ? (int32_t)gauss_fused_lds(g, job->ncu) : 0;
     return;
   }
   const int mode = (flags & PT_MCS_PLAIN) ? -1 : job_plan_mode(job, flags);
@@ -487,6 +487,7 @@ PT_API int pt_init_gauss(pt_job** out, int32_t samples, int32_t replicas, int32_
   job->alloc_ctx = g_ctx;
   job->gauss = true;
   job->use.hold(job->stream);
+  job->ncu = device_cus();
   job->g = make_geo(samples, replicas, L, dim, (int)flags, seed);
   const Geo& g = job->g;
   const size_t maps = sizeof(int32_t) * (size_t)samples * 2 * replicas;
@@ -748,7 +749,7 @@ int mcs_per_step(pt_job* job, int32_t n, uint32_t flags) {
 // one workgroup's LDS.
 bool gauss_fused_ok(const pt_job* job, uint32_t flags) {
   return job->gauss && !(flags & (PT_MCS_PLAIN | PT_MCS_MULTICLUSTER)) &&
-         gauss_fused_lds(job->g) <= kGaussFusedMaxLds;
+         gauss_fused_lds(job->g, job->ncu) <= kGaussFusedMaxLds;
 }
 
 // n fused steps of a Gaussian job, in launches of at most 500 steps, each
@@ -761,7 +762,7 @@ int mcs_gauss_fused(pt_job* job, int32_t n, uint32_t flags) {
     const uint32_t m = (uint32_t)((n - done) < chunk ? (n - done) : chunk);
     PT_HIP(job, launch_gauss_fused(job->g, job->spins, job->gJ, job->E64, job->sot, job->tos,
                                    job->gbeta, job->gcz, job->mom, job->ctr, (int)m, hou, meas,
-                                   job->meas_every, job->stream));
+                                   job->meas_every, job->ncu, job->stream));
     // n_meas: m measurements at interval 1, else one per multiple of the
     // interval among the m sweep numbers (CounterStep's rule)
     const uint32_t every = (uint32_t)job->meas_every;
