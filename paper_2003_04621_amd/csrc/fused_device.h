@@ -244,8 +244,10 @@ __device__ __forceinline__ void modes_resident(const Geo& g, const FusedLayout& 
     }
   wave_lds_sync();
   // delta < L/2: one delta a lane, all axes' pairs in a row cut over the
-  // 64 >> sh (at least two) copies of that lane range.  A copy's sum stays
-  // below 48 * 2 * 2^24.
+  // 64 >> sh (at least two) copies of that lane range: 48 of the 96 pairs at most
+  // in a copy's sum.
+  constexpr long long kPair = 2ll * (1 << 12) * (1 << 12);  // L <= 64: |P| <= 2^12
+  static_assert(48 * kPair < 1ll << 31 && 96 * (kPair / 4) < 1ll << 31, "mode sums in 32 bits");
   const Short2* pairs = reinterpret_cast<const Short2*>(cnt);
   const int sh = 32 - __clz(half - 1), dl = lane & ((1 << sh) - 1), all = g.d * half;
   const int chunk = (all + (64 >> sh) - 1) >> (6 - sh);

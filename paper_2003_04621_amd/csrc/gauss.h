@@ -30,6 +30,12 @@ namespace ptsg {
 
 constexpr int kGaussUnitBits = 16;       // J = n 2^-16
 constexpr int32_t kGaussMaxUnits = 1 << 19;  // |J| <= 8
+// What 32 bits have to hold: twice a local field exactly as a float (the
+// acceptance tiers), a wavefront's local fields of a group of four sites a lane
+// (the sweep's energies), the boundary bonds of a 2D row, each -2n (Houdayer moves).
+static_assert(2ll * 6 * kGaussMaxUnits < 1ll << 24, "local fields as floats");
+static_assert(64ll * 4 * 6 * kGaussMaxUnits < 1ll << 31, "wavefront sums of local fields");
+static_assert(32ll * 4 * (2ll * kGaussMaxUnits + 1) < 1ll << 31, "a row's energy change");
 
 // Groups of four same-colour sites per colour of a lattice.
 __host__ __device__ constexpr int gauss_groups(const Geo& g) {

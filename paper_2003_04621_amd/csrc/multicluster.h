@@ -72,6 +72,18 @@ struct MultiRow<3> {
   static constexpr int kShift = 4;
 };
 
+// A label is a run's name, below NR S, with a coin in its top bit; an edge holds
+// two numbers of runs, L / 2 at most.
+constexpr bool multi_fits() {
+  for (int L = 4; L <= 64; L += 2) {
+    if (L * multi_row_stride(L) > 0x8000 || L / 2 > 1 << MultiRow<2>::kShift) return false;
+    if (L * L * L > kMultiMaxSites) continue;
+    if (L * L * multi_row_stride(L) > 0x8000 || L > 32 || L / 2 > 1 << MultiRow<3>::kShift) return false;
+  }
+  return true;
+}
+static_assert(multi_fits(), "names, masks and edges of the multi-cluster labels");
+
 // LDS words of one team's scratch for geometry g: overlap and cluster words
 // (2 NW each), row masks, coins (one bit per site, 128-bit blocks), labels
 // (16-bit), edges and edge counts.
