@@ -454,7 +454,8 @@ int pt_batch_set_stream(pt_batch *b, void *hip_stream);
 
 /* mcs Monte Carlo steps of every job (Sec. 2.4), flags as pt_mcs
  * (PT_MCS_HOUDAYER, PT_MCS_MEASURE) plus PT_BATCH_GRAPH: the launch
- * (queue reset, persistent kernel, counter advance) is captured once as a
+ * (one persistent kernel, whose last workgroup advances the counters and
+ * leaves the queue at zero for the next) is captured once as a
  * hipGraph per (mcs, flags, configuration) and replayed; the device counters
  * make every replay continue the random-number streams.  Workgroups take
  * (job, sample, replica sets) items from a device queue, largest first by

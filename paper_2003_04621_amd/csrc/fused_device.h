@@ -43,8 +43,9 @@ __device__ __forceinline__ void wave_lds_sync() {
 // carried up from below: with the pre-pass map m0, the configuration at
 // position k before step k is m0[j] for some j <= k, and b = m0[k+1].  All
 // candidate decisions (c, k, j) are evaluated in parallel and kept as bits
-// (one wavefront ballot per 64 of them), then one lane per set walks the
-// chain.
+// (exchange_decide: half a wavefront per row (c, k) up to 32 temperatures, a
+// wavefront above), then a wavefront per set follows the chain by ballots
+// (exchange_chain: one lane per set above 64 temperatures).
 // ---------------------------------------------------------------------------
 // The inputs of pass u that the step's sweep and Houdayer move do not change:
 // the map before the pass and one Philox word per (set, k).  Written before

@@ -693,9 +693,13 @@ int check_mcs(pt_job* job, int32_t n, uint32_t flags) {
 }
 
 // n Monte Carlo steps as separate kernels, one launch per step and kernel
-// (no scratch, no allocation).  Within one step every counter is read by
-// exactly one kernel, so a single advance per step keeps the numbering of
-// the separate entry points.
+// (no scratch, no allocation).  A step advances each counter once, so that the
+// numbering is that of the separate entry points, and never in a kernel some of
+// whose workgroups may still have to read it.  +-J steps: the exchange kernel
+// reads u and advances t and v (read by the sweep and the Houdayer kernel, which
+// have ended); the measurement reads t, already advanced, and advances u and
+// n_meas, or without one a launch of its own advances u.  Gaussian steps: one
+// advance of all four at the end, the measurement reading t before it.
 int mcs_per_step(pt_job* job, int32_t n, uint32_t flags) {
   hipStream_t st = job->stream;
   plan_report(job, flags | PT_MCS_PLAIN, job->ran);
