@@ -512,13 +512,18 @@ int build_worklist_ex(pt_batch* b, const std::vector<int>& steps, const std::vec
 // 9.6; at the line, 3D L = 8, 8 x 2 x 32: 10.8 / 9.3.
 //
 // A call pays for the spread form once (more workgroups to start, in a measuring
-// call also the parts' moments brought together) and gains per step the flips
-// that a workgroup no longer makes, less a meeting of all of them; in flips of one
-// workgroup (0.125 ns each) fitted to 28 shapes of 3D L = 8 to 48 and 2D L = 28 to
-// 64, calls of 1 to 40 steps.  Measured calls of 1 / 4 / 40 steps, own plan against spread
-// (us): 2D L = 32, 60 x 2 x 24: 23.2 / 34.6, 52.6 / 61.0, 408 / 387; 3D L = 8, 100 x
-// 2 x 32: 24.3 / 35.6, 53.8 / 65.4, 413 / 427; 3D L = 24, 60 x 2 x 8: 48.3 / 42.1,
-// 147 / 83, 1331 / 575.
+// call also the parts' moments brought together), less the share of an int8 job's
+// spins that a workgroup then need not pack and unpack (byte by byte where 4 does
+// not divide L), and gains per step the flips that a workgroup no longer makes, a
+// little more where the rows have an odd number of a colour's sites, less a meeting
+// of all parts; in flips of one workgroup (0.125 ns each) fitted to 64 shapes, 3D
+// L = 8 to 48 and 2D L = 28 to 64, 1 to 120 samples, both layouts, calls of 1 to 16
+// steps back to back: of 960 calls 14 take the form that is more than 3% slower,
+// none by more than 11%.  Own plan against spread (us): measured calls of 1 / 4 / 16 steps, packed,
+// 2D L = 32, 60 x 2 x 24: 23.0 / 34.3, 52.7 / 60.6, 172 / 169; 3D L = 8, 100 x 2 x
+// 32: 24.1 / 35.5, 53.8 / 64.8, 174 / 186; 3D L = 24, 60 x 2 x 8: 48.6 / 42.2, 147 /
+// 83, 541 / 249; unmeasured of 1 step, 1 x 2 x 24: 3D L = 12 packed 29.7 / 25.1,
+// int8 36.1 / 26.6; L = 14 48.8 / 25.3, 73.6 / 27.1.
 constexpr double kSpreadFlips = 8192;
 SpreadRule spread_rule(const pt_job* j, uint32_t flags, int ncu) {
   SpreadRule none, r;
@@ -532,10 +537,13 @@ SpreadRule spread_rule(const pt_job* j, uint32_t flags, int ncu) {
   if (p < (mode == 3 ? has + 1 : 2 * has)) return none;
   if (!split_plan(g, r.plan, j->track_walk, j->track_modes, p) || r.plan.parts <= has) return none;
   const int parts = r.plan.parts;
-  const double gain = flips * (1.0 / has - 1.0 / parts) - (16000 + 25.0 * g.S * parts);
-  const double once = flags & PT_MCS_MEASURE ? 60000 + 3500.0 * parts : 36000 + 2500.0 * parts;
+  const bool odd = g.H % 2;
+  const double saved = flips * (1.0 / has - 1.0 / parts);
+  const double gain = (odd ? 1.2 : 1.0) * saved - (15000 + 45.0 * g.S * parts);
+  const double load = g.layout == kLayoutInt8 ? (odd ? 2.25 : 0.2) * saved : 0;
+  const double once = (flags & PT_MCS_MEASURE ? 62000 + 3500.0 * parts : 20000 + 3000.0 * parts) - load;
   if (gain <= 0) return none;
-  r.from = (int)std::min(std::ceil(once / gain), 1e9);
+  r.from = (int)std::min(std::max(std::ceil(once / gain), 1.0), 1e9);
   return r;
 }
 

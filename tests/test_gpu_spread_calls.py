@@ -109,8 +109,9 @@ def test_the_shapes_of_the_spread_tests_spread(pt, d, L, S, NT, layout, walk, mo
 @pytest.mark.parametrize("d,L,samples,NT,steps,houdayer,parts", [
     (3, 8, 8, 31, 300, False, 1), (3, 8, 8, 32, 300, False, 2), (2, 16, 8, 96, 300, False, 1),
     (2, 64, 4, 4, 300, False, 2), (2, 64, 4, 3, 300, False, 1), (3, 16, "half", 32, 1, False, 2),
-    (3, 16, "more", 32, 20, False, 1), (3, 16, 4, 32, 20, True, 1), (3, 8, 8, 32, 9, False, 1),
-    (3, 8, 8, 32, 10, False, 4), (3, 16, 2, 16, 1, False, 1), (3, 16, 2, 16, 2, False, 16)])
+    (3, 16, "more", 32, 20, False, 1), (3, 16, 4, 32, 20, True, 1), (3, 8, 8, 32, 8, False, 1),
+    (3, 8, 8, 32, 9, False, 4), (3, 16, 2, 10, 1, False, 1), (3, 16, 2, 10, 2, False, 10),
+    (3, 14, 1, 24, 1, False, 16)])
 def test_where_spreading_begins(pt, d, L, samples, NT, steps, houdayer, parts):
     S = {"half": cus() // 2, "more": cus() // 2 + 1}.get(samples, samples)
     job, _ = make(pt, d, L, S, NT)
