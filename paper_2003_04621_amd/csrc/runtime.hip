@@ -207,6 +207,16 @@ int host_word_row(const Geo& g, int w, int f) {
   return f * g.B + w;
 }
 
+// Whether n couplings or spins are all +1 or -1: (c + 1) & ~2 is 0 for these only.
+// Without a branch each, which the processor cannot predict and whose cost moved
+// with the code's place: pt_init's 408 samples of 3D L = 12, 10 ms -> 0.08;
+// pt_set_spins of 2D L = 64, 364 x 2 x 2, 16.1-18.5 ms -> 0.28.
+bool all_units(const int8_t* c, size_t n) {
+  uint8_t bad = 0;
+  for (size_t i = 0; i < n; ++i) bad |= (uint8_t)((uint8_t)c[i] + 1u) & (uint8_t)~2u;
+  return bad == 0;
+}
+
 // int8 lattices <-> colour words (pt_get_spins / pt_set_spins, packed layout)
 void pack_host(const Geo& g, const int8_t* in, uint32_t* out) {
   const size_t nlat = (size_t)g.S * g.nslot;
@@ -305,11 +315,7 @@ int job_create(pt_job** out, int32_t samples, int32_t replicas, int32_t L, int32
   }
   const long N = (dim == 3) ? (long)L * L * L : (long)L * L;
   const long ncoup = (long)samples * dim * N;
-  // (c + 1) & ~2 is 0 for c = 1 and -1 only; without a branch per coupling, which
-  // the processor cannot predict: 408 samples of 3D L = 12, 10 ms -> 0.08 ms
-  uint8_t bad = 0;
-  for (long i = 0; i < ncoup; ++i) bad |= (uint8_t)((uint8_t)couplings[i] + 1u) & (uint8_t)~2u;
-  if (bad) return pt_fail(PT_EINVAL, "couplings must be +1 or -1");
+  if (!all_units(couplings, (size_t)ncoup)) return pt_fail(PT_EINVAL, "couplings must be +1 or -1");
   const long nlat = (long)samples * 2 * replicas;
   if (nlat > 0x7FFFFFFFL || (long)samples * replicas > 0x7FFFFFFFL)
     return pt_fail(PT_EINVAL, "too many lattices for one job");
@@ -924,8 +930,7 @@ PT_API int pt_set_spins(pt_job* job, const int8_t* in) {
   if (!in) return pt_fail(PT_EINVAL, "null input");
   const Geo& g = job->g;
   const size_t n = (size_t)g.S * g.nslot * g.N;
-  for (size_t i = 0; i < n; ++i)
-    if (in[i] != 1 && in[i] != -1) return pt_fail(PT_EINVAL, "spins must be +1 or -1");
+  if (!all_units(in, n)) return pt_fail(PT_EINVAL, "spins must be +1 or -1");
   if (g.layout == kLayoutPacked) {
     std::vector<uint32_t> tmp(job->spin_bytes() / sizeof(uint32_t));
     pack_host(g, in, tmp.data());
