@@ -514,16 +514,19 @@ int build_worklist_ex(pt_batch* b, const std::vector<int>& steps, const std::vec
 // A call pays for the spread form once (more workgroups to start, in a measuring
 // call also the parts' moments brought together), less the share of an int8 job's
 // spins that a workgroup then need not pack and unpack (byte by byte where 4 does
-// not divide L), and gains per step the flips that a workgroup no longer makes, a
-// little more where the rows have an odd number of a colour's sites, less a meeting
-// of all parts; in flips of one workgroup (0.125 ns each) fitted to 64 shapes, 3D
-// L = 8 to 48 and 2D L = 28 to 64, 1 to 120 samples, both layouts, calls of 1 to 16
-// steps back to back: of 960 calls 14 take the form that is more than 3% slower,
-// none by more than 11%.  Own plan against spread (us): measured calls of 1 / 4 / 16 steps, packed,
-// 2D L = 32, 60 x 2 x 24: 23.0 / 34.3, 52.7 / 60.6, 172 / 169; 3D L = 8, 100 x 2 x
-// 32: 24.1 / 35.5, 53.8 / 64.8, 174 / 186; 3D L = 24, 60 x 2 x 8: 48.6 / 42.2, 147 /
-// 83, 541 / 249; unmeasured of 1 step, 1 x 2 x 24: 3D L = 12 packed 29.7 / 25.1,
-// int8 36.1 / 26.6; L = 14 48.8 / 25.3, 73.6 / 27.1.
+// not divide L).  It gains per step the flips that a workgroup no longer makes, less
+// a meeting of all parts: words of up to 12 sites take longer per flip, the two-replica
+// modes are cut over the parts too, and seven wavefronts or fewer (kFew words of
+// a colour) take one time however few words they have, latency.  In flips of one
+// workgroup (0.125 ns each), fitted to 450 shapes, 3D L = 6 to 48 and 2D L = 16 to 64,
+// 1 to 128 samples, both layouts, with and without walk and modes, calls of 1 to 16
+// steps back to back: of 6624 calls 125 take a form more than 3% slower than the
+// other, 37 more than 8%.  Own plan against spread (us): measured calls of 1 / 4 /
+// 16 steps, packed, 2D L = 32, 60 x 2 x 24: 23.0 / 34.3, 52.7 / 60.6, 172 / 169; 3D
+// L = 8, 100 x 2 x 32: 24.1 / 35.5, 53.8 / 64.8, 174 / 186; 3D L = 24, 60 x 2 x 8: 48.6 /
+// 42.2, 147 / 83, 541 / 249; unmeasured of 1 step, 1 x 2 x 24: 3D L = 12 packed
+// 29.7 / 25.1, int8 36.1 / 26.6; L = 14 48.8 / 25.3, 73.6 / 27.1; measured of 12,
+// few words: 3D L = 16, 3 x 2 x 4: 91.8 / 112.5.
 constexpr double kSpreadFlips = 8192;
 SpreadRule spread_rule(const pt_job* j, uint32_t flags, int ncu) {
   SpreadRule none, r;
@@ -537,11 +540,14 @@ SpreadRule spread_rule(const pt_job* j, uint32_t flags, int ncu) {
   if (p < (mode == 3 ? has + 1 : 2 * has)) return none;
   if (!split_plan(g, r.plan, j->track_walk, j->track_modes, p) || r.plan.parts <= has) return none;
   const int parts = r.plan.parts;
-  const bool odd = g.H % 2;
-  const double saved = flips * (1.0 / has - 1.0 / parts);
-  const double gain = (odd ? 1.2 : 1.0) * saved - (15000 + 45.0 * g.S * parts);
-  const double load = g.layout == kLayoutInt8 ? (odd ? 2.25 : 0.2) * saved : 0;
-  const double once = (flags & PT_MCS_MEASURE ? 62000 + 3500.0 * parts : 20000 + 3000.0 * parts) - load;
+  constexpr double kFew = 448;
+  const bool measure = flags & PT_MCS_MEASURE;
+  const double words = (double)g.nslot * g.NW, share = flips * (1.0 / has - 1.0 / parts);
+  const double saved = flips / words * (std::max(words / has, kFew) - std::max(words / parts, kFew));
+  const double gain = (g.P * g.H <= 12 ? 1.2 : 1.0) * saved + (measure && j->track_modes ? 0.1 * share : 0) -
+                      (measure ? 9000 + 65.0 * g.S * parts : 6000 + 25.0 * g.S * parts);
+  const double load = g.layout == kLayoutInt8 ? (g.L % 4 ? 2.25 : 0.4) * share : 0;
+  const double once = (measure ? 78000 + 1500.0 * parts : 27000 + 2750.0 * parts) - load;
   if (gain <= 0) return none;
   r.from = (int)std::min(std::max(std::ceil(once / gain), 1.0), 1e9);
   return r;

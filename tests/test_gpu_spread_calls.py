@@ -104,13 +104,14 @@ def test_the_shapes_of_the_spread_tests_spread(pt, d, L, S, NT, layout, walk, mo
 
 
 # just outside the rule: too few attempted flips per step, too few words for two
-# parts, samples on more than half the CUs, Houdayer moves, too few steps in the
-# call; and just inside it
+# parts or to fill one workgroup's wavefronts, samples on more than half the CUs,
+# Houdayer moves, too few steps in the call; and just inside it
 @pytest.mark.parametrize("d,L,samples,NT,steps,houdayer,parts", [
     (3, 8, 8, 31, 300, False, 1), (3, 8, 8, 32, 300, False, 2), (2, 16, 8, 96, 300, False, 1),
-    (2, 64, 4, 4, 300, False, 2), (2, 64, 4, 3, 300, False, 1), (3, 16, "half", 32, 1, False, 2),
-    (3, 16, "more", 32, 20, False, 1), (3, 16, 4, 32, 20, True, 1), (3, 8, 8, 32, 8, False, 1),
-    (3, 8, 8, 32, 9, False, 4), (3, 16, 2, 10, 1, False, 1), (3, 16, 2, 10, 2, False, 10),
+    (2, 64, 4, 4, 300, False, 1), (2, 64, 4, 8, 2, False, 1), (2, 64, 4, 8, 3, False, 8),
+    (3, 16, "half", 32, 1, False, 2),
+    (3, 16, "more", 32, 20, False, 1), (3, 16, 4, 32, 20, True, 1), (3, 8, 8, 32, 10, False, 1),
+    (3, 8, 8, 32, 11, False, 4), (3, 16, 2, 10, 1, False, 1), (3, 16, 2, 10, 2, False, 10),
     (3, 14, 1, 24, 1, False, 16)])
 def test_where_spreading_begins(pt, d, L, samples, NT, steps, houdayer, parts):
     S = {"half": cus() // 2, "more": cus() // 2 + 1}.get(samples, samples)
@@ -130,11 +131,11 @@ def test_calls_of_few_and_many_steps_mix(pt):
     """One job's calls take either form by their steps, against the oracle."""
     job, ref = make(pt, 3, 16, 3, 9, layout=1)
     plan = pt.pt_get_plan(job, measure=True)
-    for n in (1, 1, 4, 1, 2, 7, 7, 1, 30):
+    for n in (1, 1, 4, 1, 2, 3, 7, 7, 1, 30):
         pt.pt_mcs(job, n, measure=True)
         ref.mcs(n, measure=True)
         ran = pt.pt_get_launch(job)
-        assert ran == plan if n < 2 else ran["parts"] > 1, n
+        assert ran == plan if n < 3 else ran["parts"] > 1, n
         same(pt, job, ref)
     pt.pt_destroy(job)
 
